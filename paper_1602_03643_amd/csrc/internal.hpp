@@ -42,6 +42,7 @@ inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s);
 struct Tuning {
     int storage = OASIS_STORAGE_AUTO;
     int grid_cap = kMaxPartials / 4;   // 512: two blocks per CU, one round
+    bool grid_auto = true;             // the caller left the grid to the library
     int cg_form = OASIS_CG_FORM_AUTO;
     bool ell() const { return storage != OASIS_STORAGE_CSR; }
     bool dict() const { return storage == OASIS_STORAGE_AUTO; }
@@ -58,6 +59,7 @@ struct Tuning {
             if (t->grid_cap != 0 && (t->grid_cap < 64 || t->grid_cap > kMaxPartials)) return OASIS_EINVAL;
             v.storage = t->storage;
             v.cg_form = t->cg_form;
+            v.grid_auto = t->grid_cap == 0;
             if (t->grid_cap) v.grid_cap = t->grid_cap;
         }
         *out = v;
@@ -103,10 +105,45 @@ inline int grid_for(long long work, int per_block, int cap = kMaxPartials) {
 // ---------------------------------------------------------------------------
 // device reductions (fixed order => bitwise deterministic)
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+// The value of another lane of the same 16-lane row, moved by the VALU's
+// data-parallel primitives.  A shuffle goes through the LDS crossbar (two
+// ds_bpermute per double, some 60 cycles each step of the butterfly); these
+// moves take a few cycles, and the reductions are a serial chain at both
+// ends of every solver kernel.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;            // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;   // within 8 and within 16 lanes
+constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;     // a row's last lane into the next row(s)
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ int dpp_move(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ float dpp_move(float v) {
+    return __int_as_float(dpp_move<CTRL, ROWS>(__float_as_int(v)));
+}
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ double dpp_move(double v) {
+    return __hiloint2double(dpp_move<CTRL, ROWS>(__double2hiint(v)), dpp_move<CTRL, ROWS>(__double2loint(v)));
+}
+
+// Sum over the 16 lanes of a row; every lane gets it.  (The mirrors meet
+// values that are already equal within a quad or an octet.)
+template <typename T>
+__device__ __forceinline__ T row_sum(T v) {
+    v += dpp_move<kDppXor1>(v);
+    v += dpp_move<kDppXor2>(v);
+    v += dpp_move<kDppHalfMirror>(v);
+    v += dpp_move<kDppMirror>(v);
     return v;
+}
+
+// Sum over the wave (all lanes active); every lane gets it.
+__device__ __forceinline__ double wave_sum(double v) {
+    v = row_sum(v);
+    v += dpp_move<kDppBcast15, 0xa>(v);   // rows 1 and 3 add rows 0 and 2
+    v += dpp_move<kDppBcast31, 0xc>(v);   // rows 2 and 3 add lane 31's half
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), kWave - 1),
+                            __builtin_amdgcn_readlane(__double2loint(v), kWave - 1));
 }
 
 // Sum NV values over the block; every thread receives the totals.

@@ -31,10 +31,15 @@ struct RowCfg {
 __device__ __forceinline__ constexpr bool xcd_mapping() { return OASIS_XCD_MAP != 0; }
 
 // Sum over the L lanes of a group (L divides 64); all lanes get the sum.
+// The group's lanes are active or idle together.
 template <int L, typename T>
 __device__ __forceinline__ T group_sum(T v) {
+    if constexpr (L >= 2) v += dpp_move<kDppXor1>(v);
+    if constexpr (L >= 4) v += dpp_move<kDppXor2>(v);
+    if constexpr (L >= 8) v += dpp_move<kDppHalfMirror>(v);
+    if constexpr (L >= 16) v += dpp_move<kDppMirror>(v);
 #pragma unroll
-    for (int o = L / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, L);
+    for (int o = 16; o < L; o <<= 1) v += __shfl_xor(v, o, L);
     return v;
 }
 
