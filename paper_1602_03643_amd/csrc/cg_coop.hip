@@ -1,0 +1,512 @@
+// A run of CG iterations in one launch, for systems whose rows fit one per
+// thread of a resident grid (at most 1024 rows per CU: 262,144 on gfx950).
+//
+// What bounds the two-kernel iteration at these sizes is not the matrix but
+// the launches: on the 65x65x49 channel (199,680 rows, FP64) an iteration
+// took 20 us in k_cg_p1_ell (12 us) and k_cg_p2 (6.4 us) and the gaps
+// between them, against about 4 us that its 33 MB need at the cache rates; on the
+// 1089-row Taylor-Green square each launch took 3.9 us for no work at all.
+// Here a cooperative grid of 1024-thread blocks, one per CU, keeps the
+// matrix (values and local column indices) and the CG vectors in registers
+// and each block's part of the direction, with the neighbours' entries it
+// gathers, in LDS.  The recurrences are those of k_cg_p1 / k_cg_p2.
+//
+// An iteration has two grid-wide exchanges.  The first carries the new
+// residual's entries and the partials of r.r together: with beta known,
+// every block forms the direction of its own rows and of its halo (the
+// columns its rows reference outside its range) by the same fused
+// multiply-add, so the direction itself is never sent.  The second carries
+// the partials of p.q.  A value that crosses blocks is one agent-scope
+// atomic store into a slot that held the empty mark, and a reader polls the
+// slot itself: no flag and no fence.  (An agent-scope fence writes back and
+// invalidates the L2 and cost 38 us per barrier here; the polled exchange of
+// two doubles between 256 blocks costs 1.5 us.  Words that carry a 32-bit
+// number of the exchange beside 32 bits of payload need no emptying, but
+// twice the polled words, and took 3.4 us.)
+//
+// An exchange has three buffers, used in turn by the iterations.  In
+// iteration e a block empties its slots of iteration e + 2; they hold those
+// of iteration e - 1, which every block has read, since all have sent a
+// later exchange that this block has seen.  It waits for the emptying stores
+// before it sends anything of iteration e + 1, so whoever polls for
+// iteration e + 2, having seen all of e + 1, finds the slots empty or
+// filled, never old.
+//
+// The cooperative launch guarantees that all blocks are resident, so every
+// wait ends; each is bounded by the clock all the same.
+//
+// Per iteration, before and now: 65x65x49 FP64 20.0 -> 5.7 us (256 blocks,
+// 780 rows each: about 1.7 us for each exchange, 0.4 us for the product, the
+// rest block reductions, barriers and two divisions), FP32 with the null
+// vector 12 -> 6.2 us, 33x33x25 FP32 9.5 -> 4.7 us, 17x17x13 FP64 12 -> 3.8
+// us, the 1089-row square 8 -> 3.3 us.
+#include <algorithm>
+
+#include "krylov.hpp"
+
+namespace oasis {
+
+namespace {
+
+using u64 = unsigned long long;
+
+constexpr int kCoopThreads = 1024;             // most threads of a block
+constexpr int kCoopBlocks = 256;               // most blocks: the slot readers' four waves
+constexpr int kCoopMaxRows = kCoopBlocks * kCoopThreads;
+constexpr int kBitWords = kCoopMaxRows / 32;
+constexpr long long kCoopTicks = 200000000ll;  // 2 s of the 100 MHz wall clock
+constexpr int kCoopLost = 5, kCoopUnfit = 6;   // CGState::flag: a wait ran out; too wide a halo
+
+// The exchanged words: a T's bits, or the empty mark, a NaN that no sent
+// value has (every NaN is sent as the quiet one).
+template <typename T>
+struct Word;
+template <>
+struct Word<float> {
+    using U = unsigned;
+    static constexpr U kEmpty = 0xffffbeefu, kNan = 0x7fc00000u;
+    static __device__ __forceinline__ U of(float v) { return v == v ? __float_as_uint(v) : kNan; }
+    static __device__ __forceinline__ float value(U u) { return __uint_as_float(u); }
+};
+template <>
+struct Word<double> {
+    using U = u64;
+    static constexpr U kEmpty = 0xffffdeadbeef0001ull, kNan = 0x7ff8000000000000ull;
+    static __device__ __forceinline__ U of(double v) {
+        return v == v ? static_cast<U>(__double_as_longlong(v)) : kNan;
+    }
+    static __device__ __forceinline__ double value(U u) { return __longlong_as_double(static_cast<long long>(u)); }
+};
+template <typename U>
+__device__ __forceinline__ U word_load(const U *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename U>
+__device__ __forceinline__ void word_store(U *p, U v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// all of this thread's earlier stores have reached memory
+__device__ __forceinline__ void stores_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }   // vmcnt(0)
+
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+struct CoopArgs {
+    int n, rows;           // rows per block
+    EllCols cols;
+    const void *eval;
+    const void *cur;       // RP pairs (r, p_old) entering iteration it0
+    void *nxt[2];          // the pairs of either parity; (r, p) leave to that of the next iteration
+    void *x;
+    const void *wgt, *vnull;
+    CGState *st;
+    int it0, m, beta_zero;
+    void *ex[3];           // exchanged residual entries, n words of T each
+    u64 *slots[2];         // exchanged partials, first and second value
+};
+
+// Partial slots of a value: [exchange kind][buffer][copy][block].  A block sends each value
+// to eight copies and reads the one of its XCD: 256 readers of the same 2 KB
+// wait for each other (2.5 us an exchange, 1.7 us with the copies).
+constexpr int kCopies = kXcds;
+constexpr int kSlotWords = 2 * 3 * kCopies * kCoopBlocks;
+__device__ __forceinline__ int slot_set(int kind, int buf) { return (kind * 3 + buf) * kCopies * kCoopBlocks; }
+
+// BS: threads of a block, and the most rows it has.
+template <typename T, int BS>
+__global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
+    constexpr int E = kEll;
+    constexpr int kCoopWaves = BS / kWave;
+    constexpr int kCoopHaloPer = BS >= 1024 ? 4 : 8;   // halo entries per thread at most
+    constexpr int kCoopHalo = kCoopHaloPer * BS;
+    constexpr size_t kSetup = kBitWords * sizeof(unsigned) + kBitWords * sizeof(unsigned short);
+    constexpr size_t kDir = (BS + kCoopHalo) * sizeof(T);
+    // the bitmap of referenced columns (set-up) and the direction (iterations)
+    __shared__ __align__(16) unsigned char shared[kSetup > kDir ? kSetup : kDir];
+    __shared__ int halo[kCoopHalo];
+    // [exchange kind][value]: the block's waves' sums and the grid's totals
+    __shared__ double red[2][2][kCoopWaves], all[2][2];
+    __shared__ int scan[kCoopWaves];
+    __shared__ int quit;
+    const int t = threadIdx.x, wv = t / kWave, wl = t & (kWave - 1);
+    const int nb = gridDim.x, bid = blockIdx.x;
+    const int r0 = bid * a.rows, r1 = min(a.n, r0 + a.rows);
+    const int row = r0 + t;
+    const bool own = row < r1;                 // this thread has a row
+    const int at = own ? row : r0;             // a valid row for the loads
+    CGState *st = a.st;
+    if (t == 0) quit = 0;
+
+    // columns, and the bitmap of those outside the block's range
+    unsigned *bits = reinterpret_cast<unsigned *>(shared);
+    unsigned short *rank = reinterpret_cast<unsigned short *>(shared + kBitWords * sizeof(unsigned));
+    const int nw = (a.n + 31) / 32;
+    for (int w = t; w < nw; w += BS) bits[w] = 0u;
+    __syncthreads();
+    int c[E];
+    T val[E];
+    {
+        const short *off = a.cols.offsets(at);
+        const T *ev = static_cast<const T *>(a.eval) + static_cast<size_t>(at) * kEll;
+#pragma unroll
+        for (int g = 0; g < E / 4; ++g) {
+            const short4 d = *reinterpret_cast<const short4 *>(off + 4 * g);
+            c[4 * g] = ell_col(at, d.x, a.n);
+            c[4 * g + 1] = ell_col(at, d.y, a.n);
+            c[4 * g + 2] = ell_col(at, d.z, a.n);
+            c[4 * g + 3] = ell_col(at, d.w, a.n);
+            T v[4];
+            load4(ev + 4 * g, v);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) val[4 * g + k] = own ? v[k] : T(0);
+        }
+    }
+    if (own) {
+#pragma unroll
+        for (int k = 0; k < E; ++k)
+            if (c[k] < r0 || c[k] >= r1) atomicOr(&bits[c[k] >> 5], 1u << (c[k] & 31));
+    }
+    __syncthreads();
+    // ranks: halo entries in ascending column order
+    int nh = 0;
+    {
+        constexpr int PER = kBitWords / BS;
+        int cnt[PER], sum = 0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int w = t * PER + k;
+            cnt[k] = w < nw ? __popc(bits[w]) : 0;
+            sum += cnt[k];
+        }
+        int inc = sum;
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int up = __shfl_up(inc, o, kWave);
+            if (wl >= o) inc += up;
+        }
+        if (wl == kWave - 1) scan[wv] = inc;
+        __syncthreads();
+        int base = inc - sum;
+        for (int w = 0; w < kCoopWaves; ++w) {
+            if (w < wv) base += scan[w];
+            nh += scan[w];
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int w = t * PER + k;
+            if (w < nw) {
+                rank[w] = static_cast<unsigned short>(min(base, 65535));
+                unsigned b = bits[w];
+                int q = base;
+                while (b) {
+                    const int j = __builtin_ctz(b);
+                    b &= b - 1;
+                    if (q < kCoopHalo) halo[q] = w * 32 + j;
+                    ++q;
+                }
+                base = q;
+            }
+        }
+    }
+    __syncthreads();
+    if (nh > kCoopHalo) {
+        // not a system for this kernel: nothing has been sent, so no block
+        // gets past its first exchange, and the host takes the other kernels
+        if (t == 0) atomicMax(&st->flag, kCoopUnfit);
+        return;
+    }
+    unsigned idx[E / 2];
+#pragma unroll
+    for (int k = 0; k < E; k += 2) {
+        unsigned both[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int cc = c[k + q];
+            const bool in = cc >= r0 && cc < r1;
+            const int w = cc >> 5;
+            const int h = in || !own ? 0 : rank[w] + __popc(bits[w] & ((1u << (cc & 31)) - 1u));
+            both[q] = !own ? 0u : in ? cc - r0 : BS + h;
+        }
+        idx[k / 2] = both[0] | (both[1] << 16);
+    }
+    __syncthreads();
+    T *dir = reinterpret_cast<T *>(shared);
+
+    const RP<T> *cur = static_cast<const RP<T> *>(a.cur);
+    T *xg = static_cast<T *>(a.x);
+    const T *vn = static_cast<const T *>(a.vnull);
+    RP<T> me = cur[at];
+    T x = xg[at];
+    const double wgt = static_cast<double>(static_cast<const T *>(a.wgt)[at]);
+    const T v = vn ? vn[at] : T(0);
+    T r = me.r, p = a.beta_zero ? T(0) : me.p;
+#pragma unroll
+    for (int k = 0; k < kCoopHaloPer; ++k) {
+        const int h = t + k * BS;
+        if (h < nh) dir[BS + h] = a.beta_zero ? T(0) : cur[halo[h]].p;
+    }
+    const double tol2 = st->tol2, upd2 = st->upd2;
+    double rr_prev = st->rr[(a.it0 + 1) & 1];
+    using W = Word<T>;
+    using D = Word<double>;
+    const int nv1 = vn ? 2 : 1;                // values of the second exchange
+
+    // ask again, with the clock as a bound, while again() says so
+    auto poll = [&](auto &&again) {
+        if (!again()) return;
+        const long long began = wall_clock64();
+        int k = 0;
+        while (again()) {
+            if ((++k & 63) == 0 &&
+                (__hip_atomic_load(&st->flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopLost ||
+                 wall_clock64() - began > kCoopTicks)) {
+                quit = 1;
+                return;
+            }
+        }
+    };
+    int buf = 0, spare = 2;                    // buffers of this iteration and of the one after next
+    // wave 0's slots: lanes 0..7 send the first value's copies, 8..15 the second's
+    u64 *mine = (wl < kCopies ? a.slots[0] : a.slots[1]) + (wl & (kCopies - 1)) * kCoopBlocks + bid;
+    const u64 *from0 = a.slots[0] + (bid & (kCopies - 1)) * kCoopBlocks + wl;
+    const u64 *from1 = a.slots[1] + (bid & (kCopies - 1)) * kCoopBlocks + wl;
+    // the block's sums of nv values, sent as its slots of an exchange
+    auto give = [&](double s0, double s1, int nv, int kind) {
+        s0 = wave_sum(s0);
+        if (nv > 1) s1 = wave_sum(s1);
+        if (wl == 0) {
+            red[kind][0][wv] = s0;
+            red[kind][1][wv] = s1;
+        }
+        __syncthreads();
+        if (wv == 0) {
+            const double u0 = row_sum(wl < kCoopWaves ? red[kind][0][wl] : 0.0);
+            const double u1 = nv > 1 ? row_sum(wl < kCoopWaves ? red[kind][1][wl] : 0.0) : 0.0;
+            if (wl < nv * kCopies) {
+                word_store(mine + slot_set(kind, buf), D::of(wl < kCopies ? u0 : u1));
+                word_store(mine + slot_set(kind, spare), D::kEmpty);
+            }
+        }
+    };
+    // every block's slots, read by wave 0 and summed in a fixed order; after
+    // the next barrier the totals are in `all`
+    auto take = [&](int nv, int kind) {
+        if (wv != 0) return;
+        constexpr int PER = kCoopBlocks / kWave;
+        u64 u0[PER], u1[PER];
+        const u64 *p0 = from0 + slot_set(kind, buf), *p1 = from1 + slot_set(kind, buf);
+        poll([&] {
+            bool miss = false;
+#pragma unroll
+            for (int k = 0; k < PER; ++k)
+                if (wl + k * kWave < nb) {
+                    u0[k] = word_load(p0 + k * kWave);
+                    if (nv > 1) u1[k] = word_load(p1 + k * kWave);
+                }
+#pragma unroll
+            for (int k = 0; k < PER; ++k)
+                if (wl + k * kWave < nb) miss |= u0[k] == D::kEmpty || (nv > 1 && u1[k] == D::kEmpty);
+            return miss;
+        });
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (wl + k * kWave < nb) {
+                s0 += D::value(u0[k]);
+                if (nv > 1) s1 += D::value(u1[k]);
+            }
+        s0 = wave_sum(s0);
+        if (nv > 1) s1 = wave_sum(s1);
+        if (wl == 0) {
+            all[kind][0] = s0;
+            all[kind][1] = nv > 1 ? s1 : 0.0;
+        }
+    };
+
+    int flag = 0, it = a.it0;
+    double rr = 0.0, wrr = 0.0;
+    for (; it < a.it0 + a.m; ++it) {
+        typename W::U *ex = static_cast<typename W::U *>(a.ex[buf]);
+        stores_done();
+        if (own) {
+            word_store(static_cast<typename W::U *>(a.ex[spare]) + row, W::kEmpty);
+            word_store(ex + row, W::of(r));
+        }
+        const double rd = r;
+        give(own ? rd * rd : 0.0, own ? wgt * rd * rd : 0.0, 2, 0);
+        typename W::U hw[kCoopHaloPer];
+        poll([&] {
+            bool miss = false;
+#pragma unroll
+            for (int k = 0; k < kCoopHaloPer; ++k) {
+                const int h = t + k * BS;
+                if (h < nh) hw[k] = word_load(ex + halo[h]);
+            }
+#pragma unroll
+            for (int k = 0; k < kCoopHaloPer; ++k)
+                if (t + k * BS < nh) miss |= hw[k] == W::kEmpty;
+            return miss;
+        });
+        take(2, 0);
+        __syncthreads();
+        if (quit) break;
+        rr = all[0][0];
+        wrr = all[0][1];
+        if (!finite(wrr) || !finite(rr))
+            flag = 3;
+        else if (wrr <= tol2)
+            flag = 1;
+        else if (wrr <= upd2)
+            flag = 4;
+        if (flag) break;
+        const bool fresh = a.beta_zero && it == a.it0;
+        const T beta = fresh ? T(0) : static_cast<T>(rr / rr_prev);
+        rr_prev = rr;
+        p = fresh ? r : fma_t(beta, p, r);
+        if (own) dir[t] = p;
+#pragma unroll
+        for (int k = 0; k < kCoopHaloPer; ++k) {
+            const int h = t + k * BS;
+            if (h < nh) {
+                const T rh = W::value(hw[k]);
+                dir[BS + h] = fresh ? rh : fma_t(beta, dir[BS + h], rh);
+            }
+        }
+        __syncthreads();
+        T q = T(0);
+#pragma unroll
+        for (int k = 0; k < E; k += 2) {
+            q += val[k] * dir[idx[k / 2] & 0xffffu];
+            q += val[k + 1] * dir[idx[k / 2] >> 16];
+        }
+        give(own ? static_cast<double>(p) * static_cast<double>(q) : 0.0,
+             own ? static_cast<double>(v) * static_cast<double>(q) : 0.0, nv1, 1);
+        take(nv1, 1);
+        __syncthreads();
+        if (quit) break;
+        const double pq = all[1][0], vq = all[1][1];
+        if (!(pq > 0.0) || !finite(pq)) {
+            flag = finite(pq) ? 2 : 3;
+            break;
+        }
+        const T al = static_cast<T>(rr / pq), cv = static_cast<T>(vq);
+        x += al * p;
+        r -= al * (vn ? q - cv * v : q);
+        spare = buf;
+        buf = buf == 2 ? 0 : buf + 1;
+    }
+    if (quit) {
+        if (t == 0) atomicMax(&st->flag, kCoopLost);
+        return;
+    }
+    if (own) {
+        xg[row] = x;
+        static_cast<RP<T> *>(a.nxt[it & 1])[row] = RP<T>{r, p};
+    }
+    if (bid == 0 && t == 0) {
+        const int last = flag ? it : it - 1;   // the last iteration whose residual was seen
+        if (flag) {
+            st->flag = flag;
+            st->it_done = it;
+            if (flag != 2) st->wrr = wrr;
+        }
+        if (!flag || flag == 2) {
+            st->rr[last & 1] = rr;
+            st->wrr_it = wrr;
+            st->it_last = last;
+        } else {
+            st->rr[(it + 1) & 1] = rr_prev;
+        }
+    }
+}
+
+// every exchange slot empty
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_words_clear(int n, CoopArgs a) {
+    using W = Word<T>;
+    const int step = gridDim.x * blockDim.x, i0 = blockIdx.x * blockDim.x + threadIdx.x;
+    for (int k = 0; k < 3; ++k)
+        for (int i = i0; i < n; i += step) static_cast<typename W::U *>(a.ex[k])[i] = W::kEmpty;
+    for (int i = i0; i < kSlotWords; i += step) a.slots[0][i] = a.slots[1][i] = Word<double>::kEmpty;
+}
+
+}  // namespace
+
+template <typename T>
+bool cg_coop_fits(int n, const CGWork<T> &w) {
+    // one row per thread of one block per CU; the kernel and grid the caller
+    // asked for by name are left as they are
+    if (w.coop_off || !w.cols.any() || !w.eval || !w.tun.ell() || w.tun.cg_form != OASIS_CG_FORM_AUTO ||
+        !w.tun.grid_auto || n > kCoopMaxRows)
+        return false;
+    int dev = 0, cu = 0, coop = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess)
+        return false;
+    return coop != 0 && n <= static_cast<long long>(std::min(cu, kCoopBlocks)) * kCoopThreads;
+}
+
+template <typename T>
+int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T *vnull, int it0, int m, bool beta_zero) {
+    int dev = 0, cu = 0;
+    OASIS_TRY_HIP(hipGetDevice(&dev));
+    OASIS_TRY_HIP(hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev));
+    // as many blocks as there are, down to 256 rows each: fewer rows per
+    // block shorten the gathers, and the exchange hardly depends on the grid
+    // (1.4 us between 32 blocks, 1.5 us between 256)
+    const int most = std::min(cu, kCoopBlocks);
+    const int grid = std::min(most, (n + kBlock - 1) / kBlock);
+    CoopArgs a{};
+    a.n = n;
+    a.rows = (n + grid - 1) / grid;
+    a.cols = w.cols;
+    a.eval = w.eval;
+    a.cur = w.pair[it0 & 1];
+    // the exchanged words live in the second halves of the two CG records
+    // (the pairs use the first ones) and in the partial arrays, which this
+    // form does not use
+    for (int k = 0; k < 2; ++k) a.nxt[k] = w.pair[k];
+    a.ex[0] = reinterpret_cast<T *>(w.pair[0] + n);
+    a.ex[1] = reinterpret_cast<T *>(w.pair[0] + n) + n;
+    a.ex[2] = reinterpret_cast<T *>(w.pair[1] + n);
+    a.x = x;
+    a.wgt = wgt;
+    a.vnull = vnull;
+    a.st = w.st;
+    a.it0 = it0;
+    a.m = m;
+    a.beta_zero = beta_zero ? 1 : 0;
+    a.slots[0] = reinterpret_cast<u64 *>(w.partA);
+    a.slots[1] = reinterpret_cast<u64 *>(w.partB);
+    hipLaunchKernelGGL(k_words_clear<T>, dim3(grid_for(n, kBlock, 1024)), dim3(kBlock), 0, s, n, a);
+    OASIS_TRY_LAUNCH();
+    void *args[] = {&a};
+    const void *kern;
+    int bs;
+    if (a.rows <= 256) {
+        kern = reinterpret_cast<const void *>(&k_cg_coop<T, 256>);
+        bs = 256;
+    } else if (a.rows <= 512) {
+        kern = reinterpret_cast<const void *>(&k_cg_coop<T, 512>);
+        bs = 512;
+    } else {
+        kern = reinterpret_cast<const void *>(&k_cg_coop<T, 1024>);
+        bs = 1024;
+    }
+    const hipError_t e = hipLaunchCooperativeKernel(kern, dim3(grid), dim3(bs), args, 0, s);
+    if (e != hipSuccess) {
+        // refused (nothing has run): the caller takes the other kernels
+        (void)hipGetLastError();
+        return OASIS_EUNSUPPORTED;
+    }
+    return OASIS_OK;
+}
+
+template bool cg_coop_fits<double>(int, const CGWork<double> &);
+template bool cg_coop_fits<float>(int, const CGWork<float> &);
+template int cg_coop_run<double>(hipStream_t, int, CGWork<double> &, double *, const double *, const double *, int,
+                                 int, bool);
+template int cg_coop_run<float>(hipStream_t, int, CGWork<float> &, float *, const float *, const float *, int, int,
+                                bool);
+
+}  // namespace oasis

@@ -869,42 +869,69 @@ static int cg_run(hipStream_t s, int n, const int *rp, const int *ci, const T *v
     };
     OASIS_TRY(residual(0, 0));
     if (sr) OASIS_TRY(loop.start(0, false));
+    bool coop = sizeof(T) == 8 && cg_coop_fits(n, w);
     CGState h;
-    OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
     ChunkPlan plan(check_every);
-    plan.restart(h.wrr, 0, h.tol2);
+    // a cooperative run tests the start residual itself
+    if (!coop) {
+        OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
+        plan.restart(h.wrr, 0, h.tol2);
+    }
     int it = 0, restart_at = 0;
     int rc = OASIS_OK;
     auto finish = [&](double wrr, double wbb) {
         out.rel_res = wbb > 0.0 ? std::sqrt(wrr / wbb) : std::sqrt(wrr);
     };
+    // the other kernels go on from the explicit residual
+    auto leave_coop = [&](int at) -> int {
+        coop = false;
+        w.coop_off = true;
+        restart_at = at;
+        return residual(1, at);
+    };
     while (true) {
-        const int m = std::min(plan.next, maxit - it);
-        for (int j = 0; j < m; ++j) {
-            const int itj = it + j;
-            // after a restart the incoming partials are k_cg_init's (3 per block)
-            const bool fresh = itj == restart_at;
-            if (sr) {
-                loop.iterate(itj, fresh ? 1 : 0, x);
-                OASIS_TRY_LAUNCH();
+        const int m = std::min(coop ? (check_every > 0 ? check_every : kCoopRun) : plan.next, maxit - it);
+        if (coop && m > 0) {
+            const int rcc = cg_coop_run<T>(s, n, w, x, wgt, nullptr, it, m, it == restart_at);
+            if (rcc == OASIS_EUNSUPPORTED) {
+                OASIS_TRY(leave_coop(it));
                 continue;
             }
-            const int nin = fresh ? gi : g.p2, stride = fresh ? 3 : 2;
-            if (ell)
-                launch_p1_ell<T, BS>(s, cap, n, w.cols, w.eval, w.pair[itj & 1], w.pair[(itj + 1) & 1], w.q,
-                                     w.partB, nin, stride, w.st, itj, fresh ? 1 : 0, static_cast<const T *>(nullptr),
-                                     w.partA);
-            else
-                hipLaunchKernelGGL((k_cg_p1<T, C, BS>), dim3(g1), dim3(BS), 0, s, n, rp, ci, val,
-                                   w.pair[itj & 1], w.pair[(itj + 1) & 1], w.q, w.partB, nin, stride, w.st, itj,
-                                   fresh ? 1 : 0, static_cast<const T *>(nullptr), w.partA);
-            OASIS_TRY_LAUNCH();
-            hipLaunchKernelGGL((k_cg_p2<T, BS>), dim3(g.p2), dim3(BS), 0, s, n, w.pair[(itj + 1) & 1], w.q, x,
-                               wgt, w.partA, g1, w.st, itj, static_cast<const T *>(nullptr), w.partB);
-            OASIS_TRY_LAUNCH();
+            OASIS_TRY(rcc);
+        } else {
+            for (int j = 0; j < m; ++j) {
+                const int itj = it + j;
+                // after a restart the incoming partials are k_cg_init's (3 per block)
+                const bool fresh = itj == restart_at;
+                if (sr) {
+                    loop.iterate(itj, fresh ? 1 : 0, x);
+                    OASIS_TRY_LAUNCH();
+                    continue;
+                }
+                const int nin = fresh ? gi : g.p2, stride = fresh ? 3 : 2;
+                if (ell)
+                    launch_p1_ell<T, BS>(s, cap, n, w.cols, w.eval, w.pair[itj & 1], w.pair[(itj + 1) & 1], w.q,
+                                         w.partB, nin, stride, w.st, itj, fresh ? 1 : 0, static_cast<const T *>(nullptr),
+                                         w.partA);
+                else
+                    hipLaunchKernelGGL((k_cg_p1<T, C, BS>), dim3(g1), dim3(BS), 0, s, n, rp, ci, val,
+                                       w.pair[itj & 1], w.pair[(itj + 1) & 1], w.q, w.partB, nin, stride, w.st, itj,
+                                       fresh ? 1 : 0, static_cast<const T *>(nullptr), w.partA);
+                OASIS_TRY_LAUNCH();
+                hipLaunchKernelGGL((k_cg_p2<T, BS>), dim3(g.p2), dim3(BS), 0, s, n, w.pair[(itj + 1) & 1], w.q, x,
+                                   wgt, w.partA, g1, w.st, itj, static_cast<const T *>(nullptr), w.partB);
+                OASIS_TRY_LAUNCH();
+            }
         }
         it += m;
         OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
+        if (h.flag == 5) return OASIS_EHIP;
+        if (h.flag == 6) {
+            // no iteration has run
+            it -= m;
+            OASIS_TRY(leave_coop(it));
+            continue;
+        }
         if (h.flag == 0) {
             if (it < maxit) {
                 plan.observe(h.wrr_it, h.it_last, h.tol2);
@@ -1000,7 +1027,9 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
     const int gv = grid_for(n, kBlock, cap);                  // k_cg_cast, k_add_lo
     const CgGrids<BS> g = CgGrids<BS>::template make<C>(n, cap);
     const bool ell = w.cols.any() && w.eval && w.tun.ell();
-    const bool sr = ell && w.tun.single(4);
+    // cooperative runs keep the (r, p) pairs of the two-kernel form
+    bool coop = cg_coop_fits(n, w);
+    bool sr = ell && w.tun.single(4) && !coop;
     SrLoop<float> loop(s, n, w, wgt32, vnull, vscale);
     const int g1 = ell ? launch_p1_ell<float, BS>(s, cap, n, w.cols, w.eval, nullptr, nullptr, nullptr, nullptr, 0,
                                                   2, nullptr, 0, 0, nullptr, nullptr, true)
@@ -1050,31 +1079,60 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
     plan.restart(h.wrr, 0, std::max(h.upd2, tol2));
     int it = 0, restart_at = 0, nin = gv;     // partials of k_cg_cast first, then of k_cg_p2
     int rc = OASIS_OK;
+    // the single-reduction (or two-kernel) iterations go on from the FP64
+    // residual with a fresh direction
+    auto leave_coop = [&](int at) -> int {
+        coop = false;
+        w.coop_off = true;
+        sr = ell && w.tun.single(4);
+        restart_at = at;
+        OASIS_TRY(fold());
+        OASIS_TRY(replace(1));
+        return cast(at, false);
+    };
     while (true) {
-        const int m = std::min(plan.next, maxit - it);
-        for (int j = 0; j < m; ++j) {
-            const int itj = it + j;
-            if (sr) {
-                loop.iterate(itj, itj == restart_at ? 1 : 0, xlo);
-                OASIS_TRY_LAUNCH();
+        const int m = std::min(coop ? (check_every > 0 ? check_every : kCoopRun) : plan.next, maxit - it);
+        if (coop && m > 0) {
+            const int rcc = cg_coop_run<float>(s, n, w, xlo, wgt32, vnull, it, m, it == restart_at);
+            if (rcc == OASIS_EUNSUPPORTED) {
+                OASIS_TRY(leave_coop(it));
+                nin = gv;
                 continue;
             }
-            const int ni = j == 0 ? nin : g.p2;
-            if (ell)
-                launch_p1_ell<float, BS>(s, cap, n, w.cols, w.eval, w.pair[itj & 1], w.pair[(itj + 1) & 1], w.q,
-                                         w.partB, ni, 2, w.st, itj, itj == restart_at ? 1 : 0, vnull, w.partA);
-            else
-                hipLaunchKernelGGL((k_cg_p1<float, C, BS>), dim3(g1), dim3(BS), 0, s, n, rp, ci, val32,
-                                   w.pair[itj & 1], w.pair[(itj + 1) & 1], w.q, w.partB, ni, 2, w.st, itj,
-                                   itj == restart_at ? 1 : 0, vnull, w.partA);
-            OASIS_TRY_LAUNCH();
-            hipLaunchKernelGGL((k_cg_p2<float, BS>), dim3(g.p2), dim3(BS), 0, s, n, w.pair[(itj + 1) & 1], w.q,
-                               xlo, wgt32, w.partA, g1, w.st, itj, vnull, w.partB);
-            OASIS_TRY_LAUNCH();
+            OASIS_TRY(rcc);
+        } else {
+            for (int j = 0; j < m; ++j) {
+                const int itj = it + j;
+                if (sr) {
+                    loop.iterate(itj, itj == restart_at ? 1 : 0, xlo);
+                    OASIS_TRY_LAUNCH();
+                    continue;
+                }
+                const int ni = j == 0 ? nin : g.p2;
+                if (ell)
+                    launch_p1_ell<float, BS>(s, cap, n, w.cols, w.eval, w.pair[itj & 1], w.pair[(itj + 1) & 1], w.q,
+                                             w.partB, ni, 2, w.st, itj, itj == restart_at ? 1 : 0, vnull, w.partA);
+                else
+                    hipLaunchKernelGGL((k_cg_p1<float, C, BS>), dim3(g1), dim3(BS), 0, s, n, rp, ci, val32,
+                                       w.pair[itj & 1], w.pair[(itj + 1) & 1], w.q, w.partB, ni, 2, w.st, itj,
+                                       itj == restart_at ? 1 : 0, vnull, w.partA);
+                OASIS_TRY_LAUNCH();
+                hipLaunchKernelGGL((k_cg_p2<float, BS>), dim3(g.p2), dim3(BS), 0, s, n, w.pair[(itj + 1) & 1], w.q,
+                                   xlo, wgt32, w.partA, g1, w.st, itj, vnull, w.partB);
+                OASIS_TRY_LAUNCH();
+            }
         }
         it += m;
         nin = g.p2;
         OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
+        if (h.flag == 5) return OASIS_EHIP;
+        if (h.flag == 6) {
+            // no iteration has run
+            it -= m;
+            OASIS_TRY(leave_coop(it));
+            nin = gv;
+            continue;
+        }
         if (h.flag == 2 || h.flag == 3) {
             OASIS_TRY(fold());
             out.iters = h.it_done;

@@ -15,7 +15,8 @@ struct CGState {
     double wrr;        // weighted ||r||^2 seen by the last finalize
     double upd2;       // mixed precision: replace the residual once wrr <= upd2
     int flag;          // 0 running, 1 converged candidate, 2 breakdown, 3 non-finite,
-                       // 4 residual replacement due (mixed precision)
+                       // 4 residual replacement due (mixed precision),
+                       // 5, 6 a cooperative run that was lost or that does not fit (cg_coop.hip)
     int it_done;       // iteration index at which flag was raised
     double wrr_it;     // weighted r.r entering iteration it_last (the last one that ran)
     int it_last;
@@ -55,6 +56,7 @@ struct CGWork {
     const T *eval = nullptr;
     Tuning tun;
     HostStage stage;   // the owner's read-back block (may be null)
+    bool coop_off = false;   // the pattern's halo is too wide for cooperative runs
 };
 
 struct BiState {
@@ -157,6 +159,18 @@ int cg_mixed_solve(hipStream_t s, int n, const int *rp, const int *ci, const dou
                    double vscale, const double *b, double *x, double rtol, double delta, int maxit,
                    int check_every, bool time_kernel, CGWork<float> &w, float *xlo, double *rhi,
                    SolveOut &out);
+
+// Cooperative CG runs (cg_coop.hip): up to m iterations in one launch on
+// the (r, p) pairs, from iteration it0, with k_cg_p1 / k_cg_p2's recurrences,
+// tests and state; beta_zero starts a fresh direction.  cg_coop_fits: whether
+// the system, the device and the tuning allow them.  cg_coop_run:
+// EUNSUPPORTED when the launch was refused.
+template <typename T>
+bool cg_coop_fits(int n, const CGWork<T> &w);
+template <typename T>
+int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T *vnull, int it0, int m, bool beta_zero);
+// Iterations of one cooperative run at most (it stops by itself).
+constexpr int kCoopRun = 4096;
 
 // Longest row of a CSR pattern (synchronises; tmp: one device int).
 int csr_max_row(hipStream_t s, int n, const int *rp, int *tmp, int *out);
