@@ -157,6 +157,15 @@ int oasis_assemble_p1(void *stream, const oasis_mesh *mesh, int32_t form,
                       const double *const *uab, double alpha, const oasis_csr *base,
                       oasis_csr *out);
 
+/* The same assembly for callers with scratch memory (at least
+ * oasis_assemble_p1_workspace_size bytes): the colours place every dof's
+ * cells in a table, and each row adds its own entries.  At most 128 colours
+ * (EUNSUPPORTED). */
+int oasis_assemble_p1_workspace_size(const oasis_mesh *mesh, size_t *bytes);
+int oasis_assemble_p1_ws(void *stream, const oasis_mesh *mesh, int32_t form,
+                         const double *const *uab, double alpha, const oasis_csr *base,
+                         oasis_csr *out, void *ws, size_t ws_bytes);
+
 /* ---- sparse matrix-vector product (Sec. 5, eq:tent_algebraic terms) ----- */
 
 /* y = alpha * A x + beta * y.  x and y have A's dtype; F32 products are

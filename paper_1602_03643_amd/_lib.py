@@ -105,6 +105,8 @@ _SIGS = {
     "oasis_rcm": (i32, [vp, i32, vp, vp, vp, vp, vp, sz]),
     "oasis_relabel": (i32, [vp, i32, vp, vp, vp]),
     "oasis_assemble_p1": (i32, [vp, P(Mesh), i32, P(vp), f64, P(Csr), P(Csr)]),
+    "oasis_assemble_p1_workspace_size": (i32, [P(Mesh), P(sz)]),
+    "oasis_assemble_p1_ws": (i32, [vp, P(Mesh), i32, P(vp), f64, P(Csr), P(Csr), vp, sz]),
     "oasis_spmv": (i32, [vp, P(Csr), vp, vp, f64, f64]),
     "oasis_krylov_workspace_size": (i32, [i32, i32, i32, P(KrylovOpts), P(sz)]),
     "oasis_pcg": (i32, [vp, P(Csr), vp, vp, P(KrylovOpts), vp, sz, P(KrylovStats)]),

@@ -187,8 +187,18 @@ def assemble_p1(mesh: DeviceMesh, pattern: DeviceCSR, form: int, uab=None, alpha
     arr = None
     if uab is not None:
         arr = (C.c_void_p * 3)(*[u.data_ptr() for u in uab] + [None] * (3 - len(uab)))
-    L.check(_lib().oasis_assemble_p1(_stream(stream), C.byref(mesh.c()), form, arr, float(alpha),
-                                     None if B is None else C.byref(B), C.byref(A)), "oasis_assemble_p1")
+    lib, cm = _lib(), mesh.c()
+    nb = C.c_size_t()
+    Bp = None if B is None else C.byref(B)
+    if mesh.n_colors and lib.oasis_assemble_p1_workspace_size(C.byref(cm), C.byref(nb)) == L.OK:
+        # the workspace belongs to the stream that uses it
+        with torch.cuda.stream(stream):
+            ws = _workspace(nb.value, val.device)
+        rc = lib.oasis_assemble_p1_ws(_stream(stream), C.byref(cm), form, arr, float(alpha), Bp, C.byref(A), _p(ws),
+                                      ws.numel())
+    else:
+        rc = lib.oasis_assemble_p1(_stream(stream), C.byref(cm), form, arr, float(alpha), Bp, C.byref(A))
+    L.check(rc, "oasis_assemble_p1")
     return val
 
 

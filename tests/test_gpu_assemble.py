@@ -1,0 +1,74 @@
+"""The row-wise assembly (oasis_assemble_p1_ws, what the binding calls)
+against the colour-wise one and the oracle: every form, in 2D and 3D, with
+rows longer than the kernel's register slots, with a base matrix, in place,
+and with an entry missing from the pattern (skipped by both)."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from gpu_util import T, csr_host, device_mesh, say
+from oracle import p1
+from test_gpu_graph import _fan
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def oa():
+    import paper_1602_03643_amd as m
+    return m
+
+
+def _colour_wise(oa, dm, pat, form, uab, alpha, base):
+    from paper_1602_03643_amd import _lib as L
+    val = torch.empty(pat.nnz, dtype=torch.float64, device=pat.row_ptr.device)
+    arr = (C.c_void_p * 3)(*[u.data_ptr() for u in uab] + [None] * (3 - len(uab)))
+    A = pat.with_values(val).c()
+    B = None if base is None else C.byref(pat.with_values(base).c())
+    rc = L.load().oasis_assemble_p1(None, C.byref(dm.c()), form, arr, float(alpha), B, C.byref(A))
+    assert rc == 0
+    torch.cuda.synchronize()
+    return val
+
+
+@pytest.mark.parametrize("mesh", [_fan(5), _fan(15), _fan(16), _fan(40), synth.unit_square(7),
+                                  synth.channel(9, 9, 7), synth.channel(18, 15, 12, displace_seed=2),
+                                  synth.permute_mesh(synth.channel(17, 17, 13), 4)[0]], ids=lambda m: m.name)
+def test_rows_match_colours_and_oracle(oa, mesh):
+    say("assembly by rows", mesh.name)
+    dm, pat, _ = device_mesh(mesh)
+    rng = np.random.default_rng(5)
+    u = rng.normal(size=(mesh.dim, mesh.n_dof))
+    uab = [T(v) for v in u]
+    base = T(rng.normal(size=pat.nnz))
+    geo = p1.element_geometry(mesh)
+    H = csr_host(pat)
+    K, Cm = p1.on_pattern(p1.stiffness_matrix(mesh, geo), H), p1.on_pattern(p1.convection_matrix(mesh, u, geo), H)
+    forms = [oa.FORM_MASS, oa.FORM_STIFF, oa.FORM_GRAD_X, oa.FORM_GRAD_Y, oa.FORM_CONV]
+    if mesh.dim == 3:
+        forms.append(oa.FORM_GRAD_Z)
+    for form in forms:
+        for b in (None, base):
+            ref = _colour_wise(oa, dm, pat, form, uab, -0.75, b).cpu().numpy()
+            out = None if b is None else b.clone()
+            val = oa.assemble_p1(dm, pat, form, uab=uab, alpha=-0.75, base=out, out=out).cpu().numpy()
+            # sums of at most some 50 terms per entry
+            assert np.abs(val - ref).max() <= 1e-14 * max(1.0, np.abs(ref).max())
+        if form in (oa.FORM_STIFF, oa.FORM_CONV):
+            want = base.cpu().numpy() - 0.75 * (K if form == oa.FORM_STIFF else Cm)
+            assert np.linalg.norm(val - want) <= 1e-13 * np.linalg.norm(want)
+
+
+def test_entries_outside_the_pattern_are_skipped(oa):
+    mesh = synth.channel(9, 9, 7)
+    say("assembly on a pattern with holes", mesh.name)
+    dm, pat, _ = device_mesh(mesh)
+    full = oa.assemble_p1(dm, pat, oa.FORM_STIFF)
+    rows = np.repeat(np.arange(mesh.n_dof), np.diff(pat.row_ptr.cpu().numpy()))
+    keep = rows != pat.col_idx.cpu().numpy()                      # no diagonal
+    rp = np.concatenate([[0], np.cumsum(np.bincount(rows[keep], minlength=mesh.n_dof))])
+    cut = oa.DeviceCSR(T(rp, torch.int32), pat.col_idx[torch.as_tensor(keep, device=full.device)].contiguous())
+    assert torch.equal(oa.assemble_p1(dm, cut, oa.FORM_STIFF), full[torch.as_tensor(keep, device=full.device)])
