@@ -259,8 +259,8 @@ int oasis_pcg(void *stream, const oasis_csr *A, const double *b, double *x,
  * same solve, with its workspace in a file-scope device array of the
  * library of OASIS_PCG_NOALLOC_BYTES bytes (one per device, held until the
  * process ends) instead of a caller workspace.  It calls no hipMalloc,
- * hipFree or other allocating routine; the offset dictionary (built on the
- * host) is not used, and OASIS_KRYLOV_TIME is refused (EINVAL).
+ * hipFree or other allocating routine; the offset dictionary is not used,
+ * and OASIS_KRYLOV_TIME is refused (EINVAL).
  * EUNSUPPORTED when oasis_krylov_workspace_size(n, nnz, 1, opt) exceeds
  * OASIS_PCG_NOALLOC_BYTES.  All calls on one device share the array: calls
  * that overlap on one device (other streams, other threads) race.

@@ -342,7 +342,7 @@ extern "C" int oasis_amg_upload(void *stream, oasis_amg *h, void *ws, size_t ws_
             OASIS_TRY_LAUNCH();
         }
         int npat = 0;
-        OASIS_TRY(ell_dictionary(s, h->n, d.ecol, d.pid, d.ptab, &npat, h->tun.dict()));
+        OASIS_TRY(ell_dictionary(s, h->n, d.ecol, d.pid, d.ptab, d.tmp, &npat, h->tun.dict()));
         d.cols = ell_cols(d.ecol, d.pid, d.ptab, npat);
         d.ell_storage = npat > 0 ? npat : -1;
     }

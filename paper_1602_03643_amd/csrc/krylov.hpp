@@ -191,8 +191,8 @@ constexpr int kMaxEllPatterns = 4096;
 // [kMaxEllPatterns][kEll] the distinct offset lists, numbered in order of
 // first occurrence.  *npat = their number, or 0 when there are more than
 // min(kMaxEllPatterns, n / 8) (pid and ptab then must not be used) or
-// `enable` is false.  Host work on a copy of ecol; synchronises.
-int ell_dictionary(hipStream_t s, int n, const short *ecol, unsigned short *pid, short *ptab, int *npat,
+// `enable` is false.  tmp: one device int.  Synchronises.
+int ell_dictionary(hipStream_t s, int n, const short *ecol, unsigned short *pid, short *ptab, int *tmp, int *npat,
                    bool enable);
 
 // The columns of an ELL copy: the dictionary when it was built, else the
