@@ -42,54 +42,11 @@
 // us, the 1089-row square 8 -> 3.3 us.
 #include <algorithm>
 
-#include "krylov.hpp"
+#include "coop.hpp"
 
 namespace oasis {
 
 namespace {
-
-using u64 = unsigned long long;
-
-constexpr int kCoopThreads = 1024;             // most threads of a block
-constexpr int kCoopBlocks = 256;               // most blocks: the slot readers' four waves
-constexpr int kCoopMaxRows = kCoopBlocks * kCoopThreads;
-constexpr int kBitWords = kCoopMaxRows / 32;
-constexpr long long kCoopTicks = 200000000ll;  // 2 s of the 100 MHz wall clock
-constexpr int kCoopLost = 5, kCoopUnfit = 6;   // CGState::flag: a wait ran out; too wide a halo
-
-// The exchanged words: a T's bits, or the empty mark, a NaN that no sent
-// value has (every NaN is sent as the quiet one).
-template <typename T>
-struct Word;
-template <>
-struct Word<float> {
-    using U = unsigned;
-    static constexpr U kEmpty = 0xffffbeefu, kNan = 0x7fc00000u;
-    static __device__ __forceinline__ U of(float v) { return v == v ? __float_as_uint(v) : kNan; }
-    static __device__ __forceinline__ float value(U u) { return __uint_as_float(u); }
-};
-template <>
-struct Word<double> {
-    using U = u64;
-    static constexpr U kEmpty = 0xffffdeadbeef0001ull, kNan = 0x7ff8000000000000ull;
-    static __device__ __forceinline__ U of(double v) {
-        return v == v ? static_cast<U>(__double_as_longlong(v)) : kNan;
-    }
-    static __device__ __forceinline__ double value(U u) { return __longlong_as_double(static_cast<long long>(u)); }
-};
-template <typename U>
-__device__ __forceinline__ U word_load(const U *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename U>
-__device__ __forceinline__ void word_store(U *p, U v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// all of this thread's earlier stores have reached memory
-__device__ __forceinline__ void stores_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }   // vmcnt(0)
-
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 struct CoopArgs {
     int n, rows;           // rows per block
@@ -117,12 +74,10 @@ template <typename T, int BS>
 __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
     constexpr int E = kEll;
     constexpr int kCoopWaves = BS / kWave;
-    constexpr int kCoopHaloPer = BS >= 1024 ? 4 : 8;   // halo entries per thread at most
-    constexpr int kCoopHalo = kCoopHaloPer * BS;
-    constexpr size_t kSetup = kBitWords * sizeof(unsigned) + kBitWords * sizeof(unsigned short);
+    constexpr int kHaloPer = kCoopHaloPer<BS>, kCoopHalo = kHaloPer * BS;
     constexpr size_t kDir = (BS + kCoopHalo) * sizeof(T);
     // the bitmap of referenced columns (set-up) and the direction (iterations)
-    __shared__ __align__(16) unsigned char shared[kSetup > kDir ? kSetup : kDir];
+    __shared__ __align__(16) unsigned char shared[kCoopSetup > kDir ? kCoopSetup : kDir];
     __shared__ int halo[kCoopHalo];
     // [exchange kind][value]: the block's waves' sums and the grid's totals
     __shared__ double red[2][2][kCoopWaves], all[2][2];
@@ -137,98 +92,16 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
     CGState *st = a.st;
     if (t == 0) quit = 0;
 
-    // columns, and the bitmap of those outside the block's range
-    unsigned *bits = reinterpret_cast<unsigned *>(shared);
-    unsigned short *rank = reinterpret_cast<unsigned short *>(shared + kBitWords * sizeof(unsigned));
-    const int nw = (a.n + 31) / 32;
-    for (int w = t; w < nw; w += BS) bits[w] = 0u;
-    __syncthreads();
-    int c[E];
     T val[E];
-    {
-        const short *off = a.cols.offsets(at);
-        const T *ev = static_cast<const T *>(a.eval) + static_cast<size_t>(at) * kEll;
-#pragma unroll
-        for (int g = 0; g < E / 4; ++g) {
-            const short4 d = *reinterpret_cast<const short4 *>(off + 4 * g);
-            c[4 * g] = ell_col(at, d.x, a.n);
-            c[4 * g + 1] = ell_col(at, d.y, a.n);
-            c[4 * g + 2] = ell_col(at, d.z, a.n);
-            c[4 * g + 3] = ell_col(at, d.w, a.n);
-            T v[4];
-            load4(ev + 4 * g, v);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) val[4 * g + k] = own ? v[k] : T(0);
-        }
-    }
-    if (own) {
-#pragma unroll
-        for (int k = 0; k < E; ++k)
-            if (c[k] < r0 || c[k] >= r1) atomicOr(&bits[c[k] >> 5], 1u << (c[k] & 31));
-    }
-    __syncthreads();
-    // ranks: halo entries in ascending column order
-    int nh = 0;
-    {
-        constexpr int PER = kBitWords / BS;
-        int cnt[PER], sum = 0;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int w = t * PER + k;
-            cnt[k] = w < nw ? __popc(bits[w]) : 0;
-            sum += cnt[k];
-        }
-        int inc = sum;
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int up = __shfl_up(inc, o, kWave);
-            if (wl >= o) inc += up;
-        }
-        if (wl == kWave - 1) scan[wv] = inc;
-        __syncthreads();
-        int base = inc - sum;
-        for (int w = 0; w < kCoopWaves; ++w) {
-            if (w < wv) base += scan[w];
-            nh += scan[w];
-        }
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int w = t * PER + k;
-            if (w < nw) {
-                rank[w] = static_cast<unsigned short>(min(base, 65535));
-                unsigned b = bits[w];
-                int q = base;
-                while (b) {
-                    const int j = __builtin_ctz(b);
-                    b &= b - 1;
-                    if (q < kCoopHalo) halo[q] = w * 32 + j;
-                    ++q;
-                }
-                base = q;
-            }
-        }
-    }
-    __syncthreads();
+    unsigned idx[E / 2];
+    const int nh = coop_columns<T, BS>(a.n, a.cols, static_cast<const T *>(a.eval), r0, r1, at, own, shared, halo, scan,
+                                       val, idx);
     if (nh > kCoopHalo) {
         // not a system for this kernel: nothing has been sent, so no block
         // gets past its first exchange, and the host takes the other kernels
         if (t == 0) atomicMax(&st->flag, kCoopUnfit);
         return;
     }
-    unsigned idx[E / 2];
-#pragma unroll
-    for (int k = 0; k < E; k += 2) {
-        unsigned both[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int cc = c[k + q];
-            const bool in = cc >= r0 && cc < r1;
-            const int w = cc >> 5;
-            const int h = in || !own ? 0 : rank[w] + __popc(bits[w] & ((1u << (cc & 31)) - 1u));
-            both[q] = !own ? 0u : in ? cc - r0 : BS + h;
-        }
-        idx[k / 2] = both[0] | (both[1] << 16);
-    }
-    __syncthreads();
     T *dir = reinterpret_cast<T *>(shared);
 
     const RP<T> *cur = static_cast<const RP<T> *>(a.cur);
@@ -240,7 +113,7 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
     const T v = vn ? vn[at] : T(0);
     T r = me.r, p = a.beta_zero ? T(0) : me.p;
 #pragma unroll
-    for (int k = 0; k < kCoopHaloPer; ++k) {
+    for (int k = 0; k < kHaloPer; ++k) {
         const int h = t + k * BS;
         if (h < nh) dir[BS + h] = a.beta_zero ? T(0) : cur[halo[h]].p;
     }
@@ -333,16 +206,16 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
         }
         const double rd = r;
         give(own ? rd * rd : 0.0, own ? wgt * rd * rd : 0.0, 2, 0);
-        typename W::U hw[kCoopHaloPer];
+        typename W::U hw[kHaloPer];
         poll([&] {
             bool miss = false;
 #pragma unroll
-            for (int k = 0; k < kCoopHaloPer; ++k) {
+            for (int k = 0; k < kHaloPer; ++k) {
                 const int h = t + k * BS;
                 if (h < nh) hw[k] = word_load(ex + halo[h]);
             }
 #pragma unroll
-            for (int k = 0; k < kCoopHaloPer; ++k)
+            for (int k = 0; k < kHaloPer; ++k)
                 if (t + k * BS < nh) miss |= hw[k] == W::kEmpty;
             return miss;
         });
@@ -364,7 +237,7 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
         p = fresh ? r : fma_t(beta, p, r);
         if (own) dir[t] = p;
 #pragma unroll
-        for (int k = 0; k < kCoopHaloPer; ++k) {
+        for (int k = 0; k < kHaloPer; ++k) {
             const int h = t + k * BS;
             if (h < nh) {
                 const T rh = W::value(hw[k]);

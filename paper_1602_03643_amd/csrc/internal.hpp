@@ -110,7 +110,7 @@ inline int grid_for(long long work, int per_block, int cap = kMaxPartials) {
 // ds_bpermute per double, some 60 cycles each step of the butterfly); these
 // moves take a few cycles, and the reductions are a serial chain at both
 // ends of every solver kernel.
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;            // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor3 = 0x1B;   // quad_perm [1,0,3,2], [2,3,0,1], [3,2,1,0]
 constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;   // within 8 and within 16 lanes
 constexpr int kDppBcast15 = 0x142, kDppBcast31 = 0x143;     // a row's last lane into the next row(s)
 template <int CTRL, int ROWS = 0xf>

@@ -2277,6 +2277,10 @@ template <typename T>
 int bicgstab_solve(hipStream_t s, int n, int nrhs, const int *rp, const int *ci, const T *val,
                    const T *wgt, const T *const *b, T *const *x, double rtol, int maxit,
                    int check_every, bool time_kernel, BiWork<T> &w, SolveOut *out, bool inner) {
+    if (!time_kernel) {
+        const int rc = bicg_coop_solve<T>(s, n, nrhs, wgt, b, x, rtol, maxit, w, out, inner);
+        if (rc != OASIS_EUNSUPPORTED) return rc;
+    }
     return with_cfg([&](auto c) {
         using C = decltype(c);
         if (nrhs == 1)

@@ -109,6 +109,7 @@ struct BiWork {
     const T *eval = nullptr;
     HostStage stage;   // the owner's read-back block (may be null)
     Tuning tun;
+    bool coop_off = false;   // the pattern's halo is too wide for a cooperative solve
 };
 
 struct SolveOut {
@@ -171,6 +172,13 @@ template <typename T>
 int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T *vnull, int it0, int m, bool beta_zero);
 // Iterations of one cooperative run at most (it stops by itself).
 constexpr int kCoopRun = 4096;
+
+// A whole BiCGStab solve in one cooperative launch (bicg_coop.hip), for one to
+// three right-hand sides; arguments and results of bicgstab_solve.
+// EUNSUPPORTED, with nothing changed: not for this system, device or tuning.
+template <typename T>
+int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const *b, T *const *x, double rtol, int maxit,
+                    BiWork<T> &w, SolveOut *out, bool inner);
 
 // Longest row of a CSR pattern (synchronises; tmp: one device int).
 int csr_max_row(hipStream_t s, int n, const int *rp, int *tmp, int *out);
