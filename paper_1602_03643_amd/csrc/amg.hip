@@ -13,7 +13,11 @@
 //   prolong  t = w .* b + P x_{l+1}
 //   post     x = t + w .* (b - A t)
 // Level 0 runs on the ELL copy of the matrix (16-bit offsets, dictionary on
-// structured meshes) when it fits, CSR otherwise; coarser levels on CSR.
+// structured meshes) when it fits, CSR otherwise; coarser levels on CSR.  On
+// the levels that are small enough (multiply_out in amg_setup.hip) pre and
+// restrict are one matrix, and so are prolong and post: two products a level
+// instead of four kernels of 4-5 us.  On 105,000 rows in FP64 an iteration
+// went from 84 to 66 us.
 // The cycle is in FP64 or FP32 (values and vectors); CG stays in FP64 and
 // its dot products too, so the FP32 cycle is an inner approximation only.
 #include <algorithm>
@@ -83,6 +87,80 @@ __global__ __launch_bounds__(kBlock) void k_amg_pre_ell(int n, EllCols cols, con
     ell_rows_pipe<T, 1, 2, DICT, T, TB>(n, cols, e, load, add, own, fin);
 }
 
+// The rows of M x, M in CSR, summed by C::L lanes each: finish(row, own, sum)
+// on the first of them, own(row) what it needs besides.  A row's extent, its
+// entries and the operand they gather are three loads that wait for each
+// other, so while a row's operands are gathered the entries of the group's
+// next row and the extent of the one after it are on their way.  (Rows of
+// several hundred entries are read P a lane at a time: one at a time took
+// 14 us where this takes 9, on 670 rows of 534.)
+template <typename T, class C, class Own, class Finish>
+__device__ __forceinline__ void csr_pipe(int n, const int *__restrict__ rp, const int *__restrict__ ci,
+                                         const T *__restrict__ val, const T *__restrict__ x, Own own, Finish finish) {
+    constexpr int L = C::L, P = C::P;
+    const int lane = threadIdx.x & (L - 1);
+    const RowRange<L, kBlock> rr(n);
+    struct Extent {
+        int s, e;
+    };
+    struct Chunk {
+        int c[P], in;   // columns, bits of the entries that are the row's
+        T v[P];
+    };
+    auto extent = [&](long long row) {
+        Extent r{0, 0};
+        if (row < rr.last) {
+            r.s = rp[row];
+            r.e = rp[row + 1];
+        }
+        return r;
+    };
+    // P entries from j on (beyond the row: its first one, or the matrix's)
+    auto chunk = [&](int s, int j, int e) {
+        Chunk k;
+        k.in = 0;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const int q = j + p * L, at = q < e ? q : e > s ? s : 0;
+            k.in |= (q < e ? 1 : 0) << p;
+            k.c[p] = ci[at];
+            k.v[p] = val[at];
+        }
+        return k;
+    };
+    auto add = [&](const Chunk &k, const T(&g)[P], T a) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) a += (k.in >> p) & 1 ? k.v[p] * g[p] : T(0);
+        return a;
+    };
+    long long row = rr.first + rr.gid;
+    if (row >= rr.last) return;   // (of this function: its callers go on to their barriers)
+    Extent r0 = extent(row);
+    Chunk k0 = chunk(r0.s, r0.s + lane, r0.e);
+    Extent r1 = extent(row + rr.ngroups);
+    for (; row < rr.last; row += rr.ngroups) {
+        T g[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) g[p] = x[k0.c[p]];
+        const auto o = own(row);
+        const Chunk k1 = chunk(r1.s, r1.s + lane, r1.e);
+        const Extent r2 = extent(row + 2 * rr.ngroups);
+        T acc = add(k0, g, T(0));
+        for (int j = r0.s + P * L + lane; j - lane < r0.e; j += P * L) {
+            const Chunk k = chunk(r0.s, j, r0.e);
+            T h[P];
+#pragma unroll
+            for (int p = 0; p < P; ++p) h[p] = x[k.c[p]];
+            acc = add(k, h, acc);
+        }
+        acc = group_sum<L>(acc);
+        if (lane == 0) finish(row, o, acc);
+        r0 = r1;
+        r1 = r2;
+        k0 = k1;
+    }
+}
+
 // pre-smoothing residual, CSR
 template <typename T, typename TB, class C>
 __global__ __launch_bounds__(kBlock) void k_amg_pre_csr(int n, const int *__restrict__ rp, const int *__restrict__ ci,
@@ -90,36 +168,34 @@ __global__ __launch_bounds__(kBlock) void k_amg_pre_csr(int n, const int *__rest
                                                         const TB *__restrict__ b, T *__restrict__ t,
                                                         const int *flag) {
     if (stopped(flag)) return;
-    csr_rows<T, 1, C>(
-        n, rp, ci, val,
-        [&](int, int c, T v, bool ok, T(&a)[1]) {
-            const T g = v * y[c];
-            a[0] += ok ? g : T(0);
-        },
-        [&](int row, int lane, T(&a)[1]) {
-            if (lane == 0) t[row] = static_cast<T>(b[row]) - a[0];
-        });
+    csr_pipe<T, C>(
+        n, rp, ci, val, y, [&](long long row) { return b[row]; },
+        [&](long long row, TB br, T sum) { t[row] = static_cast<T>(br) - sum; });
 }
 
-// restriction b_c = R t (R = P^T as CSR), and y_c = w_c .* b_c when the
-// next level smooths (wdc non-null)
+// y = M x: the cycle's halves on the levels where they are multiplied out
+template <typename T, class C>
+__global__ __launch_bounds__(kBlock) void k_amg_rows(int n, const int *__restrict__ rp, const int *__restrict__ ci,
+                                                     const T *__restrict__ val, const T *__restrict__ x,
+                                                     T *__restrict__ y, const int *flag) {
+    if (stopped(flag)) return;
+    csr_pipe<T, C>(
+        n, rp, ci, val, x, [](long long) { return 0; }, [&](long long row, int, T sum) { y[row] = sum; });
+}
+
+// restriction b_c = R t (R = P^T as CSR), and y_c = w_c .* b_c when the next
+// level smooths (wdc non-null)
 template <typename T, class C>
 __global__ __launch_bounds__(kBlock) void k_amg_restrict(int n, const int *__restrict__ rp, const int *__restrict__ ci,
                                                          const T *__restrict__ val, const T *__restrict__ x,
                                                          T *__restrict__ bc, const T *__restrict__ wdc,
                                                          T *__restrict__ yc, const int *flag) {
     if (stopped(flag)) return;
-    csr_rows<T, 1, C>(
-        n, rp, ci, val,
-        [&](int, int c, T v, bool ok, T(&a)[1]) {
-            const T g = v * x[c];
-            a[0] += ok ? g : T(0);
-        },
-        [&](int row, int lane, T(&a)[1]) {
-            if (lane == 0) {
-                bc[row] = a[0];
-                if (wdc) yc[row] = wdc[row] * a[0];
-            }
+    csr_pipe<T, C>(
+        n, rp, ci, val, x, [&](long long row) { return wdc ? wdc[row] : T(0); },
+        [&](long long row, T w, T sum) {
+            bc[row] = sum;
+            if (wdc) yc[row] = w * sum;
         });
 }
 
@@ -130,15 +206,9 @@ __global__ __launch_bounds__(kBlock) void k_amg_prolong(int n, const int *__rest
                                                         const T *__restrict__ val, const T *__restrict__ xc,
                                                         const T *__restrict__ y, T *__restrict__ t, const int *flag) {
     if (stopped(flag)) return;
-    csr_rows<T, 1, C>(
-        n, rp, ci, val,
-        [&](int, int c, T v, bool ok, T(&a)[1]) {
-            const T g = v * xc[c];
-            a[0] += ok ? g : T(0);
-        },
-        [&](int row, int lane, T(&a)[1]) {
-            if (lane == 0) t[row] = y[row] + a[0];
-        });
+    csr_pipe<T, C>(
+        n, rp, ci, val, xc, [&](long long row) { return y[row]; },
+        [&](long long row, T yr, T sum) { t[row] = yr + sum; });
 }
 
 // post-smoothing x = t + w .* (b - A t), written as TO at out[i * os];
@@ -193,14 +263,11 @@ __global__ __launch_bounds__(kBlock) void k_amg_post_csr(int n, const int *__res
     if (stopped(flag)) return;
     double acc[2] = {0.0, 0.0};
     const double *w2 = part ? wgt : nullptr;
-    csr_rows<T, 1, C>(
-        n, rp, ci, val,
-        [&](int, int c, T v, bool ok, T(&a)[1]) {
-            const T g = v * t[c];
-            a[0] += ok ? g : T(0);
-        },
-        [&](int row, int lane, T(&a)[1]) {
-            if (lane == 0) amg_post_finish<T, TB, TO>(row, t[row], wd[row], b[row], a[0], out, os, w2, acc);
+    using O = PostOwn<T, TB>;
+    csr_pipe<T, C>(
+        n, rp, ci, val, t, [&](long long row) { return O{t[row], wd[row], b[row]}; },
+        [&](long long row, const O &o, T sum) {
+            amg_post_finish<T, TB, TO>(static_cast<int>(row), o.t, o.w, o.b, sum, out, os, w2, acc);
         });
     if (part) write_partials<2>(acc, part, lds);
 }
@@ -301,8 +368,10 @@ __global__ __launch_bounds__(kBlock) void k_amg_to_f32(int n, const double *__re
         b[i] = static_cast<float>(a[i]);
 }
 
+// csr_pipe: resident blocks only, so that a group of lanes has rows to run
+// ahead on
 template <class C>
-int csr_grid(int n) { return grid_for(n, rows_per_block<C>(), 1 << 20); }
+int rows_grid(int n) { return grid_for(n, rows_per_block<C>(), 2048); }
 
 // reps launches of `launch` back to back between two events on s
 template <class Launch>
@@ -349,9 +418,35 @@ int amg_vcycle(hipStream_t s, const AmgCycle<T> &c, const TB *r, bool y0_ready, 
                            v.wd, r, v.y, flag);
         OASIS_TRY_LAUNCH();
     }
+    // a level's matrix products: level 0 on its ELL copy or CSR with the outer
+    // types, the levels below on CSR in T
+    auto pre_csr = [&](const AmgDevLevel<T> &v, const auto *b) -> int {
+        using B = std::remove_const_t<std::remove_pointer_t<decltype(b)>>;
+        return with_lanes(v.A.lanes, [&](auto cfg) -> int {
+            using C = decltype(cfg);
+            hipLaunchKernelGGL((k_amg_pre_csr<T, B, C>), dim3(rows_grid<C>(v.n)), dim3(kBlock), 0, s, v.n, v.A.rp,
+                               v.A.ci, v.A.val, v.y, b, v.t, flag);
+            OASIS_TRY_LAUNCH();
+            return OASIS_OK;
+        });
+    };
+    auto rows = [&](const AmgDevCsr<T> &m, const T *x, T *y) -> int {
+        return with_lanes(m.lanes, [&](auto cfg) -> int {
+            using C = decltype(cfg);
+            hipLaunchKernelGGL((k_amg_rows<T, C>), dim3(rows_grid<C>(m.n)), dim3(kBlock), 0, s, m.n, m.rp, m.ci, m.val,
+                               x, y, flag);
+            OASIS_TRY_LAUNCH();
+            return OASIS_OK;
+        });
+    };
     // down
+    const AmgDevLevel<T> &v0 = c.lv[0];
     for (int l = 0; l + 1 < L; ++l) {
-        const AmgDevLevel<T> &v = c.lv[l];
+        const AmgDevLevel<T> &v = c.lv[l], &nx = c.lv[l + 1];
+        if (v.down.n) {
+            OASIS_TRY(rows(v.down, v.b, nx.b));
+            continue;
+        }
         if (l == 0 && ell0) {
             const int g = ell_grid(v.n, grid_cap);   // several rows per lane group: the row loop prefetches
             bool done = false;
@@ -375,26 +470,15 @@ int amg_vcycle(hipStream_t s, const AmgCycle<T> &c, const TB *r, bool y0_ready, 
                                        c.e, v.y, r, v.t, flag);
             }
             OASIS_TRY_LAUNCH();
+        } else if (l == 0) {
+            OASIS_TRY(pre_csr(v, r));
         } else {
-            OASIS_TRY(with_lanes(v.alanes, [&](auto cfg) -> int {
-                using C = decltype(cfg);
-                if (l == 0)
-                    hipLaunchKernelGGL((k_amg_pre_csr<T, TB, C>), dim3(csr_grid<C>(v.n)), dim3(kBlock), 0, s,
-                                       v.n, v.rp, v.ci, v.val, v.y, r, v.t, flag);
-                else
-                    hipLaunchKernelGGL((k_amg_pre_csr<T, T, C>), dim3(csr_grid<C>(v.n)), dim3(kBlock), 0, s, v.n,
-                                       v.rp, v.ci, v.val, v.y, v.b, v.t, flag);
-                OASIS_TRY_LAUNCH();
-                return OASIS_OK;
-            }));
+            OASIS_TRY(pre_csr(v, static_cast<const T *>(v.b)));
         }
-        const AmgDevLevel<T> &nx = c.lv[l + 1];
-        const bool smooth_next = l + 2 < L;
-        OASIS_TRY(with_lanes(v.rlanes, [&](auto cfg) -> int {
+        OASIS_TRY(with_lanes(v.R.lanes, [&](auto cfg) -> int {
             using C = decltype(cfg);
-            hipLaunchKernelGGL((k_amg_restrict<T, C>), dim3(csr_grid<C>(nx.n)), dim3(kBlock), 0, s, nx.n, v.rrp,
-                               v.rci, v.rval, v.t, nx.b, smooth_next ? nx.wd : nullptr,
-                               smooth_next ? nx.y : nullptr, flag);
+            hipLaunchKernelGGL((k_amg_restrict<T, C>), dim3(rows_grid<C>(nx.n)), dim3(kBlock), 0, s, nx.n, v.R.rp,
+                               v.R.ci, v.R.val, v.t, nx.b, nx.wd, nx.y, flag);
             OASIS_TRY_LAUNCH();
             return OASIS_OK;
         }));
@@ -410,57 +494,62 @@ int amg_vcycle(hipStream_t s, const AmgCycle<T> &c, const TB *r, bool y0_ready, 
     // up
     for (int l = L - 2; l >= 0; --l) {
         const AmgDevLevel<T> &v = c.lv[l];
-        const AmgDevLevel<T> &nx = c.lv[l + 1];
-        OASIS_TRY(with_lanes(v.planes, [&](auto cfg) -> int {
+        if (v.up.n) {
+            OASIS_TRY(rows(v.up, v.b, v.x));
+            continue;
+        }
+        OASIS_TRY(with_lanes(v.P.lanes, [&](auto cfg) -> int {
             using C = decltype(cfg);
-            hipLaunchKernelGGL((k_amg_prolong<T, C>), dim3(csr_grid<C>(v.n)), dim3(kBlock), 0, s, v.n, v.prp, v.pci,
-                               v.pval, nx.x, v.y, v.t, flag);
+            hipLaunchKernelGGL((k_amg_prolong<T, C>), dim3(rows_grid<C>(v.n)), dim3(kBlock), 0, s, v.n, v.P.rp, v.P.ci,
+                               v.P.val, c.lv[l + 1].x, v.y, v.t, flag);
             OASIS_TRY_LAUNCH();
             return OASIS_OK;
         }));
-        if (l == 0 && ell0) {
-            const int g = ell_grid(v.n, part ? grid_cap : 1 << 20);
-            bool done = false;
-            if constexpr (std::is_same<T, float>::value) {
-                if (c.e16) {
-                    if (dict)
-                        hipLaunchKernelGGL((k_amg_post_ell<T, TB, TO, true, _Float16>), dim3(g), dim3(kBlock), 0, s,
-                                           v.n, c.cols, c.e16, v.wd, r, v.t, z, zs, wgt, part, flag);
-                    else
-                        hipLaunchKernelGGL((k_amg_post_ell<T, TB, TO, false, _Float16>), dim3(g), dim3(kBlock), 0,
-                                           s, v.n, c.cols, c.e16, v.wd, r, v.t, z, zs, wgt, part, flag);
-                    done = true;
-                }
-            }
-            if (!done) {
-                if (dict)
-                    hipLaunchKernelGGL((k_amg_post_ell<T, TB, TO, true>), dim3(g), dim3(kBlock), 0, s, v.n,
-                                       c.cols, c.e, v.wd, r, v.t, z, zs, wgt, part, flag);
-                else
-                    hipLaunchKernelGGL((k_amg_post_ell<T, TB, TO, false>), dim3(g), dim3(kBlock), 0, s, v.n,
-                                       c.cols, c.e, v.wd, r, v.t, z, zs, wgt, part, flag);
-            }
+        if (l == 0) break;
+        OASIS_TRY(with_lanes(v.A.lanes, [&](auto cfg) -> int {
+            using C = decltype(cfg);
+            hipLaunchKernelGGL((k_amg_post_csr<T, T, T, C>), dim3(rows_grid<C>(v.n)), dim3(kBlock), 0, s, v.n,
+                               v.A.rp, v.A.ci, v.A.val, v.wd, v.b, v.t, v.x, 1,
+                               static_cast<const double *>(nullptr), static_cast<double *>(nullptr), flag);
             OASIS_TRY_LAUNCH();
-            if (gpost) *gpost = g;
-        } else {
-            OASIS_TRY(with_lanes(v.alanes, [&](auto cfg) -> int {
-                using C = decltype(cfg);
-                if (l == 0) {
-                    const int g = std::min(csr_grid<C>(v.n), part ? grid_cap : 1 << 20);
-                    hipLaunchKernelGGL((k_amg_post_csr<T, TB, TO, C>), dim3(g), dim3(kBlock), 0, s, v.n,
-                                       v.rp, v.ci, v.val, v.wd, r, v.t, z, zs, wgt, part, flag);
-                    if (gpost) *gpost = g;
-                } else {
-                    hipLaunchKernelGGL((k_amg_post_csr<T, T, T, C>), dim3(csr_grid<C>(v.n)), dim3(kBlock), 0, s, v.n,
-                                       v.rp, v.ci, v.val, v.wd, v.b, v.t, v.x, 1,
-                                       static_cast<const double *>(nullptr), static_cast<double *>(nullptr), flag);
-                }
-                OASIS_TRY_LAUNCH();
-                return OASIS_OK;
-            }));
-        }
+            return OASIS_OK;
+        }));
     }
-    return OASIS_OK;
+    if (ell0) {
+        const int g = ell_grid(v0.n, part ? grid_cap : 1 << 20);
+        bool done = false;
+        if constexpr (std::is_same<T, float>::value) {
+            if (c.e16) {
+                if (dict)
+                    hipLaunchKernelGGL((k_amg_post_ell<T, TB, TO, true, _Float16>), dim3(g), dim3(kBlock), 0, s,
+                                       v0.n, c.cols, c.e16, v0.wd, r, v0.t, z, zs, wgt, part, flag);
+                else
+                    hipLaunchKernelGGL((k_amg_post_ell<T, TB, TO, false, _Float16>), dim3(g), dim3(kBlock), 0, s,
+                                       v0.n, c.cols, c.e16, v0.wd, r, v0.t, z, zs, wgt, part, flag);
+                done = true;
+            }
+        }
+        if (!done) {
+            if (dict)
+                hipLaunchKernelGGL((k_amg_post_ell<T, TB, TO, true>), dim3(g), dim3(kBlock), 0, s, v0.n, c.cols, c.e,
+                                   v0.wd, r, v0.t, z, zs, wgt, part, flag);
+            else
+                hipLaunchKernelGGL((k_amg_post_ell<T, TB, TO, false>), dim3(g), dim3(kBlock), 0, s, v0.n, c.cols,
+                                   c.e, v0.wd, r, v0.t, z, zs, wgt, part, flag);
+        }
+        OASIS_TRY_LAUNCH();
+        if (gpost) *gpost = g;
+        return OASIS_OK;
+    }
+    return with_lanes(v0.A.lanes, [&](auto cfg) -> int {
+        using C = decltype(cfg);
+        const int g = std::min(rows_grid<C>(v0.n), part ? grid_cap : 1 << 20);
+        hipLaunchKernelGGL((k_amg_post_csr<T, TB, TO, C>), dim3(g), dim3(kBlock), 0, s, v0.n, v0.A.rp, v0.A.ci,
+                           v0.A.val, v0.wd, r, v0.t, z, zs, wgt, part, flag);
+        OASIS_TRY_LAUNCH();
+        if (gpost) *gpost = g;
+        return OASIS_OK;
+    });
 }
 
 // Iterations to launch before the next poll: from the observed rate of
@@ -658,7 +747,7 @@ int amg_pcg_mixed(hipStream_t s, int n, const int *rp, const int *ci, const doub
     };
     int restart_at = 0;
     auto iterate = [&](int itj) -> int {
-        OASIS_TRY(cg_product_launch(s, cap, n, l0.rp, l0.ci, l0.val, ell32 ? c.cols : EllCols{},
+        OASIS_TRY(cg_product_launch(s, cap, n, l0.A.rp, l0.A.ci, l0.A.val, ell32 ? c.cols : EllCols{},
                                     ell32 ? c.e : nullptr, w.pair[itj & 1], w.pair[(itj + 1) & 1], w.q, pv, gpost,
                                     2, w.st, itj, itj == restart_at ? 1 : 0, pq, &g1));
         hipLaunchKernelGGL(k_apcg_update32, dim3(grid_for(n, kBlock, kMaxPartials)), dim3(kBlock), 0, s, n,

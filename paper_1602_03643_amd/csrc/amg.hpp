@@ -30,6 +30,10 @@ struct HostLevel {
     int n_agg = 0;
     HostCsr P;                   // n x n_agg
     HostCsr R;                   // P^T
+    // The cycle's two halves as matrices (from the first level on where that
+    // pays, to the one above the coarsest; else empty): with W the smoother weights, b_{l+1} = down b_l, down = R (I - A W), and
+    // x_l = up [b_l; x_{l+1}], up = [2 W - W A W | (I - W A) P]
+    HostCsr down, up;
 };
 
 struct AmgHostParams {
@@ -46,22 +50,27 @@ struct AmgHostParams {
 int amg_build(const HostCsr &A0, const std::vector<double> &B0, const AmgHostParams &p,
               std::vector<HostLevel> &levels, std::vector<double> &coarse_inv);
 
-// Device image of one level below the coarsest: matrix (CSR; level 0 uses
-// the ELL copy instead), smoother weights w_i = omega / a_ii, prolongator P
-// and restriction R = P^T (CSR), and the cycle's vectors.
+// A CSR matrix on the device and its lanes per row.
 template <typename T>
-struct AmgDevLevel {
+struct AmgDevCsr {
     int n = 0;
     const int *rp = nullptr, *ci = nullptr;
     const T *val = nullptr;
+    int lanes = 4;
+};
+
+// Device image of one level: the matrix (CSR; level 0 may use the cycle's ELL
+// copy instead), smoother weights w_i = omega / a_ii, prolongator P and
+// restriction R = P^T, y = w .* b (the pre-smoothed iterate) and a scratch
+// vector t; or, where they are multiplied out, the two halves of the cycle.
+// Right-hand side b and solution x below level 0; x_{l+1} follows b_l where
+// `up` wants them so.
+template <typename T>
+struct AmgDevLevel {
+    int n = 0;
+    AmgDevCsr<T> A, P, R, down, up;
     const T *wd = nullptr;
-    const int *prp = nullptr, *pci = nullptr;
-    const T *pval = nullptr;
-    const int *rrp = nullptr, *rci = nullptr;
-    const T *rval = nullptr;
-    T *b = nullptr, *t = nullptr, *x = nullptr;   // right-hand side, scratch, solution
-    T *y = nullptr;                               // w .* b, the pre-smoothed iterate
-    int alanes = 4, planes = 4, rlanes = 4;       // CSR lanes per row of A, P and R
+    T *b = nullptr, *t = nullptr, *x = nullptr, *y = nullptr;
 };
 
 // The cycle in precision T: level 0's matrix is the ELL copy (cols, e),

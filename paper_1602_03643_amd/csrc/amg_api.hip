@@ -68,6 +68,22 @@ bool ell_fits_host(const HostCsr &A) {
     return true;
 }
 
+// CSR lanes per row from the mean row length (the coarse levels' rows grow
+// long, 70-140 entries, and are few: wider groups there)
+int csr_lanes(const HostCsr &M) {
+    const double avg = M.n ? static_cast<double>(M.nnz()) / M.n : 0.0;
+    return avg <= 6.0 ? 2 : avg <= 12.0 ? 4 : avg <= 28.0 ? 8 : avg <= 56.0 ? 16 : avg <= 100.0 ? 32 : 64;
+}
+
+template <typename T>
+void carve_csr(Carver &c, const HostCsr &M, AmgDevCsr<T> &d) {
+    d.n = M.n;
+    d.rp = c.take<int>(M.n + 1);
+    d.ci = c.take<int>(M.nnz());
+    d.val = c.take<T>(M.nnz());
+    d.lanes = csr_lanes(M);
+}
+
 template <typename T>
 void carve_levels(Carver &c, const oasis_amg &h, AmgCycle<T> &cy) {
     const int L = static_cast<int>(h.levels.size());
@@ -76,49 +92,35 @@ void carve_levels(Carver &c, const oasis_amg &h, AmgCycle<T> &cy) {
     for (int l = 0; l < L; ++l) {
         const HostLevel &hl = h.levels[l];
         AmgDevLevel<T> &d = cy.lv[l];
-        d.n = hl.A.n;
+        const int n = d.n = hl.A.n;
+        const bool last = l + 1 == L;
+        const bool out = hl.up.n > 0;   // multiplied out
         if (l > 0) {
-            d.rp = c.take<int>(hl.A.n + 1);
-            d.ci = c.take<int>(hl.A.nnz());
-            d.val = c.take<T>(hl.A.nnz());
-        } else if (!h.ell_fits) {
-            d.rp = h.rp;
-            d.ci = h.ci;
-            d.val = c.take<T>(hl.A.nnz());
+            d.b = c.take<T>(out ? n + h.levels[l + 1].A.n : n);
+            d.x = h.levels[l - 1].up.n > 0 ? cy.lv[l - 1].b + cy.lv[l - 1].n : c.take<T>(n);
         }
-        if (l + 1 < L) {
-            d.wd = c.take<T>(hl.A.n);
-            d.y = c.take<T>(hl.A.n);
-            d.prp = c.take<int>(hl.A.n + 1);
-            d.pci = c.take<int>(hl.P.nnz());
-            d.pval = c.take<T>(hl.P.nnz());
-            const HostCsr &R = hl.R;
-            d.rrp = c.take<int>(R.n + 1);
-            d.rci = c.take<int>(R.nnz());
-            d.rval = c.take<T>(R.nnz());
-            d.t = c.take<T>(hl.A.n);
+        if (l == 0 && !h.ell_fits) {
+            d.A.n = n;
+            d.A.rp = h.rp;
+            d.A.ci = h.ci;
+            d.A.val = c.take<T>(hl.A.nnz());
+            d.A.lanes = csr_lanes(hl.A);
         }
-        if (l > 0) {
-            d.b = c.take<T>(hl.A.n);
-            d.x = c.take<T>(hl.A.n);
+        if (last) continue;
+        if (out) {
+            carve_csr(c, hl.down, d.down);
+            carve_csr(c, hl.up, d.up);
+            continue;
         }
+        if (l > 0) carve_csr(c, hl.A, d.A);
+        d.wd = c.take<T>(n);
+        d.y = c.take<T>(n);
+        d.t = c.take<T>(n);
+        carve_csr(c, hl.P, d.P);
+        carve_csr(c, hl.R, d.R);
     }
     cy.nc = h.levels.back().A.n;
     cy.cinv = c.take<T>(static_cast<size_t>(cy.nc) * cy.nc);
-    // CSR lanes per row from the mean row length (the coarse levels' rows
-    // grow long, 70-140 entries, and are few: wider groups there)
-    auto lanes = [](const HostCsr &M) {
-        const double avg = M.n ? static_cast<double>(M.nnz()) / M.n : 0.0;
-        return avg <= 6.0 ? 2 : avg <= 12.0 ? 4 : avg <= 28.0 ? 8 : avg <= 56.0 ? 16 : avg <= 100.0 ? 32 : 64;
-    };
-    for (int l = 0; l < L; ++l) {
-        const HostLevel &hl = h.levels[l];
-        cy.lv[l].alanes = lanes(hl.A);
-        if (l + 1 < L) {
-            cy.lv[l].planes = lanes(hl.P);
-            cy.lv[l].rlanes = lanes(hl.R);
-        }
-    }
 }
 
 void carve_amg(Carver &c, const oasis_amg &h, AmgImage &d) {
@@ -179,26 +181,29 @@ std::vector<double> weights(const HostLevel &hl) {
 }
 
 template <typename T>
+int put_csr(hipStream_t s, const AmgDevCsr<T> &d, const HostCsr &M) {
+    OASIS_TRY(put(s, const_cast<int *>(d.rp), M.rp));
+    OASIS_TRY(put(s, const_cast<int *>(d.ci), M.ci));
+    return put(s, const_cast<T *>(d.val), cast<T>(M.v));
+}
+
+template <typename T>
 int upload_levels(hipStream_t s, oasis_amg &h, AmgCycle<T> &cy) {
     const int L = cy.nlev;
     for (int l = 0; l < L; ++l) {
         const HostLevel &hl = h.levels[l];
         AmgDevLevel<T> &d = cy.lv[l];
-        if (l > 0) {
-            OASIS_TRY(put(s, const_cast<int *>(d.rp), hl.A.rp));
-            OASIS_TRY(put(s, const_cast<int *>(d.ci), hl.A.ci));
+        if (l == 0 && !h.ell_fits) OASIS_TRY(put(s, const_cast<T *>(d.A.val), cast<T>(hl.A.v)));
+        if (l + 1 == L) break;
+        if (d.up.n) {
+            OASIS_TRY(put_csr(s, d.down, hl.down));
+            OASIS_TRY(put_csr(s, d.up, hl.up));
+            continue;
         }
-        if (l > 0 || !h.ell_fits) OASIS_TRY(put(s, const_cast<T *>(d.val), cast<T>(hl.A.v)));
-        if (l + 1 < L) {
-            OASIS_TRY(put(s, const_cast<T *>(d.wd), cast<T>(weights(hl))));
-            OASIS_TRY(put(s, const_cast<int *>(d.prp), hl.P.rp));
-            OASIS_TRY(put(s, const_cast<int *>(d.pci), hl.P.ci));
-            OASIS_TRY(put(s, const_cast<T *>(d.pval), cast<T>(hl.P.v)));
-            const HostCsr &R = hl.R;
-            OASIS_TRY(put(s, const_cast<int *>(d.rrp), R.rp));
-            OASIS_TRY(put(s, const_cast<int *>(d.rci), R.ci));
-            OASIS_TRY(put(s, const_cast<T *>(d.rval), cast<T>(R.v)));
-        }
+        if (l > 0) OASIS_TRY(put_csr(s, d.A, hl.A));
+        OASIS_TRY(put(s, const_cast<T *>(d.wd), cast<T>(weights(hl))));
+        OASIS_TRY(put_csr(s, d.P, hl.P));
+        OASIS_TRY(put_csr(s, d.R, hl.R));
     }
     OASIS_TRY(put(s, const_cast<T *>(cy.cinv), cast<T>(h.cinv)));
     if (h.ell_fits) {

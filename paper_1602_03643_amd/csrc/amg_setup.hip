@@ -20,7 +20,9 @@
 //                     weighted by B unless that would halve it),
 //                     w = (4/3) / rho(D_F^-1 A_F), rho estimated from above
 //                     (rho_estimate; the smoother's weight likewise);
-//   coarse matrix     A_c = P^T A P.
+//   coarse matrix     A_c = P^T A P;
+//   halves of the cycle multiplied out (cycle_halves) on the levels below
+//                     level 0 where that is faster.
 // The coarsest level (at most coarse_size rows) gets a dense inverse,
 // regularised along its near-null vector when the matrix is singular.
 #include <algorithm>
@@ -234,6 +236,59 @@ HostCsr filtered(const HostCsr &A, const std::vector<char> &S, const std::vector
     return F;
 }
 
+// The cycle of a level between 0 and the coarsest, multiplied out.  From
+// x = 0 the pre-smoothing and the restriction of its residual are
+//   b_c = R (b - A W b),
+// the prolongation and the post-smoothing
+//   t = W b + P x_c,  x = t + W (b - A t) = (2 W - W A W) b + (P - W A P) x_c.
+void cycle_halves(HostLevel &lv, const std::vector<double> &d, const HostCsr &AP) {
+    const HostCsr &A = lv.A;
+    std::vector<double> w(A.n);
+    for (int i = 0; i < A.n; ++i) w[i] = lv.omega / d[i];
+    {
+        HostCsr &D = lv.down;
+        D.n = lv.R.n;
+        D.m = A.n;
+        D.rp.push_back(0);
+        Spa spa(A.n);
+        for (int c = 0; c < lv.R.n; ++c) {
+            for (int k = lv.R.rp[c]; k < lv.R.rp[c + 1]; ++k) {
+                const int i = lv.R.ci[k];
+                const double r = lv.R.v[k];
+                spa.add(c, i, r);
+                for (int q = A.rp[i]; q < A.rp[i + 1]; ++q) spa.add(c, A.ci[q], -r * A.v[q] * w[A.ci[q]]);
+            }
+            spa.flush(D);
+        }
+    }
+    HostCsr &U = lv.up;
+    U.n = A.n;
+    U.m = A.n + lv.P.m;
+    U.rp.push_back(0);
+    U.ci.reserve(A.ci.size() + AP.ci.size());
+    U.v.reserve(A.ci.size() + AP.ci.size());
+    Spa spa(U.m);
+    for (int i = 0; i < A.n; ++i) {
+        spa.add(i, i, 2.0 * w[i]);
+        for (int q = A.rp[i]; q < A.rp[i + 1]; ++q) spa.add(i, A.ci[q], -w[i] * A.v[q] * w[A.ci[q]]);
+        for (int k = lv.P.rp[i]; k < lv.P.rp[i + 1]; ++k) spa.add(i, A.n + lv.P.ci[k], lv.P.v[k]);
+        for (int k = AP.rp[i]; k < AP.rp[i + 1]; ++k) spa.add(i, A.n + AP.ci[k], -w[i] * AP.v[k]);
+        spa.flush(U);
+    }
+}
+
+// Whether cycle_halves is faster than smoothing, restricting, prolonging and
+// smoothing in turn: it saves two launches, 4-5 us each with the gap before
+// them, but A P has more entries than A, and a coarse level's products take
+// time by the entry (its gathers: 360 an ns; 20.1 M entries of `up` 56 us on
+// 474,000 rows, where A twice and P took 68 us for 23.4 M and `down` adds 27
+// us against 13).  Entries that two launches are worth:
+constexpr long long kLaunchEntries = 3000000;
+bool multiply_out(const HostLevel &lv, const HostCsr &AP) {
+    // `down` has the pattern of (A P)^T
+    return lv.A.nnz() + 2 * AP.nnz() <= 2 * lv.A.nnz() + 2 * lv.P.nnz() + kLaunchEntries;
+}
+
 // Inverse of a dense SPD matrix (row-major, n x n) by Cholesky; false if a
 // pivot is not positive.
 bool spd_inverse(int n, std::vector<double> &M) {
@@ -347,6 +402,7 @@ int amg_build(const HostCsr &A0, const std::vector<double> &B0, const AmgHostPar
         lv.n_agg = na;
         lv.P = std::move(P);
         lv.R = R;
+        if (l > 0 && (levels[l - 1].up.n || multiply_out(lv, AP))) cycle_halves(lv, d, AP);
         levels.push_back(std::move(next));
     }
     // dense inverse of the coarsest level
