@@ -113,6 +113,13 @@ int oasis_p1_pattern(void *stream, const oasis_mesh *mesh, int32_t *row_ptr,
                      int32_t *col_idx, int64_t col_capacity, int32_t *nnz_out,
                      void *ws, size_t ws_bytes);
 
+/* The column indices (device int32 [nnz]) after oasis_p1_pattern with
+ * col_idx = NULL on the same mesh and workspace: it reads the lists that that
+ * call left in ws, instead of building them again, and the row_ptr that it
+ * wrote.  Synchronises `stream`. */
+int oasis_p1_pattern_columns(void *stream, const oasis_mesh *mesh, const int32_t *row_ptr,
+                             int32_t *col_idx, void *ws, size_t ws_bytes);
+
 /* Greedy first-fit colouring of the cells, visiting cells in decreasing
  * `priority` (device int32 [n_cell], pairwise distinct): every cell takes
  * the least colour not used by an already coloured cell sharing a dof.

@@ -74,3 +74,21 @@ def test_too_many_colours_and_equal_priorities_are_refused(oa):
         dm = oa.DeviceMesh.from_arrays(2, mesh.coords, mesh.cells, mesh.vert2dof, mesh.n_dof, dev())
         with pytest.raises(oa.OasisError):
             oa.color_cells(dm, T(pri, torch.int32))
+
+
+def test_pattern_in_one_call_and_in_two(oa):
+    """oasis_p1_pattern with col_idx against the binding's count and columns."""
+    import ctypes as C
+    import torch
+    from paper_1602_03643_amd import _lib as L
+    mesh = synth.permute_mesh(synth.channel(9, 9, 7), 2)[0]
+    say("pattern in one call", mesh.name)
+    dm = oa.DeviceMesh.from_arrays(mesh.dim, mesh.coords, mesh.cells, mesh.vert2dof, mesh.n_dof, dev())
+    pat, cm, nb, nnz = oa.p1_pattern(dm), dm.c(), C.c_size_t(), C.c_int32()
+    assert L.load().oasis_graph_workspace_size(C.byref(cm), C.byref(nb)) == 0
+    ws = torch.empty(nb.value, dtype=torch.uint8, device=dev())
+    rp, ci = torch.empty_like(pat.row_ptr), torch.empty_like(pat.col_idx)
+    ptr = lambda t: C.c_void_p(t.data_ptr())                            # noqa: E731
+    assert L.load().oasis_p1_pattern(None, C.byref(cm), ptr(rp), ptr(ci), ci.numel(), C.byref(nnz), ptr(ws),
+                                     ws.numel()) == 0
+    assert torch.equal(rp, pat.row_ptr) and torch.equal(ci, pat.col_idx) and nnz.value == ci.numel()
