@@ -42,11 +42,14 @@ static_assert(kDecBlocks <= kGradBlocks, "the launch has the blocks that sum");
 typedef short bf4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
+// to bfloat16, nearest even, one and two at a time (the lower half the first)
 __device__ __forceinline__ unsigned short f2bf(float f) {
-    // round to nearest even on the upper 16 bits
-    unsigned u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return static_cast<unsigned short>(u >> 16);
+    return __builtin_bit_cast(unsigned short, static_cast<__bf16>(f));
+}
+__device__ __forceinline__ unsigned f2bf(float lo, float hi) {
+    typedef float F2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 B2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((F2{lo, hi}), B2));
 }
 __device__ __forceinline__ float bf2f(unsigned short b) { return __uint_as_float(static_cast<unsigned>(b) << 16); }
 
@@ -256,9 +259,8 @@ __global__ __launch_bounds__(kBlock) void k_mp_feat2(int n, const double *__rest
                 for (int k = 0; k < kIn; ++k) acc += W[o * kIn + k] * xn[k];
                 v2[e] = acc;
             }
-            zw[p] = static_cast<unsigned>(f2bf(v2[0])) | (static_cast<unsigned>(f2bf(v2[1])) << 16);
-            hw[p] = static_cast<unsigned>(f2bf(fmaxf(v2[0], 0.f))) |
-                    (static_cast<unsigned>(f2bf(fmaxf(v2[1], 0.f))) << 16);
+            zw[p] = f2bf(v2[0], v2[1]);
+            hw[p] = f2bf(fmaxf(v2[0], 0.f), fmaxf(v2[1], 0.f));
         }
         if (STORE) *reinterpret_cast<uint4 *>(Z0 + i * kHid + q * 8) = make_uint4(zw[0], zw[1], zw[2], zw[3]);
         *reinterpret_cast<uint4 *>(H0 + i * kHid + q * 8) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
@@ -392,7 +394,7 @@ __global__ __launch_bounds__(kBlock) void k_mp_layer(int n, int l, const int *__
                                                      double *__restrict__ guess, const double *__restrict__ phi_prev,
                                                      const double *scal) {
     __shared__ unsigned short B[2 * kHid][kHid];
-    __shared__ unsigned short T[kTile][2 * kHid + 8];   // [h | a] per node, padded rows
+    __shared__ __align__(16) unsigned short T[kTile][2 * kHid + 8];   // [h | a] per node, padded rows
     __shared__ float cvec[kHid], wd[kHid];
     load_layer_weights(P, l, B);
     if (threadIdx.x < kHid) {
@@ -418,24 +420,17 @@ __global__ __launch_bounds__(kBlock) void k_mp_layer(int n, int l, const int *__
                 else
                     agg8(static_cast<int>(i), f0, rp, ci, Ks, s, Hin, true, a);
                 const float inv = static_cast<float>(-1.0 / si);
-                const unsigned hv[4] = {hq.x, hq.y, hq.z, hq.w};
                 unsigned av[4];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const unsigned lo = f2bf(a[2 * k] * inv), hi = f2bf(a[2 * k + 1] * inv);
-                    av[k] = lo | (hi << 16);
-                    T[ln][f0 + 2 * k] = static_cast<unsigned short>(hv[k] & 0xffffu);
-                    T[ln][f0 + 2 * k + 1] = static_cast<unsigned short>(hv[k] >> 16);
-                    T[ln][kHid + f0 + 2 * k] = static_cast<unsigned short>(lo);
-                    T[ln][kHid + f0 + 2 * k + 1] = static_cast<unsigned short>(hi);
-                }
-                if (STORE)
-                    *reinterpret_cast<uint4 *>(Aout + (size_t)i * kHid + f0) = make_uint4(av[0], av[1], av[2], av[3]);
+                for (int k = 0; k < 4; ++k) av[k] = f2bf(a[2 * k] * inv, a[2 * k + 1] * inv);
+                const uint4 aq = make_uint4(av[0], av[1], av[2], av[3]);
+                *reinterpret_cast<uint4 *>(&T[ln][f0]) = hq;
+                *reinterpret_cast<uint4 *>(&T[ln][kHid + f0]) = aq;
+                if (STORE) *reinterpret_cast<uint4 *>(Aout + (size_t)i * kHid + f0) = aq;
             } else {
-                for (int k = 0; k < 8; ++k) {
-                    T[ln][f0 + k] = 0;
-                    T[ln][kHid + f0 + k] = 0;
-                }
+                const uint4 none = make_uint4(0u, 0u, 0u, 0u);
+                *reinterpret_cast<uint4 *>(&T[ln][f0]) = none;
+                *reinterpret_cast<uint4 *>(&T[ln][kHid + f0]) = none;
             }
         }
         __syncthreads();
@@ -448,16 +443,15 @@ __global__ __launch_bounds__(kBlock) void k_mp_layer(int n, int l, const int *__
             acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kt = 0; kt < 4; ++kt) {
-                bf4 af, bfr;
+                const bf4 af = *reinterpret_cast<const bf4 *>(&T[r0 + m][kt * 16 + kq]);
+                bf4 bfr;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    af[q] = static_cast<short>(T[r0 + m][kt * 16 + kq + q]);
-                    bfr[q] = static_cast<short>(B[kt * 16 + kq + q][nt * 16 + m]);
-                }
+                for (int q = 0; q < 4; ++q) bfr[q] = static_cast<short>(B[kt * 16 + kq + q][nt * 16 + m]);
                 acc[nt] = mfma16(af, bfr, acc[nt]);
             }
         }
-        // epilogue: rows r0 + kq + q, column nt*16 + m
+        // epilogue: rows r0 + kq + q, column nt*16 + m; h and z take the
+        // places of the wave's own h and a, and leave in 16-byte pieces
         float dpart[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
@@ -465,14 +459,23 @@ __global__ __launch_bounds__(kBlock) void k_mp_layer(int n, int l, const int *__
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int ln = r0 + kq + q;
-                const long long i = base + ln;
                 const float z = acc[nt][q] + cvec[o];
-                const float hn = bf2f(T[ln][o]) + fmaxf(z, 0.f);
-                if (i < n) {
-                    if (STORE) Zout[(size_t)i * kHid + o] = f2bf(z);
-                    if (STORE || !LAST) Hout[(size_t)i * kHid + o] = f2bf(hn);
-                }
-                if (LAST) dpart[q] += bf2f(f2bf(hn)) * wd[o];
+                const unsigned short hn = f2bf(bf2f(T[ln][o]) + fmaxf(z, 0.f));
+                if (STORE) T[ln][kHid + o] = f2bf(z);
+                if (STORE || !LAST) T[ln][o] = hn;
+                if (LAST) dpart[q] += bf2f(hn) * wd[o];
+            }
+        }
+        if (STORE || !LAST) {
+            __builtin_amdgcn_wave_barrier();
+            const int ln = threadIdx.x >> 2, f0 = (threadIdx.x & 3) * 8;   // a row of this wave
+            const long long i = base + ln;
+            if (i < n) {
+                if (STORE)
+                    *reinterpret_cast<uint4 *>(Zout + (size_t)i * kHid + f0) =
+                        *reinterpret_cast<const uint4 *>(&T[ln][kHid + f0]);
+                *reinterpret_cast<uint4 *>(Hout + (size_t)i * kHid + f0) =
+                    *reinterpret_cast<const uint4 *>(&T[ln][f0]);
             }
         }
         if (LAST) {
@@ -597,7 +600,7 @@ __global__ __launch_bounds__(kWideBlock) void k_mp_bwd_dec(int n, const unsigned
 // Each thread moves eight features of a node in 16-byte pieces, and the next
 // tile's pieces are in flight while this one is multiplied (element by
 // element, one tile of 64 nodes at a time, a layer took 97 us on 200,000
-// nodes; now 44 us, 2.8 TB/s).  Two blocks of kGzWaves waves per CU, 16 nodes
+// nodes; now 19 us, 4.6 TB/s).  Two blocks of kGzWaves waves per CU, 16 nodes
 // a wave; four waves at a time hold the four 16x16 blocks of both weight
 // gradients over their 64 nodes, and the sets are summed at the end.
 constexpr int kGzWaves = 8, kGzBlock = kGzWaves * kWave, kGzTile = kGzWaves * 16, kGzSets = kGzWaves / 4;
@@ -613,7 +616,7 @@ __global__ __launch_bounds__(kGzBlock) void k_mp_bwd_gz(int n, int l, const doub
     __shared__ __align__(16) unsigned short Bn[kHid][kHid];     // Bn[o][k] = Wn_l[o][k]
     __shared__ __align__(16) unsigned short lds[4][kGzTile][W];
     auto &Tg = lds[0], &Th = lds[1], &Ta = lds[2], &Ty = lds[3];
-    __shared__ float gcp[kGzSets][kHid];
+    __shared__ float gcp[kGzSets][kHid], sc[kGzTile];
     for (int q = threadIdx.x; q < kHid * kHid; q += blockDim.x)
         Bn[q / kHid][q % kHid] = f2bf(P[kOffWn + l * kHid * kHid + q]);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -624,52 +627,51 @@ __global__ __launch_bounds__(kGzBlock) void k_mp_bwd_gz(int n, int l, const doub
     f4 gws = f4{0.f, 0.f, 0.f, 0.f}, gwn = f4{0.f, 0.f, 0.f, 0.f}, gc = f4{0.f, 0.f, 0.f, 0.f};
     const bf4 one = bf4{0x3f80, 0x3f80, 0x3f80, 0x3f80};
     const int ln = threadIdx.x >> 2, f0 = (threadIdx.x & 3) * 8;   // this thread's piece of a tile
-    struct Piece {
-        uint4 z, h, a;
-        float4 g0, g1;
-    };
-    auto fetch = [&](Piece &p, long long base) {
+    // (native vectors, each of its own: as a structure they went through
+    // scratch memory, and every load was waited for at once)
+    typedef unsigned U4 __attribute__((ext_vector_type(4)));
+    U4 pz, ph, pa;
+    f4 pg0, pg1;
+    double ps;   // (read where it is used it would wait for all of the next piece)
+    auto fetch = [&](long long base) {
         const long long i = base + ln < n ? base + ln : n - 1;
-        p.z = *reinterpret_cast<const uint4 *>(Zl + i * kHid + f0);
-        p.h = *reinterpret_cast<const uint4 *>(Hl + i * kHid + f0);
-        p.a = *reinterpret_cast<const uint4 *>(Al + i * kHid + f0);
-        p.g0 = *reinterpret_cast<const float4 *>(G + i * kHid + f0);
-        p.g1 = *reinterpret_cast<const float4 *>(G + i * kHid + f0 + 4);
+        pz = *reinterpret_cast<const U4 *>(Zl + i * kHid + f0);
+        ph = *reinterpret_cast<const U4 *>(Hl + i * kHid + f0);
+        pa = *reinterpret_cast<const U4 *>(Al + i * kHid + f0);
+        pg0 = *reinterpret_cast<const f4 *>(G + i * kHid + f0);
+        pg1 = *reinterpret_cast<const f4 *>(G + i * kHid + f0 + 4);
+        ps = s[i];
     };
     const long long step = (long long)gridDim.x * kGzTile;
     long long base = (long long)blockIdx.x * kGzTile;
-    Piece p;
-    if (base < n) fetch(p, base);
+    fetch(base);
     for (; base < n; base += step) {
         __syncthreads();
         {
             const bool in = base + ln < n;
-            const unsigned zw[4] = {p.z.x, p.z.y, p.z.z, p.z.w};
-            const float gv[8] = {p.g0.x, p.g0.y, p.g0.z, p.g0.w, p.g1.x, p.g1.y, p.g1.z, p.g1.w};
-            unsigned gw[4];
+            U4 g;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const float lo = bf2f(static_cast<unsigned short>(zw[k] & 0xffffu)) > 0.f ? gv[2 * k] : 0.f;
-                const float hi = bf2f(static_cast<unsigned short>(zw[k] >> 16)) > 0.f ? gv[2 * k + 1] : 0.f;
-                gw[k] = in ? static_cast<unsigned>(f2bf(lo)) | (static_cast<unsigned>(f2bf(hi)) << 16) : 0u;
+                const float g0 = k < 2 ? pg0[2 * k] : pg1[2 * k - 4], g1 = k < 2 ? pg0[2 * k + 1] : pg1[2 * k - 3];
+                const float lo = bf2f(static_cast<unsigned short>(pz[k] & 0xffffu)) > 0.f ? g0 : 0.f;
+                const float hi = bf2f(static_cast<unsigned short>(pz[k] >> 16)) > 0.f ? g1 : 0.f;
+                g[k] = in ? f2bf(lo, hi) : 0u;
             }
-            const uint4 g = make_uint4(gw[0], gw[1], gw[2], gw[3]), none = make_uint4(0u, 0u, 0u, 0u);
-            *reinterpret_cast<uint4 *>(&Tg[ln][f0]) = g;
-            *reinterpret_cast<uint4 *>(&Th[ln][f0]) = in ? p.h : none;
-            *reinterpret_cast<uint4 *>(&Ta[ln][f0]) = in ? p.a : none;
-            if (in) *reinterpret_cast<uint4 *>(GZ + (base + ln) * kHid + f0) = g;
+            const U4 none = U4{0u, 0u, 0u, 0u};
+            *reinterpret_cast<U4 *>(&Tg[ln][f0]) = g;
+            *reinterpret_cast<U4 *>(&Th[ln][f0]) = in ? ph : none;
+            *reinterpret_cast<U4 *>(&Ta[ln][f0]) = in ? pa : none;
+            if (f0 == 0) sc[ln] = static_cast<float>(ps);
+            if (in) *reinterpret_cast<U4 *>(GZ + (base + ln) * kHid + f0) = g;
         }
-        if (base + step < n) fetch(p, base + step);
+        fetch(base + step);
         __syncthreads();
         // Y = gz Wn / s for this wave's 16 nodes
         {
             const int r0 = wv * 16;
             float sv[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const long long i = base + r0 + kq + q;
-                sv[q] = static_cast<float>(s[i < n ? i : n - 1]);
-            }
+            for (int q = 0; q < 4; ++q) sv[q] = sc[r0 + kq + q];
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) {
                 f4 acc = f4{0.f, 0.f, 0.f, 0.f};
@@ -739,8 +741,8 @@ __global__ __launch_bounds__(kBlock) void k_mp_bwd_h(int n, int l, const int *__
                                                      const unsigned short *__restrict__ GZ,
                                                      const unsigned short *__restrict__ Y, float *__restrict__ G) {
     __shared__ unsigned short Bs[kHid][kHid];     // Bs[o][k] = Ws_l[o][k]
-    __shared__ unsigned short Tg[kTile][kHid + 8];
-    __shared__ float Tagg[kTile][kHid + 1];
+    __shared__ __align__(16) unsigned short Tg[kTile][kHid + 8];
+    __shared__ __align__(16) float Tagg[kTile][kHid + 4];
     for (int q = threadIdx.x; q < kHid * kHid; q += blockDim.x)
         Bs[q / kHid][q % kHid] = f2bf(P[kOffWs + l * kHid * kHid + q]);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -749,22 +751,24 @@ __global__ __launch_bounds__(kBlock) void k_mp_bwd_h(int n, int l, const int *__
     for (long long tile = tiles.first; tile < tiles.last; tile += tiles.step) {
         const long long base = tile * kTile;
         __syncthreads();
-        {
-            const int ln = threadIdx.x >> 2, f0 = (threadIdx.x & 3) * 8;
-            const long long i = base + ln;
-            if (i < n) {
-                float a[8];
-                agg8(static_cast<int>(i), f0, rp, ci, Ks, s, Y, false, a);
-                const float sc = static_cast<float>(-s[i]);
-                for (int k = 0; k < 8; ++k) Tagg[ln][f0 + k] = a[k] * sc;
-                for (int k = 0; k < 8; ++k) Tg[ln][f0 + k] = GZ[i * kHid + f0 + k];
-            } else {
-                for (int k = 0; k < 8; ++k) {
-                    Tagg[ln][f0 + k] = 0.f;
-                    Tg[ln][f0 + k] = 0;
-                }
-            }
+        // eight features a thread, in 16-byte pieces
+        const int ln = threadIdx.x >> 2, f0 = (threadIdx.x & 3) * 8;
+        const long long i = base + ln;
+        float4 g0 = make_float4(0.f, 0.f, 0.f, 0.f), g1 = g0, a0 = g0, a1 = g0;
+        uint4 gz = make_uint4(0u, 0u, 0u, 0u);
+        if (i < n) {
+            g0 = *reinterpret_cast<const float4 *>(G + i * kHid + f0);
+            g1 = *reinterpret_cast<const float4 *>(G + i * kHid + f0 + 4);
+            gz = *reinterpret_cast<const uint4 *>(GZ + i * kHid + f0);
+            float a[8];
+            agg8(static_cast<int>(i), f0, rp, ci, Ks, s, Y, false, a);
+            const float sc = static_cast<float>(-s[i]);
+            a0 = make_float4(a[0] * sc, a[1] * sc, a[2] * sc, a[3] * sc);
+            a1 = make_float4(a[4] * sc, a[5] * sc, a[6] * sc, a[7] * sc);
         }
+        *reinterpret_cast<float4 *>(&Tagg[ln][f0]) = a0;
+        *reinterpret_cast<float4 *>(&Tagg[ln][f0 + 4]) = a1;
+        *reinterpret_cast<uint4 *>(&Tg[ln][f0]) = gz;
         __syncthreads();
         const int r0 = wv * 16;
 #pragma unroll
@@ -772,20 +776,26 @@ __global__ __launch_bounds__(kBlock) void k_mp_bwd_h(int n, int l, const int *__
             f4 acc = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt) {
-                bf4 af, bfr;
+                const bf4 af = *reinterpret_cast<const bf4 *>(&Tg[r0 + m][kt * 16 + kq]);
+                bf4 bfr;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    af[q] = static_cast<short>(Tg[r0 + m][kt * 16 + kq + q]);
-                    bfr[q] = static_cast<short>(Bs[kt * 16 + kq + q][nt * 16 + m]);
-                }
+                for (int q = 0; q < 4; ++q) bfr[q] = static_cast<short>(Bs[kt * 16 + kq + q][nt * 16 + m]);
                 acc = mfma16(af, bfr, acc);
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int ln = r0 + kq + q, o = nt * 16 + m;
-                const long long i = base + ln;
-                if (i < n) G[i * kHid + o] += acc[q] + Tagg[ln][o];
+                float &sum = Tagg[r0 + kq + q][nt * 16 + m];
+                sum = acc[q] + sum;
             }
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (i < n) {   // a row of this wave
+            const float4 s0 = *reinterpret_cast<const float4 *>(&Tagg[ln][f0]);
+            const float4 s1 = *reinterpret_cast<const float4 *>(&Tagg[ln][f0 + 4]);
+            *reinterpret_cast<float4 *>(G + i * kHid + f0) =
+                make_float4(g0.x + s0.x, g0.y + s0.y, g0.z + s0.z, g0.w + s0.w);
+            *reinterpret_cast<float4 *>(G + i * kHid + f0 + 4) =
+                make_float4(g1.x + s1.x, g1.y + s1.y, g1.z + s1.z, g1.w + s1.w);
         }
     }
 }
