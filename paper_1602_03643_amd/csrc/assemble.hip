@@ -157,7 +157,7 @@ __global__ __launch_bounds__(kBlock) void k_slot_fill(int ncell, int w, const in
 // each dof's slots without the empty ones and ascending, in place (one wave
 // per dof); deg[d]: their number.  Ascending, so that neighbouring rows
 // read neighbouring cells at the same time: in colour order the rows took
-// 732 us instead of 429 on the 97x97x73 channel.  Up to 64 slots are ranked
+// 732 us where 429 then did on the 97x97x73 channel.  Up to 64 slots are ranked
 // from lane to lane; longer tables are only packed.
 __global__ __launch_bounds__(kBlock) void k_slot_pack(int n, int w, int *slots, int *__restrict__ deg) {
     const int wl = threadIdx.x & (kWave - 1);
@@ -187,57 +187,84 @@ __global__ __launch_bounds__(kBlock) void k_slot_clear(long long m, int4 *slots)
         slots[i] = int4{-1, -1, -1, -1};
 }
 
-// u_bar interleaved per dof, one gather per vertex
+// What the convection form needs of a vertex besides its dof, coordinates and
+// u_bar, as D planes of two doubles.  Neighbouring rows gather
+// neighbouring vertices, so a plane's 64 gathers lie in some 8 lines, those of
+// a structure of 64 bytes per vertex in 32, four times over (450 us where the
+// planes take 329; coordinates and u_bar of 24 and 32 bytes, 355).
 template <int D>
-__global__ __launch_bounds__(kBlock) void k_interleave(int n, P3 U, double *__restrict__ ub) {
-    constexpr int UW = D == 3 ? 4 : 2;
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+__global__ __launch_bounds__(kBlock) void k_vertices(int nvert, const int *__restrict__ v2d,
+                                                     const double *__restrict__ X, P3 U, double2 *__restrict__ vert) {
+    for (int v = blockIdx.x * kBlock + threadIdx.x; v < nvert; v += gridDim.x * kBlock) {
+        const int d = v2d[v];
+        double r[2 * D];
 #pragma unroll
-        for (int c = 0; c < D; ++c) ub[(long long)i * UW + c] = U.p[c][i];
-        if (D == 3) ub[(long long)i * UW + 3] = 0.0;
+        for (int c = 0; c < D; ++c) {
+            r[c] = X[(long long)v * D + c];
+            r[D + c] = U.p[c][d];
+        }
+#pragma unroll
+        for (int q = 0; q < D; ++q) vert[(long long)q * nvert + v] = double2{r[2 * q], r[2 * q + 1]};
     }
 }
 
-// One thread per row; its entries in kRowCap registers, matched by column
-// (as in the time step's row assembly), NC cells' loads in flight (a tail's
-// clamped copies are added with weight 0).  Longer rows add to their own
-// entries in memory.  Bound by the gathers incidence -> vertices -> dofs ->
-// coordinates and u_bar that the registers of a row leave room for.
+// One thread per row; its entries and their columns in its column of LDS,
+// found by halving (matched one by one in registers, 256 instructions a cell,
+// convection on 670,000 rows took 434 us where this took 380), NC cells' loads
+// in flight (four: 355) and the row's slots read NC at a time (302 us with the
+// planes).
+// Rows that are longer, or not in column order, add to their own entries in
+// memory.  Bound by the gathers incidence -> vertices -> dofs -> coordinates
+// and u_bar.
 constexpr int kRowCap = 16;
-template <int D, int FORM, int NC = D == 3 && FORM == OASIS_FORM_CONV ? 3 : 2>
+template <int D, int FORM, int NC = D == 3 && FORM == OASIS_FORM_CONV ? 4 : 2>
 __global__ __launch_bounds__(kBlock) void k_assemble_rows(int n, int w, const int *__restrict__ slots,
                                                           const int *__restrict__ deg,
                                                           const int *__restrict__ cells,
-                                                          const int *__restrict__ v2d,
+                                                          const int *__restrict__ v2d, int nvert,
                                                           const double *__restrict__ X,
-                                                          const double *__restrict__ ub,
+                                                          const double2 *__restrict__ vert,
                                                           const int *__restrict__ rp,
                                                           const int *__restrict__ ci, const double *base,
                                                           double *out, double alpha, int gk) {
-    constexpr int NV = D + 1, UW = D == 3 ? 4 : 2;
+    constexpr int NV = D + 1;
     constexpr double mfac = 1.0 / ((D + 1) * (D + 2));
     constexpr bool kConv = FORM == OASIS_FORM_CONV;
     struct Cell {
         double x[NV][D], u[kConv ? NV : 1][D];
         int dof[NV], la;
     };
+    // a thread's row: columns and sums (no other thread reads them)
+    __shared__ int col[kRowCap][kBlock];
+    __shared__ double a[kRowCap][kBlock];
     const RowRange<1> rr(n);
     for (long long row = rr.first + rr.gid; row < rr.last; row += rr.ngroups) {
         const int s = rp[row], len = rp[row + 1] - s;
         const int m = deg[row];
         const int *inc = slots + row * w;
-        auto load = [&](int t, Cell &C) {
-            const int code = inc[t];
+        auto load = [&](int code, Cell &C) {
             const int cell = code / NV;
             C.la = code - cell * NV;
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
                 const int v = cells[(long long)cell * NV + k];
                 C.dof[k] = v2d[v];
+                if constexpr (kConv) {
+                    double r[2 * D];
 #pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    C.x[k][c] = X[(long long)v * D + c];
-                    if constexpr (kConv) C.u[k][c] = ub[(long long)C.dof[k] * UW + c];
+                    for (int q = 0; q < D; ++q) {
+                        const double2 p = vert[(long long)q * nvert + v];
+                        r[2 * q] = p.x;
+                        r[2 * q + 1] = p.y;
+                    }
+#pragma unroll
+                    for (int c = 0; c < D; ++c) {
+                        C.x[k][c] = r[c];
+                        C.u[k][c] = r[D + c];
+                    }
+                } else {
+#pragma unroll
+                    for (int c = 0; c < D; ++c) C.x[k][c] = X[(long long)v * D + c];
                 }
             }
         };
@@ -280,38 +307,54 @@ __global__ __launch_bounds__(kBlock) void k_assemble_rows(int n, int w, const in
                 }
             }
         };
-        if (len <= kRowCap) {
-            int col[kRowCap];
-            double a[kRowCap];
+        const int tid = threadIdx.x;
+        bool fits = len <= kRowCap;
+        if (fits) {
+            int last = -1;
 #pragma unroll
             for (int q = 0; q < kRowCap; ++q) {
-                col[q] = q < len ? ci[s + q] : -1;
-                a[q] = base && q < len ? base[s + q] : 0.0;
+                const int c = q < len ? ci[s + q] : 0x7fffffff;
+                col[q][tid] = c;
+                a[q][tid] = base && q < len ? base[s + q] : 0.0;
+                fits = fits && (q >= len || c > last);   // ascending
+                last = c;
             }
+        }
+        if (fits) {
             for (int t = 0; t < m; t += NC) {
+                // (a row has w slots, a multiple of NC)
+                typedef int Codes __attribute__((ext_vector_type(NC)));
+                const Codes code = *reinterpret_cast<const Codes *>(inc + t);
                 Cell c[NC];
 #pragma unroll
-                for (int h = 0; h < NC; ++h) load(t + h < m ? t + h : t, c[h]);
+                for (int h = 0; h < NC; ++h) load(t + h < m ? code[h] : code[0], c[h]);
 #pragma unroll
                 for (int h = 0; h < NC; ++h) {
+                    if (t + h >= m) break;
                     double v[NV];
-                    entries(c[h], t + h < m ? 1.0 : 0.0, v);
+                    entries(c[h], 1.0, v);
+                    // the entry's place, by halving the sorted columns
+                    int at[NV];
+#pragma unroll
+                    for (int j = 0; j < NV; ++j) at[j] = 0;
+#pragma unroll
+                    for (int half = kRowCap / 2; half > 0; half >>= 1)
+#pragma unroll
+                        for (int j = 0; j < NV; ++j) at[j] += col[at[j] + half][tid] <= c[h].dof[j] ? half : 0;
 #pragma unroll
                     for (int j = 0; j < NV; ++j)
-#pragma unroll
-                        for (int q = 0; q < kRowCap; ++q)
-                            a[q] = __fma_rn(col[q] == c[h].dof[j] ? 1.0 : 0.0, v[j], a[q]);
+                        if (col[at[j]][tid] == c[h].dof[j]) a[at[j]][tid] += v[j];
                 }
             }
 #pragma unroll
             for (int q = 0; q < kRowCap; ++q)
-                if (q < len) out[s + q] = a[q];
+                if (q < len) out[s + q] = a[q][tid];
         } else {
             for (int q = 0; q < len; ++q) out[s + q] = base ? base[s + q] : 0.0;
             for (int t = 0; t < m; ++t) {
                 Cell c;
                 double v[NV];
-                load(t, c);
+                load(inc[t], c);
                 entries(c, 1.0, v);
 #pragma unroll
                 for (int j = 0; j < NV; ++j)
@@ -448,7 +491,7 @@ struct AssembleWs {
     int w = 0;                       // slots per dof
     unsigned char *color = nullptr;
     int *slots = nullptr, *deg = nullptr;
-    double *ub = nullptr;
+    double2 *vert = nullptr;         // planes of vertices
 };
 
 void carve_assemble(Carver &c, const oasis_mesh *m, AssembleWs &a) {
@@ -456,7 +499,7 @@ void carve_assemble(Carver &c, const oasis_mesh *m, AssembleWs &a) {
     a.color = c.take<unsigned char>(m->n_cell);
     a.slots = c.take<int>((size_t)m->n_dof * a.w);
     a.deg = c.take<int>(m->n_dof);
-    a.ub = c.take<double>((size_t)m->n_dof * (m->dim == 3 ? 4 : 2));
+    a.vert = c.take<double2>((size_t)m->n_vert * m->dim);
 }
 
 template <int D>
@@ -477,10 +520,11 @@ int assemble_rows(hipStream_t s, const oasis_mesh *m, int form, P3 U, double alp
     hipLaunchKernelGGL(k_slot_pack, dim3(grid_for((long long)n * kWave, kBlock, 16384)), dim3(kBlock), 0, s, n, a.w,
                        a.slots, a.deg);
     if (form == OASIS_FORM_CONV)
-        hipLaunchKernelGGL(k_interleave<D>, dim3(grid_for(n, kBlock, 8192)), dim3(kBlock), 0, s, n, U, a.ub);
+        hipLaunchKernelGGL(k_vertices<D>, dim3(grid_for(m->n_vert, kBlock, 8192)), dim3(kBlock), 0, s, m->n_vert,
+                           m->vert2dof, m->coords, U, a.vert);
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(grid_for(n, kBlock, 1 << 20)), dim3(kBlock), 0, s, n, a.w, a.slots, a.deg,
-                           m->cells, m->vert2dof, m->coords, a.ub, out->row_ptr, out->col_idx, base,
+                           m->cells, m->vert2dof, m->n_vert, m->coords, a.vert, out->row_ptr, out->col_idx, base,
                            static_cast<double *>(out->val), alpha, form - OASIS_FORM_GRAD_X);
     };
     if (form == OASIS_FORM_MASS)

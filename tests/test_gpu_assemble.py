@@ -72,3 +72,18 @@ def test_entries_outside_the_pattern_are_skipped(oa):
     rp = np.concatenate([[0], np.cumsum(np.bincount(rows[keep], minlength=mesh.n_dof))])
     cut = oa.DeviceCSR(T(rp, torch.int32), pat.col_idx[torch.as_tensor(keep, device=full.device)].contiguous())
     assert torch.equal(oa.assemble_p1(dm, cut, oa.FORM_STIFF), full[torch.as_tensor(keep, device=full.device)])
+
+
+def test_rows_out_of_column_order(oa):
+    """A matrix whose rows list their columns backwards: the rows' entries are
+    found one by one, and are those of the sorted matrix."""
+    mesh = synth.channel(9, 9, 7)
+    say("assembly on reversed rows", mesh.name)
+    dm, pat, _ = device_mesh(mesh)
+    rp = pat.row_ptr.cpu().numpy()
+    back = np.concatenate([np.arange(rp[i + 1] - 1, rp[i] - 1, -1) for i in range(mesh.n_dof)])
+    rev = oa.DeviceCSR(pat.row_ptr, pat.col_idx[torch.as_tensor(back, device=pat.col_idx.device)].contiguous())
+    u = [T(v) for v in np.random.default_rng(5).normal(size=(3, mesh.n_dof))]
+    for form in (oa.FORM_MASS, oa.FORM_CONV):
+        want = oa.assemble_p1(dm, pat, form, uab=u)[torch.as_tensor(back, device=pat.col_idx.device)]
+        assert torch.equal(oa.assemble_p1(dm, rev, form, uab=u), want)
