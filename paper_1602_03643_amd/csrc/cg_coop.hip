@@ -39,7 +39,7 @@
 // 780 rows each: about 1.7 us for each exchange, 0.4 us for the product, the
 // rest block reductions, barriers and two divisions), FP32 with the null
 // vector 12 -> 6.2 us, 33x33x25 FP32 9.5 -> 4.7 us, 17x17x13 FP64 12 -> 3.8
-// us, the 1089-row square 8 -> 3.3 us.
+// us, the 1089-row square 8 -> 3.3 us, and by one block (k_cg_one) 2.7 us.
 #include <algorithm>
 
 #include "coop.hpp"
@@ -68,6 +68,23 @@ struct CoopArgs {
 constexpr int kCopies = kXcds;
 constexpr int kSlotWords = 2 * 3 * kCopies * kCoopBlocks;
 __device__ __forceinline__ int slot_set(int kind, int buf) { return (kind * 3 + buf) * kCopies * kCoopBlocks; }
+
+// the state as k_cg_p1 and k_cg_p2 leave it
+__device__ __forceinline__ void leave(CGState *st, int flag, int it, double rr, double wrr, double rr_prev) {
+    const int last = flag ? it : it - 1;   // the last iteration whose residual was seen
+    if (flag) {
+        st->flag = flag;
+        st->it_done = it;
+        if (flag != 2) st->wrr = wrr;
+    }
+    if (!flag || flag == 2) {
+        st->rr[last & 1] = rr;
+        st->wrr_it = wrr;
+        st->it_last = last;
+    } else {
+        st->rr[(it + 1) & 1] = rr_prev;
+    }
+}
 
 // BS: threads of a block, and the most rows it has.
 template <typename T, int BS>
@@ -275,21 +292,147 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
         xg[row] = x;
         static_cast<RP<T> *>(a.nxt[it & 1])[row] = RP<T>{r, p};
     }
-    if (bid == 0 && t == 0) {
-        const int last = flag ? it : it - 1;   // the last iteration whose residual was seen
-        if (flag) {
-            st->flag = flag;
-            st->it_done = it;
-            if (flag != 2) st->wrr = wrr;
+    if (bid == 0 && t == 0) leave(st, flag, it, rr, wrr, rr_prev);
+}
+
+
+// The same run by one block, R rows a thread, for systems that fit it: what
+// the blocks exchange lies in LDS, and an iteration is two block sums and
+// three barriers.  1089 rows of 7 entries, FP64: 3.7 us an iteration by five
+// blocks, 2.7 by one (3.5 with the padding's gathers); the limit is the
+// registers of two rows.
+constexpr int kOneThreads = 1024, kOneRows = 2;
+template <typename T, int R>
+__global__ __launch_bounds__(kOneThreads) void k_cg_one(CoopArgs a) {
+    constexpr int E = kEll, WAVES = kOneThreads / kWave;
+    __shared__ T dir[R * kOneThreads];
+    __shared__ double red[2][2][WAVES];   // [sum][value]: the waves' parts
+    const int t = threadIdx.x, wv = t / kWave, wl = t & (kWave - 1);
+    CGState *st = a.st;
+    const RP<T> *cur = static_cast<const RP<T> *>(a.cur);
+    T *xg = static_cast<T *>(a.x);
+    const T *vn = static_cast<const T *>(a.vnull);
+    T val[R][E], x[R], r[R], p[R], v[R];
+    double wgt[R];
+    unsigned idx[R][E / 2];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int row = t + k * kOneThreads;
+        const bool own = row < a.n;
+        const int at = own ? row : 0;
+        const short *off = a.cols.offsets(at);
+        const T *ev = static_cast<const T *>(a.eval) + static_cast<size_t>(at) * kEll;
+#pragma unroll
+        for (int g = 0; g < E / 4; ++g) {
+            const short4 d = *reinterpret_cast<const short4 *>(off + 4 * g);
+            T w[4];
+            load4(ev + 4 * g, w);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) val[k][4 * g + q] = own ? w[q] : T(0);
+            idx[k][2 * g] = static_cast<unsigned>(ell_col(at, d.x, a.n) | ell_col(at, d.y, a.n) << 16);
+            idx[k][2 * g + 1] = static_cast<unsigned>(ell_col(at, d.z, a.n) | ell_col(at, d.w, a.n) << 16);
         }
-        if (!flag || flag == 2) {
-            st->rr[last & 1] = rr;
-            st->wrr_it = wrr;
-            st->it_last = last;
-        } else {
-            st->rr[(it + 1) & 1] = rr_prev;
+        const RP<T> me = cur[at];
+        // a thread without a row has zeros throughout
+        x[k] = own ? xg[at] : T(0);
+        r[k] = own ? me.r : T(0);
+        p[k] = own && !a.beta_zero ? me.p : T(0);
+        v[k] = own && vn ? vn[at] : T(0);
+        wgt[k] = own ? static_cast<double>(static_cast<const T *>(a.wgt)[at]) : 0.0;
+    }
+    // pairs of entries that some row has: 8 of 16 slots are padding in 2D, and
+    // the gathers from LDS are half of an iteration
+    __shared__ int pairs[WAVES];
+    int np = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+            if (__ballot(val[k][e] != T(0))) np = e / 2 + 1;
+    if (wl == 0) pairs[wv] = np;
+    __syncthreads();
+    for (int w = 0; w < WAVES; ++w) np = max(np, pairs[w]);
+    np = __builtin_amdgcn_readfirstlane(np);
+    const double tol2 = st->tol2, upd2 = st->upd2;
+    double rr_prev = st->rr[(a.it0 + 1) & 1];
+    // the block's sums in every thread, in a fixed order
+    auto total = [&](double &s0, double &s1, int kind) {
+        s0 = wave_sum(s0);
+        s1 = wave_sum(s1);
+        if (wl == 0) {
+            red[kind][0][wv] = s0;
+            red[kind][1][wv] = s1;
+        }
+        __syncthreads();
+        s0 = row_sum(red[kind][0][wl & (WAVES - 1)]);
+        s1 = row_sum(red[kind][1][wl & (WAVES - 1)]);
+    };
+    static_assert(WAVES == 16, "a row of lanes holds the waves' parts");
+
+    int flag = 0, it = a.it0;
+    double rr = 0.0, wrr = 0.0;
+    for (; it < a.it0 + a.m; ++it) {
+        rr = wrr = 0.0;
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const double rd = r[k];
+            rr += rd * rd;
+            wrr += wgt[k] * rd * rd;
+        }
+        total(rr, wrr, 0);
+        if (!finite(wrr) || !finite(rr))
+            flag = 3;
+        else if (wrr <= tol2)
+            flag = 1;
+        else if (wrr <= upd2)
+            flag = 4;
+        if (flag) break;
+        const bool fresh = a.beta_zero && it == a.it0;
+        const T beta = fresh ? T(0) : static_cast<T>(rr / rr_prev);
+        rr_prev = rr;
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            p[k] = fresh ? r[k] : fma_t(beta, p[k], r[k]);
+            dir[t + k * kOneThreads] = p[k];
+        }
+        __syncthreads();
+        T q[R];
+        double pq = 0.0, vq = 0.0;
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            q[k] = T(0);
+#pragma unroll
+            for (int e = 0; e < E; e += 2) {
+                if (e / 2 >= np) break;
+                unsigned both = idx[k][e / 2];
+                asm volatile("" : "+v"(both));   // unpacked here, not once into 16 registers
+                q[k] += val[k][e] * dir[both & 0xffffu];
+                q[k] += val[k][e + 1] * dir[both >> 16];
+            }
+            pq += static_cast<double>(p[k]) * static_cast<double>(q[k]);
+            vq += static_cast<double>(v[k]) * static_cast<double>(q[k]);
+        }
+        total(pq, vq, 1);
+        if (!(pq > 0.0) || !finite(pq)) {
+            flag = finite(pq) ? 2 : 3;
+            break;
+        }
+        const T al = static_cast<T>(rr / pq), cv = static_cast<T>(vq);
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            x[k] += al * p[k];
+            r[k] -= al * (vn ? q[k] - cv * v[k] : q[k]);
         }
     }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int row = t + k * kOneThreads;
+        if (row < a.n) {
+            xg[row] = x[k];
+            static_cast<RP<T> *>(a.nxt[it & 1])[row] = RP<T>{r[k], p[k]};
+        }
+    }
+    if (t == 0) leave(st, flag, it, rr, wrr, rr_prev);
 }
 
 // every exchange slot empty
@@ -351,6 +494,14 @@ int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T 
     a.beta_zero = beta_zero ? 1 : 0;
     a.slots[0] = reinterpret_cast<u64 *>(w.partA);
     a.slots[1] = reinterpret_cast<u64 *>(w.partB);
+    if (n <= kOneThreads * kOneRows) {
+        if (n <= kOneThreads)
+            hipLaunchKernelGGL((k_cg_one<T, 1>), dim3(1), dim3(kOneThreads), 0, s, a);
+        else
+            hipLaunchKernelGGL((k_cg_one<T, kOneRows>), dim3(1), dim3(kOneThreads), 0, s, a);
+        OASIS_TRY_LAUNCH();
+        return OASIS_OK;
+    }
     hipLaunchKernelGGL(k_words_clear<T>, dim3(grid_for(n, kBlock, 1024)), dim3(kBlock), 0, s, n, a);
     OASIS_TRY_LAUNCH();
     void *args[] = {&a};
