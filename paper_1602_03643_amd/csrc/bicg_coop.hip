@@ -73,7 +73,7 @@ struct BiCoopArgs {
     void *x[3];
     void *keep_s[3], *keep_t[3];   // s and t while an explicit residual is formed at the s stage
     void *v[3], *rhat[3];          // where these are in memory (LEAN)
-    BiBlock *blk;          // results, and glob.pause: kCoopLost or kCoopUnfit
+    BiBlock *blk;          // results, and glob.pause: kCoopUnfit
     double rtol2;
     int maxit, inner;
     void *ex[3];           // sets of vector words, [NR][n] of T each
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
         const long long began = wall_clock64();
         int k = 0;
         while (again()) {
-            if ((++k & 63) == 0 && (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopLost ||
+            if ((++k & 63) == 0 && (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopUnfit ||
                                     wall_clock64() - began > kCoopTicks)) {
                 quit = 1;
                 return;
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
             }
         }
         if (!total(c, nv)) {
-            if (t == 0) atomicMax(flag, kCoopLost);
+            if (t == 0) atomicMax(flag, kCoopUnfit);
             return;
         }
         const double s0 = all[lk], tol2 = get(kTol2 + lk);
@@ -618,7 +618,6 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
     OASIS_TRY(nrhs == 1 ? (launch<T, 1>(s, grid, a)) : nrhs == 2 ? (launch<T, 2>(s, grid, a)) : (launch<T, 3>(s, grid, a)));
     BiBlock h{};
     OASIS_TRY(read_state(s, w.stage, a.blk, &h, sizeof(h)));
-    if (h.glob.pause == kCoopLost) return OASIS_EHIP;
     if (h.glob.pause == kCoopUnfit) {
         w.coop_off = true;
         return OASIS_EUNSUPPORTED;

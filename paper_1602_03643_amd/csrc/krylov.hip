@@ -1051,9 +1051,8 @@ static int cg_run(hipStream_t s, int n, const int *rp, const int *ci, const T *v
         }
         it += m;
         OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
-        if (h.flag == 5) return OASIS_EHIP;
-        if (h.flag == 6) {
-            // no iteration has run
+        if (h.flag == 5) {
+            // no iteration counts
             it -= m;
             OASIS_TRY(leave_coop(it));
             continue;
@@ -1251,9 +1250,8 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
         it += m;
         nin = g.p2;
         OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
-        if (h.flag == 5) return OASIS_EHIP;
-        if (h.flag == 6) {
-            // no iteration has run
+        if (h.flag == 5) {
+            // no iteration counts
             it -= m;
             OASIS_TRY(leave_coop(it));
             nin = gv;

@@ -16,7 +16,7 @@ struct CGState {
     double upd2;       // mixed precision: replace the residual once wrr <= upd2
     int flag;          // 0 running, 1 converged candidate, 2 breakdown, 3 non-finite,
                        // 4 residual replacement due (mixed precision),
-                       // 5, 6 a cooperative run that was lost or that does not fit (cg_coop.hip)
+                       // 5 a cooperative run that does not fit or ran out of time (cg_coop.hip)
     int it_done;       // iteration index at which flag was raised
     double wrr_it;     // weighted r.r entering iteration it_last (the last one that ran)
     int it_last;
@@ -175,7 +175,8 @@ constexpr int kCoopRun = 4096;
 
 // A whole BiCGStab solve in one cooperative launch (bicg_coop.hip), for one to
 // three right-hand sides; arguments and results of bicgstab_solve.
-// EUNSUPPORTED, with nothing changed: not for this system, device or tuning.
+// EUNSUPPORTED: not for this system, device or tuning, or out of time; the
+// other kernels go on from x.
 template <typename T>
 int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const *b, T *const *x, double rtol, int maxit,
                     BiWork<T> &w, SolveOut *out, bool inner);
