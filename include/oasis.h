@@ -246,6 +246,11 @@ typedef struct {
     int32_t ell_patterns; /* column storage the products used: > 0 the number of distinct
                              per-row offset lists of the ELL dictionary, -1 per-entry
                              16-bit ELL offsets, 0 CSR */
+    int32_t coop_runs;    /* launches that did many iterations each (CG) or a whole solve
+                             (BiCGStab) on systems of up to 1024 rows per CU; 0: every
+                             iteration was launched */
+    int32_t coop_lost;    /* such launches that do not count: the solve went on with the
+                             launched iterations */
 } oasis_krylov_stats;
 
 /* Workspace for oasis_pcg / oasis_bicgstab with nrhs right-hand sides. */
@@ -492,6 +497,7 @@ typedef struct {
     int32_t iters_c[4];       /* BiCGStab iterations per scalar */
     double res_c[4];
     double ms_scalars;        /* scalar phase (included in ms_total) */
+    int32_t coop_runs, coop_lost;  /* of all the step's solves; see oasis_krylov_stats */
 } oasis_step_stats;
 
 /* Workspace for a handle on this mesh/pattern/params. */

@@ -61,7 +61,8 @@ class KrylovOpts(C.Structure):
 
 class KrylovStats(C.Structure):
     _fields_ = [("iters", i32), ("outer_iters", i32), ("status", i32), ("restarts", i32),
-                ("rel_res", f64), ("kernel_ms", f64), ("kernel_count", i32), ("ell_patterns", i32)]
+                ("rel_res", f64), ("kernel_ms", f64), ("kernel_count", i32), ("ell_patterns", i32),
+                ("coop_runs", i32), ("coop_lost", i32)]
 
 
 class AmgParams(C.Structure):
@@ -93,7 +94,7 @@ class StepStats(C.Structure):
                 ("status", i32), ("guess_used", i32), ("res_u", f64 * 3), ("res_p", f64),
                 ("ms_assemble", f64), ("ms_velocity", f64), ("ms_pressure", f64),
                 ("ms_update", f64), ("ms_total", f64), ("iters_m", i32 * 3), ("iters_c", i32 * 4),
-                ("res_c", f64 * 4), ("ms_scalars", f64)]
+                ("res_c", f64 * 4), ("ms_scalars", f64), ("coop_runs", i32), ("coop_lost", i32)]
 
 
 _SIGS = {

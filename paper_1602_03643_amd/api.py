@@ -221,7 +221,7 @@ def _opts(rtol, maxit, precision, inner_rtol, max_outer, check_every, time_kerne
 def _stats(st):
     return dict(iters=st.iters, outer_iters=st.outer_iters, status=st.status, restarts=st.restarts,
                 rel_res=st.rel_res, kernel_ms=st.kernel_ms, kernel_count=st.kernel_count,
-                ell_patterns=st.ell_patterns)
+                ell_patterns=st.ell_patterns, coop_runs=st.coop_runs, coop_lost=st.coop_lost)
 
 
 def pcg(A: DeviceCSR, b, x, rtol=1e-8, maxit=10000, precision=L.F64, inner_rtol=0.1, max_outer=50,
@@ -447,7 +447,7 @@ class IPCS:
                  ms_velocity=stats.ms_velocity, ms_pressure=stats.ms_pressure, ms_update=stats.ms_update,
                  ms_total=stats.ms_total, iters_m=list(stats.iters_m)[: self.dim],
                  iters_c=list(stats.iters_c)[: self.n_scalars], res_c=list(stats.res_c)[: self.n_scalars],
-                 ms_scalars=stats.ms_scalars, rc=rc)
+                 ms_scalars=stats.ms_scalars, coop_runs=stats.coop_runs, coop_lost=stats.coop_lost, rc=rc)
         return d
 
     def pressure_amg(self, precision=L.F64, theta=0.0, coarse_size=0, max_levels=0, stream=None,

@@ -428,6 +428,7 @@ extern "C" int oasis_amg_pcg(void *stream, oasis_amg *h, const double *b, double
     stats->kernel_ms = so.kernel_ms;
     stats->kernel_count = so.kernel_count;
     stats->ell_patterns = d.ell_storage;
+    stats->coop_runs = stats->coop_lost = 0;
     return rc;
 }
 

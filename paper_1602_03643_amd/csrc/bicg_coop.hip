@@ -568,7 +568,7 @@ int launch(hipStream_t s, int grid, BiCoopArgs &a) {
 
 template <typename T>
 int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const *b, T *const *x, double rtol, int maxit,
-                    BiWork<T> &w, SolveOut *out, bool inner) {
+                    BiWork<T> &w, SolveOut *out, bool inner, int *lost) {
     // one row per thread of one block per CU; a kernel and grid that the
     // caller asked for are left as they are.  An iteration takes 10-20 us:
     // kCoopRun of them bound a launch that does not converge.
@@ -620,6 +620,7 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
     OASIS_TRY(read_state(s, w.stage, a.blk, &h, sizeof(h)));
     if (h.glob.pause == kCoopUnfit) {
         w.coop_off = true;
+        *lost += 1;
         return OASIS_EUNSUPPORTED;
     }
     int worst = OASIS_OK;
@@ -629,6 +630,7 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
         out[k].status = o.event;
         out[k].iters = o.it_rec;
         out[k].replacements = o.active;
+        out[k].coop = 1;
         if (!(o.wrr_rec < 0.0)) out[k].rel_res = o.wbb > 0.0 ? std::sqrt(o.wrr_rec / o.wbb) : std::sqrt(o.wrr_rec);
         if (o.event != OASIS_OK && (worst == OASIS_OK || o.event < worst)) worst = o.event;
     }
@@ -636,8 +638,8 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
 }
 
 template int bicg_coop_solve<double>(hipStream_t, int, int, const double *, const double *const *, double *const *,
-                                     double, int, BiWork<double> &, SolveOut *, bool);
+                                     double, int, BiWork<double> &, SolveOut *, bool, int *);
 template int bicg_coop_solve<float>(hipStream_t, int, int, const float *, const float *const *, float *const *, double,
-                                    int, BiWork<float> &, SolveOut *, bool);
+                                    int, BiWork<float> &, SolveOut *, bool, int *);
 
 }  // namespace oasis

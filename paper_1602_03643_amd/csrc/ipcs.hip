@@ -1158,6 +1158,8 @@ static int ir_bicgstab(hipStream_t s, int n, int nr, const int *rp, const int *c
             out[k].outer += 1;
             out[k].kernel_ms += in[q].kernel_ms;
             out[k].kernel_count += in[q].kernel_count;
+            out[k].coop += in[q].coop;
+            out[k].lost += in[q].lost;
             as.x[q] = x[k];
             as.e[q] = ir.e32[k];
         }
@@ -1863,6 +1865,8 @@ static int scalar_solve(hipStream_t s, oasis_ipcs *h, oasis_state *st, int a, in
     hipLaunchKernelGGL(k_scale3, dim3(gvec(n)), dim3(kBlock), 0, s, n, h->dA, 2, st->Cn[a],
                        static_cast<double *>(nullptr), static_cast<double *>(nullptr));
     OASIS_TRY_LAUNCH();
+    S.coop_runs += sc[0].coop;
+    S.coop_lost += sc[0].lost;
     S.iters_c[a] = sc[0].iters;
     S.res_c[a] = sc[0].rel_res;
     *status = sc[0].status;
@@ -1966,6 +1970,16 @@ extern "C" int oasis_ipcs_step(void *stream, oasis_ipcs *h, oasis_state *st, con
     auto note = [&](int status) {
         if (status != OASIS_OK && (worst == OASIS_OK || status < worst)) worst = status;
     };
+    // a launch for several right-hand sides counts once
+    auto count = [&](const SolveOut *o, int nr) {
+        int coop = 0, lost = 0;
+        for (int k = 0; k < nr; ++k) {
+            coop = std::max(coop, o[k].coop);
+            lost = std::max(lost, o[k].lost);
+        }
+        S.coop_runs += coop;
+        S.coop_lost += lost;
+    };
     const int zero_start = h->par.pressure_start == OASIS_PSTART_ZERO ? 1 : 0;
     S.guess_used = 0;
     SolveOut su[3], sp;
@@ -1997,6 +2011,7 @@ extern "C" int oasis_ipcs_step(void *stream, oasis_ipcs *h, oasis_state *st, con
             rc_u = bicgstab_solve<double>(s, n, D, h->rp, h->ci, h->A, h->wA, h->bt, x, ko.rtol, ko.maxit, 0, false,
                                           h->bi, sui);
         if (rc_u == OASIS_EHIP) return rc_u;
+        count(sui, D);
         for (int k = 0; k < D; ++k) {
             su[k].iters += sui[k].iters;
             su[k].outer = std::max(su[k].outer, sui[k].outer);
@@ -2064,6 +2079,7 @@ extern "C" int oasis_ipcs_step(void *stream, oasis_ipcs *h, oasis_state *st, con
             rc_p = cg_solve<double>(s, n, h->rp, h->ci, h->Ks, h->wK, h->bs, h->xs, ko.rtol, ko.maxit, 0, false,
                                     h->cg, spi);
         if (rc_p == OASIS_EHIP) return rc_p;
+        count(&spi, 1);
         sp.iters += spi.iters;
         sp.outer += spi.outer;
         sp.rel_res = spi.rel_res;
@@ -2101,6 +2117,7 @@ extern "C" int oasis_ipcs_step(void *stream, oasis_ipcs *h, oasis_state *st, con
                                             o.maxit, 0, false, h->cgM, sm);
             if (rc == OASIS_EHIP) return rc;
             S.iters_m[k] = sm.iters;
+            count(&sm, 1);
             note(sm.status);
             hipLaunchKernelGGL(k_vscale, dim3(gvec(n)), dim3(kBlock), 0, s, n, un[k], h->sM, 2, un[k]);
             OASIS_TRY_LAUNCH();
@@ -2221,6 +2238,8 @@ static void fill_stats(const SolveOut &o, int ell_storage, oasis_krylov_stats *s
     st->kernel_ms = o.kernel_ms;
     st->kernel_count = o.kernel_count;
     st->ell_patterns = ell_storage;
+    st->coop_runs = o.coop;
+    st->coop_lost = o.lost;
 }
 
 static int check_opts(const oasis_krylov_opts *o) {

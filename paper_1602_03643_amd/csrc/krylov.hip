@@ -1051,6 +1051,7 @@ static int cg_run(hipStream_t s, int n, const int *rp, const int *ci, const T *v
         }
         it += m;
         OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
+        if (coop && m > 0) (h.flag == 5 ? out.lost : out.coop) += 1;
         if (h.flag == 5) {
             // no iteration counts
             it -= m;
@@ -1250,6 +1251,7 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
         it += m;
         nin = g.p2;
         OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
+        if (coop && m > 0) (h.flag == 5 ? out.lost : out.coop) += 1;
         if (h.flag == 5) {
             // no iteration counts
             it -= m;
@@ -2275,11 +2277,12 @@ template <typename T>
 int bicgstab_solve(hipStream_t s, int n, int nrhs, const int *rp, const int *ci, const T *val,
                    const T *wgt, const T *const *b, T *const *x, double rtol, int maxit,
                    int check_every, bool time_kernel, BiWork<T> &w, SolveOut *out, bool inner) {
+    int lost = 0;
     if (!time_kernel) {
-        const int rc = bicg_coop_solve<T>(s, n, nrhs, wgt, b, x, rtol, maxit, w, out, inner);
+        const int rc = bicg_coop_solve<T>(s, n, nrhs, wgt, b, x, rtol, maxit, w, out, inner, &lost);
         if (rc != OASIS_EUNSUPPORTED) return rc;
     }
-    return with_cfg([&](auto c) {
+    const int rc = with_cfg([&](auto c) {
         using C = decltype(c);
         if (nrhs == 1)
             return bi_run<T, 1, C>(s, n, rp, ci, val, wgt, b, x, rtol, maxit, check_every, time_kernel, w, out,
@@ -2290,6 +2293,8 @@ int bicgstab_solve(hipStream_t s, int n, int nrhs, const int *rp, const int *ci,
         return bi_run<T, 3, C>(s, n, rp, ci, val, wgt, b, x, rtol, maxit, check_every, time_kernel, w, out,
                                inner);
     });
+    for (int k = 0; k < nrhs; ++k) out[k].lost = lost;
+    return rc;
 }
 
 template void carve_cg<double>(Carver &, int, CGWork<double> &);

@@ -120,6 +120,7 @@ struct SolveOut {
     double rel_res = 0.0;
     double kernel_ms = 0.0;
     int kernel_count = 0;
+    int coop = 0, lost = 0;   // cooperative runs that count and that do not
 };
 
 
@@ -176,10 +177,10 @@ constexpr int kCoopRun = 4096;
 // A whole BiCGStab solve in one cooperative launch (bicg_coop.hip), for one to
 // three right-hand sides; arguments and results of bicgstab_solve.
 // EUNSUPPORTED: not for this system, device or tuning, or out of time; the
-// other kernels go on from x.
+// other kernels go on from x.  *lost: launches that do not count.
 template <typename T>
 int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const *b, T *const *x, double rtol, int maxit,
-                    BiWork<T> &w, SolveOut *out, bool inner);
+                    BiWork<T> &w, SolveOut *out, bool inner, int *lost);
 
 // Longest row of a CSR pattern (synchronises; tmp: one device int).
 int csr_max_row(hipStream_t s, int n, const int *rp, int *tmp, int *out);

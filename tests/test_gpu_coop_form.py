@@ -1,0 +1,128 @@
+"""Which kernels a solve took (coop_runs, coop_lost), and BiCGStab solves in
+one cooperative launch through every part of that kernel.
+
+The meshes are those at the edges of the cooperative kernels' shapes; a
+randomly numbered one of 25,600 rows (a halo of about 3,500 entries where
+2,048 fit) stands for those that do not fit.  BiCGStab solves take the
+cooperative form up to an iteration cap of 4096, which the calls therefore
+lower from the default.  Both forms are the same recurrences with partial
+sums in another order, so the counts may differ by the few iterations that
+rounding moves a stopping test; every solution meets the tolerance in a
+residual computed on the host in FP64, with 0.1% for the rounding of the
+device's own.
+"""
+import numpy as np
+import pytest
+import scipy.sparse as sp
+import torch
+
+import synth
+from gpu_util import T, say
+from test_gpu_coop import MESHES, _system as _spd
+from test_gpu_coop_bicgstab import _system
+
+pytestmark = pytest.mark.gpu
+RTOL = 1e-9
+FORMS = {name: (make, name not in ("too large", "halo too wide"), 0) for name, make in MESHES.items()}
+FORMS["halo too wide"] = (lambda: synth.permute_mesh(synth.channel(33, 33, 25), 9)[0], False, 1)
+
+
+@pytest.fixture(scope="module")
+def oa():
+    import paper_1602_03643_amd as m
+    return m
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("name", list(FORMS))
+def test_cg_form_is_the_expected_one(oa, name, precision):
+    make, coop, lost = FORMS[name]
+    mesh = make()
+    say("cg form", name, mesh.name, precision)
+    A, H, b = _spd(oa, mesh, 3)
+    prec = oa.F64 if precision == "f64" else oa.F32
+    for kw, want in ((dict(), coop), (dict(cg_form=oa.CG_FORM_TWO), False), (dict(grid_cap=512), False)):
+        x = torch.zeros(mesh.n_dof, dtype=torch.float64, device="cuda")
+        st = oa.pcg(A, T(b), x, rtol=RTOL, precision=prec, **kw)
+        assert (st["coop_runs"] > 0) == want and st["coop_lost"] == (0 if kw else lost), (kw, st)
+        assert np.linalg.norm(b - H @ x.cpu().numpy()) <= 1.001 * RTOL * np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("nrhs", [1, 2, 3])
+@pytest.mark.parametrize("name", list(FORMS))
+def test_bicgstab_coop_against_launched(oa, name, nrhs, precision):
+    make, coop, lost = FORMS[name]
+    mesh = make()
+    n = mesh.n_dof
+    say("bicgstab form", name, mesh.name, nrhs, precision)
+    A, H, rng = _system(oa, mesh, 3)
+    prec = oa.F64 if precision == "f64" else oa.F32
+    b, x0 = rng.normal(size=(nrhs, n)), np.zeros((nrhs, n))
+    if nrhs > 1:      # a start one part in a million from the solution: stops early
+        sol = rng.normal(size=n)
+        b[1], x0[1] = H @ sol, sol * (1 + 1e-6 * rng.normal(size=n))
+    if nrhs > 2:
+        b[2] = 0.0
+    res = []
+    for cap in (0, 512):
+        x = T(x0)
+        st = oa.bicgstab(A, T(b), x, rtol=RTOL, precision=prec, maxit=4000, grid_cap=cap, raise_on=False)
+        res.append((x.cpu().numpy(), st))
+        want = coop and cap == 0
+        assert all((s["coop_runs"] > 0) == want for s in st if s["iters"] > 0), (cap, st)
+        assert st[0]["coop_lost"] == (lost if cap == 0 else 0), (cap, st)
+    (x, st), (y, gen) = res
+    for k in range(nrhs):
+        assert st[k]["rc"] == gen[k]["rc"] == 0 and st[k]["status"] == gen[k]["status"] == 0
+        assert np.linalg.norm(b[k] - H @ x[k]) <= 1.001 * RTOL * np.linalg.norm(b[k])
+        assert abs(st[k]["iters"] - gen[k]["iters"]) <= max(2, gen[k]["iters"] // 10)
+    if nrhs > 2:
+        assert not np.any(x[2])
+
+
+def test_bicgstab_coop_breakdown_and_nan(oa):
+    """Two-by-two blocks [[1, -5/4], [-5/4, 1]] and b = (1, 2, 1, 2, ...):
+    r_hat . A r is exactly zero at the start and again after the restart;
+    beside it a right-hand side that converges and one with a NaN.  Both
+    forms must say the same."""
+    n = 3000
+    say("bicgstab coop breakdown, nan")
+    H = sp.block_diag([np.array([[1.0, -1.25], [-1.25, 1.0]])] * (n // 2), format="csr")
+    H.sort_indices()
+    A = oa.DeviceCSR(T(H.indptr, torch.int32), T(H.indices, torch.int32), T(H.data))
+    rng = np.random.default_rng(4)
+    b = np.stack([np.tile([1.0, 2.0], n // 2), rng.normal(size=n), rng.normal(size=n)])
+    for nan in (False, True):
+        if nan:
+            b[2, 777] = np.nan
+        got = []
+        for cap in (0, 512):
+            x = torch.zeros((3, n), dtype=torch.float64, device="cuda")
+            st = oa.bicgstab(A, T(b), x, rtol=RTOL, maxit=50, grid_cap=cap, raise_on=False)
+            got.append([(s["status"], s["iters"], s["restarts"]) for s in st])
+            assert all(s["coop_runs"] == (1 if cap == 0 else 0) for s in st)
+            assert np.linalg.norm(b[1] - H @ x[1].cpu().numpy()) <= 1.001 * RTOL * np.linalg.norm(b[1])
+        assert got[0] == got[1], got
+        assert got[0][0][0] == oa.EBREAKDOWN and got[0][0][2] == 1 and got[0][1][0] == oa.OK
+        assert got[0][2][0] == (oa.ENAN if nan else oa.OK)
+
+
+def test_step_counts_its_runs(oa):
+    """A step with a scalar and an iteration cap that both solvers' cooperative
+    forms take: one run for the velocity, at least one for the pressure, one
+    for the scalar; none where the caller gives the grid."""
+    from gpu_util import device_mesh
+    mesh = synth.channel(9, 9, 7)
+    say("step form", mesh.name)
+    dm, pat, _ = device_mesh(mesh)
+    n = mesh.n_dof
+    for cap, runs in ((0, 3), (512, 0)):
+        h = oa.IPCS(dm, pat, 0.01, 0.01, (1.0, 0.0, 0.0), T(mesh.bc_dofs, torch.int32), maxit=4000, diffusivity=[0.02],
+                    grid_cap=cap)
+        z = lambda *s: torch.zeros(s, dtype=torch.float64, device="cuda")     # noqa: E731
+        c = T(np.random.default_rng(1).normal(size=(1, n)))
+        st = h.step(z(3, n), z(3, n), z(3, n), z(n), z(n), bc_values=z(3, mesh.bc_dofs.size), C1=c, Cn=z(1, n),
+                    C_bc=z(1, mesh.bc_dofs.size))
+        assert st["status"] == 0 and st["coop_lost"] == 0
+        assert st["coop_runs"] >= runs if runs else st["coop_runs"] == 0, st
