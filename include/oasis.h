@@ -234,6 +234,9 @@ typedef struct {
  * iterations then keep their residual orthogonal to the (scaled) null
  * vector, which FP32 rounding of the matrix would otherwise perturb. */
 #define OASIS_KRYLOV_NULLSPACE_CONST 2
+/* For tests: one block of a cooperative launch (see coop_lost) takes its
+ * k-th wait for the others, k = 1, 2, ... < 2^15, as one that ran out. */
+#define OASIS_KRYLOV_LOSE_WAIT(k) ((k) << 16)
 
 typedef struct {
     int32_t iters;        /* total (inner) iterations */

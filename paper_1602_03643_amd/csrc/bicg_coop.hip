@@ -30,7 +30,9 @@
 // its part of the sum that follows it.
 //
 // The cooperative launch guarantees that all blocks are resident, so every
-// wait ends; each is bounded by the clock all the same.
+// wait ends; each is bounded by the clock all the same.  A block that has lost
+// a wait sends nothing more, and the host puts the start iterate back: blocks
+// that got further may have moved their part of x.
 //
 // Per iteration with three right-hand sides in FP64: 199,680 rows 37 us
 // (product 9, halo 9, sums 14, scalars and updates 4, barriers; three kernels
@@ -73,12 +75,14 @@ struct BiCoopArgs {
     void *x[3];
     void *keep_s[3], *keep_t[3];   // s and t while an explicit residual is formed at the s stage
     void *v[3], *rhat[3];          // where these are in memory (LEAN)
-    BiBlock *blk;          // results, and glob.pause: kCoopUnfit
+    void *x0;              // the start iterate, [NR][n] (not inner)
+    BiBlock *blk;          // results, and glob.pause: kCoopLost or kCoopUnfit
     double rtol2;
     int maxit, inner;
     void *ex[3];           // sets of vector words, [NR][n] of T each
     u64 *slots;            // four sets of [value][copy][block]
     int copies;            // of a slot, read by the XCDs in turn
+    int lose;              // the wait (1, 2, ...) that the last block takes as lost
 };
 
 // BS: threads of a block, and the most rows it has.
@@ -95,7 +99,9 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
     __shared__ double scal[WAVES][6 * NR];
     __shared__ BiState result[NR];
     __shared__ int scan[WAVES];
-    __shared__ int quit;
+    // a wait of a sum, of a product, was lost: two, so that a wave still at the
+    // test of one cannot see what a wave ahead of it sets in the next
+    __shared__ int quit[2];
     const int t = threadIdx.x, wv = t / kWave, wl = t & (kWave - 1);
     const int nb = gridDim.x, bid = blockIdx.x;
     const int r0 = bid * a.rows, r1 = min(a.n, r0 + a.rows);
@@ -103,7 +109,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
     const bool own = row < r1;                    // this thread has a row
     const int at = own ? row : min(r0, a.n - 1);  // a valid row for the loads
     int *flag = &a.blk->glob.pause;
-    if (t == 0) quit = 0;
+    if (t < 2) quit[t] = 0;
 
     T val[E];
     unsigned idx[E / 2];
@@ -119,15 +125,23 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
     using W = Word<T>;
     using D = Word<double>;
 
+    // the end of an exchange, after the last poll of every wave: false when one
+    // of them ran out
+    int waits = 0;
+    auto ended = [&](int kind) -> bool {
+        if (++waits == a.lose && bid == nb - 1 && t == 0) quit[kind] = 1;
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane(quit[kind]) == 0;
+    };
     // ask again, with the clock as a bound, while again() says so
-    auto poll = [&](auto &&again) {
+    auto poll = [&](int kind, auto &&again) {
         if (!again()) return;
         const long long began = wall_clock64();
         int k = 0;
         while (again()) {
-            if ((++k & 63) == 0 && (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopUnfit ||
+            if ((++k & 63) == 0 && (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopLost ||
                                     wall_clock64() - began > kCoopTicks)) {
-                quit = 1;
+                quit[kind] = 1;
                 return;
             }
         }
@@ -156,7 +170,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
             constexpr int SL = kCoopBlocks / kWave;
             u64 u[SL];
             const u64 *f = from + j * a.copies * nb;
-            poll([&] {
+            poll(0, [&] {
                 bool miss = false;
 #pragma unroll
                 for (int k = 0; k < SL; ++k)
@@ -173,14 +187,13 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
             s = wave_sum(s);
             if (wl == 0) all[j] = s;
         }
-        __syncthreads();
-        if (__builtin_amdgcn_readfirstlane(quit)) return false;
         sum_set = (sum_set + 1) & 3;
-        return true;
+        return ended(0);
     };
-    // q = As m: the vectors m go to the words and into LDS with their halo
+    // q = As m: the vectors m go to the words and into LDS with their halo;
+    // false when a wait ran out (q is not to be used then)
     int vec_set = 0;
-    auto product = [&](const T(&m)[NR], T(&q)[NR]) {
+    auto product = [&](const T(&m)[NR], T(&q)[NR]) -> bool {
         using U = typename W::U;
         void *ex = a.ex[vec_set], *spare = a.ex[vec_set == 0 ? 2 : vec_set - 1];
         const unsigned mine = static_cast<unsigned>(row) * sizeof(T), plane = static_cast<unsigned>(a.n) * sizeof(T);
@@ -197,7 +210,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
 #pragma unroll
         for (int h0 = 0; h0 < PER; h0 += CHUNK) {
             U hw[CHUNK][NR];
-            poll([&] {
+            poll(1, [&] {
                 bool miss = false;
 #pragma unroll
                 for (int h = 0; h < CHUNK; ++h)
@@ -222,7 +235,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
                 }
         }
         vec_set = vec_set == 2 ? 0 : vec_set + 1;
-        __syncthreads();
+        if (!ended(1)) return false;
 #pragma unroll
         for (int k = 0; k < NR; ++k) q[k] = T(0);
 #pragma unroll
@@ -236,6 +249,10 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
                 q[k] += val[e + 1] * vec[k * LEN + i1];
             }
         }
+        return true;
+    };
+    auto lost = [&] {
+        if (t == 0) atomicMax(flag, kCoopLost);
     };
     const double wd = static_cast<double>(item<const T>(a.wgt, static_cast<unsigned>(at) * sizeof(T)));
     const unsigned off = static_cast<unsigned>(at) * sizeof(T);
@@ -334,7 +351,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
                 else
                     m[k] = xk(k);
             }
-            product(m, q);
+            if (!product(m, q)) return lost();
         }
         // (one call of total: its code in one place stays in the instruction cache)
         double c[NV];
@@ -381,10 +398,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
                 c[NR + k] = wd * rd * rd;
             }
         }
-        if (!total(c, nv)) {
-            if (t == 0) atomicMax(flag, kCoopUnfit);
-            return;
-        }
+        if (!total(c, nv)) return lost();
         const double s0 = all[lk], tol2 = get(kTol2 + lk);
         if (step == kCap) {
             const int met = those(s0 <= tol2);
@@ -532,14 +546,26 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
 }
 
 // the words and slots that are sent before they have been emptied: those of
-// the first two vectors and sums; and the flag
+// the first two vectors and sums; the start iterate and the flag
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_bi_coop_clear(int words, int slots, BiCoopArgs a) {
     const int step = gridDim.x * blockDim.x, i0 = blockIdx.x * blockDim.x + threadIdx.x;
     for (int k = 0; k < 2; ++k)
         for (int i = i0; i < words; i += step) static_cast<typename Word<T>::U *>(a.ex[k])[i] = Word<T>::kEmpty;
     for (int i = i0; i < slots; i += step) a.slots[i] = Word<double>::kEmpty;
+    if (a.x0)
+        for (int k = 0; k < words / a.n; ++k)
+            for (int i = i0; i < a.n; i += step)
+                static_cast<T *>(a.x0)[k * a.n + i] = static_cast<const T *>(a.x[k])[i];
     if (i0 == 0) a.blk->glob.pause = 0;
+}
+
+// x as it was at the start
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_bi_coop_back(int nrhs, BiCoopArgs a) {
+    for (int k = 0; k < nrhs; ++k)
+        for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < a.n; i += gridDim.x * blockDim.x)
+            static_cast<T *>(a.x[k])[i] = static_cast<const T *>(a.x0)[k * a.n + i];
 }
 
 template <typename T, int NR>
@@ -600,12 +626,14 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
     a.rtol2 = rtol * rtol;
     a.maxit = maxit;
     a.inner = inner ? 1 : 0;
-    // the words live in the (r, v) and (r, u) pairs and the slots in the
-    // partial arrays, which this form does not use
+    a.lose = w.lose;
+    // the words live in the (r, v) and (r, u) pairs, the start iterate too, and
+    // the slots in the partial arrays, which this form does not use
     const int words = n * nrhs;
     a.ex[0] = w.rv;
     a.ex[1] = reinterpret_cast<T *>(w.rv) + words;
     a.ex[2] = w.ru;
+    a.x0 = inner ? nullptr : reinterpret_cast<T *>(w.ru) + words;
     a.slots = reinterpret_cast<u64 *>(w.part1);
     // (a set: 3 nrhs values, copies, blocks; part1, part2 and part3 hold
     // three sets of 9 values of kMaxPartials = 8 copies of 256 blocks)
@@ -618,8 +646,12 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
     OASIS_TRY(nrhs == 1 ? (launch<T, 1>(s, grid, a)) : nrhs == 2 ? (launch<T, 2>(s, grid, a)) : (launch<T, 3>(s, grid, a)));
     BiBlock h{};
     OASIS_TRY(read_state(s, w.stage, a.blk, &h, sizeof(h)));
-    if (h.glob.pause == kCoopUnfit) {
+    if (h.glob.pause != 0) {
         w.coop_off = true;
+        if (h.glob.pause == kCoopLost && a.x0) {
+            hipLaunchKernelGGL(k_bi_coop_back<T>, dim3(grid_for(n, kBlock, 1024)), dim3(kBlock), 0, s, nrhs, a);
+            OASIS_TRY_LAUNCH();
+        }
         *lost += 1;
         return OASIS_EUNSUPPORTED;
     }

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
         int k = 0;
         while (again()) {
             if ((++k & 63) == 0 &&
-                (__hip_atomic_load(&st->flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopUnfit ||
+                (__hip_atomic_load(&st->flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopLost ||
                  wall_clock64() - began > kCoopTicks)) {
                 quit = 1;
                 return;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
         buf = buf == 2 ? 0 : buf + 1;
     }
     if (quit) {
-        if (t == 0) atomicMax(&st->flag, kCoopUnfit);
+        if (t == 0) atomicMax(&st->flag, kCoopLost);
         return;
     }
     if (own) {

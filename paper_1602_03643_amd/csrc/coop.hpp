@@ -14,10 +14,6 @@ constexpr int kCoopBlocks = 256;               // most blocks: four slots per la
 constexpr int kCoopMaxRows = kCoopBlocks * kCoopThreads;
 constexpr int kBitWords = kCoopMaxRows / 32;
 constexpr long long kCoopTicks = 200000000ll;  // 2 s of the 100 MHz wall clock
-// The flag of a run that does not count: too wide a halo, or a wait that ran
-// out (something else holds the CUs that the rest of the grid needs).  The
-// host goes on with the other kernels, from the iterate in memory.
-constexpr int kCoopUnfit = 5;
 
 // The exchanged words: a T's bits, or the empty mark, a NaN that no sent
 // value has (every NaN is sent as the quiet one).

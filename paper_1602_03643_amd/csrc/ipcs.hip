@@ -2387,6 +2387,7 @@ extern "C" int oasis_bicgstab(void *stream, const oasis_csr *A, int32_t nrhs, co
     (void)Tuning::from(&opt->tuning, &tun);
     k.cg.tun = k.cg32.tun = tun;
     k.bi.tun = k.bi32.tun = tun;
+    k.bi.lose = k.bi32.lose = opt->flags >> 16;
     hipStream_t s = as_stream(stream);
     const double *val = static_cast<const double *>(A->val);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(kBlock), 0, s, 16, k.flag, 0);

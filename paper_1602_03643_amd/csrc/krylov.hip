@@ -1051,8 +1051,8 @@ static int cg_run(hipStream_t s, int n, const int *rp, const int *ci, const T *v
         }
         it += m;
         OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
-        if (coop && m > 0) (h.flag == 5 ? out.lost : out.coop) += 1;
-        if (h.flag == 5) {
+        if (coop && m > 0) (h.flag >= kCoopLost ? out.lost : out.coop) += 1;
+        if (h.flag >= kCoopLost) {
             // no iteration counts
             it -= m;
             OASIS_TRY(leave_coop(it));
@@ -1251,8 +1251,8 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
         it += m;
         nin = g.p2;
         OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
-        if (coop && m > 0) (h.flag == 5 ? out.lost : out.coop) += 1;
-        if (h.flag == 5) {
+        if (coop && m > 0) (h.flag >= kCoopLost ? out.lost : out.coop) += 1;
+        if (h.flag >= kCoopLost) {
             // no iteration counts
             it -= m;
             OASIS_TRY(leave_coop(it));

@@ -16,7 +16,7 @@ struct CGState {
     double upd2;       // mixed precision: replace the residual once wrr <= upd2
     int flag;          // 0 running, 1 converged candidate, 2 breakdown, 3 non-finite,
                        // 4 residual replacement due (mixed precision),
-                       // 5 a cooperative run that does not fit or ran out of time (cg_coop.hip)
+                       // kCoopLost or kCoopUnfit: a cooperative run that does not count
     int it_done;       // iteration index at which flag was raised
     double wrr_it;     // weighted r.r entering iteration it_last (the last one that ran)
     int it_last;
@@ -110,6 +110,7 @@ struct BiWork {
     HostStage stage;   // the owner's read-back block (may be null)
     Tuning tun;
     bool coop_off = false;   // the pattern's halo is too wide for a cooperative solve
+    int lose = 0;            // the wait of a cooperative solve that is taken as lost (tests)
 };
 
 struct SolveOut {
@@ -171,6 +172,11 @@ template <typename T>
 bool cg_coop_fits(int n, const CGWork<T> &w);
 template <typename T>
 int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T *vnull, int it0, int m, bool beta_zero);
+// The flags of a run that does not count: a wait that ran out (something else
+// holds the CUs that the rest of the grid needs), or too wide a halo, which
+// outweighs the waits that it leaves unmet.  The solve goes on with the other
+// kernels.
+constexpr int kCoopLost = 5, kCoopUnfit = 6;
 // Iterations of one cooperative run at most (it stops by itself).
 constexpr int kCoopRun = 4096;
 

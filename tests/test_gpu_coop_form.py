@@ -126,3 +126,39 @@ def test_step_counts_its_runs(oa):
                     C_bc=z(1, mesh.bc_dofs.size))
         assert st["status"] == 0 and st["coop_lost"] == 0
         assert st["coop_runs"] >= runs if runs else st["coop_runs"] == 0, st
+
+
+def _bicgstab(oa, A, b, x0, prec, flags=0, **kw):
+    """oa.bicgstab with flags of its own."""
+    import ctypes as C
+    from paper_1602_03643_amd import _lib as L
+    x = x0.clone()
+    o = L.KrylovOpts(RTOL, kw.get("maxit", 4000), prec, 1e-4, 50, 0, flags, L.Tuning(0, kw.get("grid_cap", 0), 0))
+    nb = C.c_size_t()
+    assert L.load().oasis_krylov_workspace_size(A.n, A.nnz, b.shape[0], C.byref(o), C.byref(nb)) == 0
+    ws = torch.empty(nb.value, dtype=torch.uint8, device="cuda")
+    st = (L.KrylovStats * b.shape[0])()
+    ptr = lambda t: C.c_void_p(t.data_ptr())                            # noqa: E731
+    rc = L.load().oasis_bicgstab(None, C.byref(A.c()), b.shape[0], ptr(b), ptr(x), C.byref(o), ptr(ws), ws.numel(), st)
+    return rc, x, st
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("mesh", [lambda: synth.channel(17, 17, 13), lambda: synth.channel(49, 45, 41),
+                                  lambda: synth.channel(65, 64, 65)])
+def test_bicgstab_after_a_lost_wait(oa, mesh, precision):
+    """A wait lost in the first sum, in products, in sums and late in the solve:
+    the launched form must start from the caller's iterate, so the results are
+    its own, bit for bit, whatever the lost launch had done to x."""
+    mesh = mesh()
+    say("bicgstab lost wait", mesh.name, precision)
+    prec = oa.F64 if precision == "f64" else oa.F32
+    A, H, rng = _system(oa, mesh, 6)
+    b, x0 = T(rng.normal(size=(2, mesh.n_dof))), T(rng.normal(size=(2, mesh.n_dof)))
+    torch.cuda.synchronize()
+    rc, ref, st = _bicgstab(oa, A, b, x0, prec, grid_cap=512)
+    assert rc == 0 and st[0].coop_runs == 0
+    for k in (1, 2, 3, 4, 5, 6, 7, 16, 17, 18):
+        rc, x, got = _bicgstab(oa, A, b, x0, prec, flags=k << 16)
+        assert rc == 0 and [g.coop_lost for g in got] == [1, 1], k
+        assert torch.equal(x, ref) and [g.iters for g in got] == [s.iters for s in st], k
