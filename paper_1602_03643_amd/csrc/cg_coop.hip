@@ -60,6 +60,7 @@ struct CoopArgs {
     int it0, m, beta_zero;
     void *ex[3];           // exchanged residual entries, n words of T each
     u64 *slots[2];         // exchanged partials, first and second value
+    int lose;              // the wait (1, 2, ...) that the last block takes as lost
 };
 
 // Partial slots of a value: [exchange kind][buffer][copy][block].  A block sends each value
@@ -69,11 +70,12 @@ constexpr int kCopies = kXcds;
 constexpr int kSlotWords = 2 * 3 * kCopies * kCoopBlocks;
 __device__ __forceinline__ int slot_set(int kind, int buf) { return (kind * 3 + buf) * kCopies * kCoopBlocks; }
 
-// the state as k_cg_p1 and k_cg_p2 leave it
+// the state as k_cg_p1 and k_cg_p2 leave it; the flag of a block that lost its
+// last wait outweighs the others'
 __device__ __forceinline__ void leave(CGState *st, int flag, int it, double rr, double wrr, double rr_prev) {
     const int last = flag ? it : it - 1;   // the last iteration whose residual was seen
     if (flag) {
-        st->flag = flag;
+        atomicMax(&st->flag, flag);
         st->it_done = it;
         if (flag != 2) st->wrr = wrr;
     }
@@ -140,6 +142,14 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
     using D = Word<double>;
     const int nv1 = vn ? 2 : 1;                // values of the second exchange
 
+    // the end of an exchange, after the last poll of every wave: false when one
+    // of them ran out
+    int waits = 0;
+    auto ended = [&]() -> bool {
+        if (++waits == a.lose && bid == nb - 1 && t == 0) quit = 1;
+        __syncthreads();
+        return quit == 0;
+    };
     // ask again, with the clock as a bound, while again() says so
     auto poll = [&](auto &&again) {
         if (!again()) return;
@@ -237,8 +247,7 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
             return miss;
         });
         take(2, 0);
-        __syncthreads();
-        if (quit) break;
+        if (!ended()) break;
         rr = all[0][0];
         wrr = all[0][1];
         if (!finite(wrr) || !finite(rr))
@@ -271,8 +280,7 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
         give(own ? static_cast<double>(p) * static_cast<double>(q) : 0.0,
              own ? static_cast<double>(v) * static_cast<double>(q) : 0.0, nv1, 1);
         take(nv1, 1);
-        __syncthreads();
-        if (quit) break;
+        if (!ended()) break;
         const double pq = all[1][0], vq = all[1][1];
         if (!(pq > 0.0) || !finite(pq)) {
             flag = finite(pq) ? 2 : 3;
@@ -494,6 +502,7 @@ int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T 
     a.beta_zero = beta_zero ? 1 : 0;
     a.slots[0] = reinterpret_cast<u64 *>(w.partA);
     a.slots[1] = reinterpret_cast<u64 *>(w.partB);
+    a.lose = w.lose;
     if (n <= kOneThreads * kOneRows) {
         if (n <= kOneThreads)
             hipLaunchKernelGGL((k_cg_one<T, 1>), dim3(1), dim3(kOneThreads), 0, s, a);

@@ -2268,6 +2268,7 @@ static int pcg_run(void *stream, const oasis_csr *A, const double *b, double *x,
     if (!dict && tun.storage == OASIS_STORAGE_AUTO) tun.storage = OASIS_STORAGE_ELL;
     k.cg.tun = k.cg32.tun = tun;
     k.bi.tun = k.bi32.tun = tun;
+    k.cg.lose = k.cg32.lose = opt->flags >> 16;
     hipStream_t s = as_stream(stream);
     const double *val = static_cast<const double *>(A->val);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(kBlock), 0, s, 16, k.flag, 0);

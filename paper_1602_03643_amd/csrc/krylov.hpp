@@ -57,6 +57,7 @@ struct CGWork {
     Tuning tun;
     HostStage stage;   // the owner's read-back block (may be null)
     bool coop_off = false;   // the pattern's halo is too wide for cooperative runs
+    int lose = 0;            // the wait of a cooperative run that is taken as lost (tests)
 };
 
 struct BiState {

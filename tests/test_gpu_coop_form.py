@@ -162,3 +162,42 @@ def test_bicgstab_after_a_lost_wait(oa, mesh, precision):
         rc, x, got = _bicgstab(oa, A, b, x0, prec, flags=k << 16)
         assert rc == 0 and [g.coop_lost for g in got] == [1, 1], k
         assert torch.equal(x, ref) and [g.iters for g in got] == [s.iters for s in st], k
+
+
+def _pcg(oa, A, b, prec, flags=0):
+    """oa.pcg from zero with flags of its own."""
+    import ctypes as C
+    from paper_1602_03643_amd import _lib as L
+    x = torch.zeros_like(b)
+    o = L.KrylovOpts(RTOL, 4000, prec, 0.1, 50, 0, flags, L.Tuning(0, 0, 0))
+    nb = C.c_size_t()
+    assert L.load().oasis_krylov_workspace_size(A.n, A.nnz, 1, C.byref(o), C.byref(nb)) == 0
+    ws = torch.empty(nb.value, dtype=torch.uint8, device="cuda")
+    st = L.KrylovStats()
+    ptr = lambda t: C.c_void_p(t.data_ptr())                            # noqa: E731
+    rc = L.load().oasis_pcg(None, C.byref(A.c()), ptr(b), ptr(x), C.byref(o), ptr(ws), ws.numel(), C.byref(st))
+    return rc, x, st
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("mesh", [lambda: synth.channel(17, 17, 13), lambda: synth.channel(49, 45, 41),
+                                  lambda: synth.channel(65, 64, 65)])
+def test_cg_after_a_lost_wait(oa, mesh, precision):
+    """Waits lost in the first exchanges, later, and in the one in which the
+    others see convergence: the launch must not count, and the solve still
+    meets its tolerance."""
+    mesh = mesh()
+    say("cg lost wait", mesh.name, precision)
+    prec = oa.F64 if precision == "f64" else oa.F32
+    A, H, b = _spd(oa, mesh, 6)
+    B = T(b)
+    torch.cuda.synchronize()
+    rc, x, ref = _pcg(oa, A, B, prec)
+    assert rc == 0 and ref.coop_runs > 0 and ref.coop_lost == 0
+    # a mixed solve's first launch ends when the residual has fallen tenfold
+    last = [2 * ref.iters + 1] * 4 if precision == "f64" else []
+    for k in [1, 2, 3, 4, 9, 10] + last:
+        rc, x, st = _pcg(oa, A, B, prec, flags=k << 16)
+        assert rc == 0 and st.coop_lost == 1 and st.coop_runs == 0, (k, st.coop_lost, st.coop_runs)
+        assert np.linalg.norm(b - H @ x.cpu().numpy()) <= 1.001 * RTOL * np.linalg.norm(b), k
+        assert abs(st.iters - ref.iters) <= max(3, ref.iters // 10) + k // 2
