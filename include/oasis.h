@@ -235,7 +235,8 @@ typedef struct {
  * vector, which FP32 rounding of the matrix would otherwise perturb. */
 #define OASIS_KRYLOV_NULLSPACE_CONST 2
 /* For tests: one block of a cooperative launch (see coop_lost) takes its
- * k-th wait for the others, k = 1, 2, ... < 2^15, as one that ran out. */
+ * k-th wait for the others, k = 1, 2, ... < 2^14, as one that ran out; with
+ * 2^14 added to k in the repeats of the launch too. */
 #define OASIS_KRYLOV_LOSE_WAIT(k) ((k) << 16)
 
 typedef struct {
@@ -252,8 +253,10 @@ typedef struct {
     int32_t coop_runs;    /* launches that did many iterations each (CG) or a whole solve
                              (BiCGStab) on systems of up to 1024 rows per CU; 0: every
                              iteration was launched */
-    int32_t coop_lost;    /* such launches that do not count: the solve went on with the
-                             launched iterations */
+    int32_t coop_lost;    /* such launches that do not count: what they need was held by other
+                             work for too long, or the matrix does not suit them; they were
+                             repeated, or the solve went on with launched iterations (its
+                             sums then have another order) */
 } oasis_krylov_stats;
 
 /* Workspace for oasis_pcg / oasis_bicgstab with nrhs right-hand sides. */

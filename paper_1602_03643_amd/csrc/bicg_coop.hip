@@ -29,10 +29,9 @@
 // emptying has reached memory before this block sends vector e + 2 and hence
 // its part of the sum that follows it.
 //
-// The cooperative launch guarantees that all blocks are resident, so every
-// wait ends; each is bounded by the clock all the same.  A block that has lost
-// a wait sends nothing more, and the host puts the start iterate back: blocks
-// that got further may have moved their part of x.
+// Every wait is bounded by the clock (coop.hpp).  A block that has lost one
+// sends nothing more, and the host puts the start iterate back before the solve
+// is begun again: blocks that got further may have moved their part of x.
 //
 // Per iteration with three right-hand sides in FP64: 199,680 rows 37 us
 // (product 9, halo 9, sums 14, scalars and updates 4, barriers; three kernels
@@ -76,12 +75,13 @@ struct BiCoopArgs {
     void *keep_s[3], *keep_t[3];   // s and t while an explicit residual is formed at the s stage
     void *v[3], *rhat[3];          // where these are in memory (LEAN)
     void *x0;              // the start iterate, [NR][n] (not inner)
-    BiBlock *blk;          // results, and glob.pause: kCoopLost or kCoopUnfit
+    BiBlock *blk;          // results, and glob.pause: kCoopLate to kCoopUnfit
     double rtol2;
     int maxit, inner;
     void *ex[3];           // sets of vector words, [NR][n] of T each
     u64 *slots;            // four sets of [value][copy][block]
     int copies;            // of a slot, read by the XCDs in turn
+    unsigned join;         // ticks of the first wait
     int lose;              // the wait (1, 2, ...) that the last block takes as lost
 };
 
@@ -136,11 +136,11 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
     // ask again, with the clock as a bound, while again() says so
     auto poll = [&](int kind, auto &&again) {
         if (!again()) return;
-        const long long began = wall_clock64();
+        const unsigned began = static_cast<unsigned>(wall_clock64()), most = waits == 0 ? a.join : kCoopTicks;
         int k = 0;
         while (again()) {
-            if ((++k & 63) == 0 && (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopLost ||
-                                    wall_clock64() - began > kCoopTicks)) {
+            if ((++k & 63) == 0 && (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopLate ||
+                                    static_cast<unsigned>(wall_clock64()) - began > most)) {
                 quit[kind] = 1;
                 return;
             }
@@ -251,9 +251,6 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
         }
         return true;
     };
-    auto lost = [&] {
-        if (t == 0) atomicMax(flag, kCoopLost);
-    };
     const double wd = static_cast<double>(item<const T>(a.wgt, static_cast<unsigned>(at) * sizeof(T)));
     const unsigned off = static_cast<unsigned>(at) * sizeof(T);
     auto rhs = [&](int k) { return item<const T>(a.b[k], off); };
@@ -351,7 +348,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
                 else
                     m[k] = xk(k);
             }
-            if (!product(m, q)) return lost();
+            if (!product(m, q)) break;
         }
         // (one call of total: its code in one place stays in the instruction cache)
         double c[NV];
@@ -398,7 +395,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
                 c[NR + k] = wd * rd * rd;
             }
         }
-        if (!total(c, nv)) return lost();
+        if (!total(c, nv)) break;
         const double s0 = all[lk], tol2 = get(kTol2 + lk);
         if (step == kCap) {
             const int met = those(s0 <= tol2);
@@ -540,6 +537,10 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
         put(kBeta, (s0 / get(kRho + lk)) * (get(kAlpha + lk) / get(kOmega + lk)));
         step = kP;
     }
+    if (quit[0] | quit[1]) {
+        if (t == 0) atomicMax(flag, kCoopLost);
+        return;
+    }
     if (bid == 0 && t == 0) {
         for (int k = 0; k < NR; ++k) a.blk->st[k] = result[k];
     }
@@ -583,7 +584,7 @@ int launch(hipStream_t s, int grid, BiCoopArgs &a) {
         kern = reinterpret_cast<const void *>(&k_bi_coop<T, NR, 1024>);
         bs = 1024;
     }
-    if (hipLaunchCooperativeKernel(kern, dim3(grid), dim3(bs), args, 0, s) != hipSuccess) {
+    if (hipLaunchKernel(kern, dim3(grid), dim3(bs), args, 0, s) != hipSuccess) {
         (void)hipGetLastError();
         return OASIS_EUNSUPPORTED;
     }
@@ -601,12 +602,9 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
     if (w.coop_off || !w.cols.any() || !w.eval || !w.tun.ell() || !w.tun.grid_auto || n > kCoopMaxRows ||
         maxit > kCoopRun)
         return OASIS_EUNSUPPORTED;
-    int dev = 0, cu = 0, coop = 0;
-    OASIS_TRY_HIP(hipGetDevice(&dev));
-    OASIS_TRY_HIP(hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev));
-    OASIS_TRY_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
-    const int most = std::min(cu, kCoopBlocks);
-    if (!coop || n > static_cast<long long>(most) * kCoopThreads) return OASIS_EUNSUPPORTED;
+    int most = 0;
+    OASIS_TRY(coop_blocks(s, &most));
+    if (n > most * kCoopThreads) return OASIS_EUNSUPPORTED;
     const int grid = std::min(most, (n + kBlock - 1) / kBlock);
     BiCoopArgs a{};
     a.n = n;
@@ -626,7 +624,6 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
     a.rtol2 = rtol * rtol;
     a.maxit = maxit;
     a.inner = inner ? 1 : 0;
-    a.lose = w.lose;
     // the words live in the (r, v) and (r, u) pairs, the start iterate too, and
     // the slots in the partial arrays, which this form does not use
     const int words = n * nrhs;
@@ -640,20 +637,25 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
     constexpr int kWords = 3 * 9 * kMaxPartials;
     if (w.part3 != w.part1 + 2 * 9 * kMaxPartials) return OASIS_EUNSUPPORTED;
     a.copies = std::min(kXcds, kWords / (4 * 3 * nrhs * grid));
-    hipLaunchKernelGGL(k_bi_coop_clear<T>, dim3(grid_for(words, kBlock, 1024)), dim3(kBlock), 0, s, words,
-                       2 * 3 * nrhs * a.copies * grid, a);
-    OASIS_TRY_LAUNCH();
-    OASIS_TRY(nrhs == 1 ? (launch<T, 1>(s, grid, a)) : nrhs == 2 ? (launch<T, 2>(s, grid, a)) : (launch<T, 3>(s, grid, a)));
     BiBlock h{};
-    OASIS_TRY(read_state(s, w.stage, a.blk, &h, sizeof(h)));
-    if (h.glob.pause != 0) {
-        w.coop_off = true;
-        if (h.glob.pause == kCoopLost && a.x0) {
+    for (int attempt = 0;; ++attempt) {
+        a.join = join_ticks();
+        a.lose = lose_wait(w.lose, attempt);
+        hipLaunchKernelGGL(k_bi_coop_clear<T>, dim3(grid_for(words, kBlock, 1024)), dim3(kBlock), 0, s, words,
+                           2 * 3 * nrhs * a.copies * grid, a);
+        OASIS_TRY_LAUNCH();
+        OASIS_TRY(nrhs == 1 ? (launch<T, 1>(s, grid, a)) : nrhs == 2 ? (launch<T, 2>(s, grid, a)) : (launch<T, 3>(s, grid, a)));
+        OASIS_TRY(read_state(s, w.stage, a.blk, &h, sizeof(h)));
+        if (h.glob.pause == 0) break;
+        *lost += 1;
+        if (h.glob.pause != kCoopUnfit && a.x0) {
             hipLaunchKernelGGL(k_bi_coop_back<T>, dim3(grid_for(n, kBlock, 1024)), dim3(kBlock), 0, s, nrhs, a);
             OASIS_TRY_LAUNCH();
         }
-        *lost += 1;
-        return OASIS_EUNSUPPORTED;
+        if (h.glob.pause == kCoopUnfit || attempt + 1 == kCoopTries) {
+            w.coop_off = true;
+            return OASIS_EUNSUPPORTED;
+        }
     }
     int worst = OASIS_OK;
     for (int k = 0; k < nrhs; ++k) {
@@ -663,6 +665,7 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
         out[k].iters = o.it_rec;
         out[k].replacements = o.active;
         out[k].coop = 1;
+        out[k].lost = *lost;
         if (!(o.wrr_rec < 0.0)) out[k].rel_res = o.wbb > 0.0 ? std::sqrt(o.wrr_rec / o.wbb) : std::sqrt(o.wrr_rec);
         if (o.event != OASIS_OK && (worst == OASIS_OK || o.event < worst)) worst = o.event;
     }

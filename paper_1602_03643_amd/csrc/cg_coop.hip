@@ -32,8 +32,7 @@
 // iteration e + 2, having seen all of e + 1, finds the slots empty or
 // filled, never old.
 //
-// The cooperative launch guarantees that all blocks are resident, so every
-// wait ends; each is bounded by the clock all the same.
+// Every wait is bounded by the clock (coop.hpp).
 //
 // Per iteration, before and now: 65x65x49 FP64 20.0 -> 5.7 us (256 blocks,
 // 780 rows each: about 1.7 us for each exchange, 0.4 us for the product, the
@@ -60,6 +59,7 @@ struct CoopArgs {
     int it0, m, beta_zero;
     void *ex[3];           // exchanged residual entries, n words of T each
     u64 *slots[2];         // exchanged partials, first and second value
+    unsigned join;         // ticks of the first wait
     int lose;              // the wait (1, 2, ...) that the last block takes as lost
 };
 
@@ -146,19 +146,27 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
     // of them ran out
     int waits = 0;
     auto ended = [&]() -> bool {
-        if (++waits == a.lose && bid == nb - 1 && t == 0) quit = 1;
+        if (++waits == a.lose && bid == nb - 1 && t == 0) {
+            atomicMax(&st->flag, waits == 1 ? kCoopLate : kCoopLost);
+            quit = 1;
+        }
         __syncthreads();
         return quit == 0;
     };
-    // ask again, with the clock as a bound, while again() says so
+    // ask again, with the clock as a bound, while again() says so; the flag is
+    // raised by whoever loses a wait first, not by those that it leaves behind
     auto poll = [&](auto &&again) {
         if (!again()) return;
-        const long long began = wall_clock64();
+        const unsigned began = static_cast<unsigned>(wall_clock64()), most = waits == 0 ? a.join : kCoopTicks;
         int k = 0;
         while (again()) {
-            if ((++k & 63) == 0 &&
-                (__hip_atomic_load(&st->flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopLost ||
-                 wall_clock64() - began > kCoopTicks)) {
+            if ((++k & 63) != 0) continue;
+            if (__hip_atomic_load(&st->flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopLate) {
+                quit = 1;
+                return;
+            }
+            if (static_cast<unsigned>(wall_clock64()) - began > most) {
+                atomicMax(&st->flag, waits == 0 ? kCoopLate : kCoopLost);
                 quit = 1;
                 return;
             }
@@ -292,10 +300,7 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
         spare = buf;
         buf = buf == 2 ? 0 : buf + 1;
     }
-    if (quit) {
-        if (t == 0) atomicMax(&st->flag, kCoopLost);
-        return;
-    }
+    if (quit) return;
     if (own) {
         xg[row] = x;
         static_cast<RP<T> *>(a.nxt[it & 1])[row] = RP<T>{r, p};
@@ -443,7 +448,7 @@ __global__ __launch_bounds__(kOneThreads) void k_cg_one(CoopArgs a) {
     if (t == 0) leave(st, flag, it, rr, wrr, rr_prev);
 }
 
-// every exchange slot empty
+// every exchange slot empty, and no flag
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_words_clear(int n, CoopArgs a) {
     using W = Word<T>;
@@ -451,34 +456,30 @@ __global__ __launch_bounds__(kBlock) void k_words_clear(int n, CoopArgs a) {
     for (int k = 0; k < 3; ++k)
         for (int i = i0; i < n; i += step) static_cast<typename W::U *>(a.ex[k])[i] = W::kEmpty;
     for (int i = i0; i < kSlotWords; i += step) a.slots[0][i] = a.slots[1][i] = Word<double>::kEmpty;
+    if (i0 == 0) a.st->flag = 0;
 }
 
 }  // namespace
 
 template <typename T>
-bool cg_coop_fits(int n, const CGWork<T> &w) {
+bool cg_coop_fits(hipStream_t s, int n, const CGWork<T> &w) {
     // one row per thread of one block per CU; the kernel and grid the caller
     // asked for by name are left as they are
     if (w.coop_off || !w.cols.any() || !w.eval || !w.tun.ell() || w.tun.cg_form != OASIS_CG_FORM_AUTO ||
         !w.tun.grid_auto || n > kCoopMaxRows)
         return false;
-    int dev = 0, cu = 0, coop = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess)
-        return false;
-    return coop != 0 && n <= static_cast<long long>(std::min(cu, kCoopBlocks)) * kCoopThreads;
+    int most = 0;
+    return coop_blocks(s, &most) == OASIS_OK && n <= most * kCoopThreads;
 }
 
 template <typename T>
-int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T *vnull, int it0, int m, bool beta_zero) {
-    int dev = 0, cu = 0;
-    OASIS_TRY_HIP(hipGetDevice(&dev));
-    OASIS_TRY_HIP(hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev));
+int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T *vnull, int it0, int m, bool beta_zero,
+                CGState *h, int *lost) {
+    int most = 0;
+    OASIS_TRY(coop_blocks(s, &most));
     // as many blocks as there are, down to 256 rows each: fewer rows per
     // block shorten the gathers, and the exchange hardly depends on the grid
     // (1.4 us between 32 blocks, 1.5 us between 256)
-    const int most = std::min(cu, kCoopBlocks);
     const int grid = std::min(most, (n + kBlock - 1) / kBlock);
     CoopArgs a{};
     a.n = n;
@@ -502,17 +503,14 @@ int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T 
     a.beta_zero = beta_zero ? 1 : 0;
     a.slots[0] = reinterpret_cast<u64 *>(w.partA);
     a.slots[1] = reinterpret_cast<u64 *>(w.partB);
-    a.lose = w.lose;
     if (n <= kOneThreads * kOneRows) {
         if (n <= kOneThreads)
             hipLaunchKernelGGL((k_cg_one<T, 1>), dim3(1), dim3(kOneThreads), 0, s, a);
         else
             hipLaunchKernelGGL((k_cg_one<T, kOneRows>), dim3(1), dim3(kOneThreads), 0, s, a);
         OASIS_TRY_LAUNCH();
-        return OASIS_OK;
+        return read_state(s, w.stage, w.st, h, sizeof(*h));
     }
-    hipLaunchKernelGGL(k_words_clear<T>, dim3(grid_for(n, kBlock, 1024)), dim3(kBlock), 0, s, n, a);
-    OASIS_TRY_LAUNCH();
     void *args[] = {&a};
     const void *kern;
     int bs;
@@ -526,20 +524,29 @@ int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T 
         kern = reinterpret_cast<const void *>(&k_cg_coop<T, 1024>);
         bs = 1024;
     }
-    const hipError_t e = hipLaunchCooperativeKernel(kern, dim3(grid), dim3(bs), args, 0, s);
-    if (e != hipSuccess) {
-        // refused (nothing has run): the caller takes the other kernels
-        (void)hipGetLastError();
-        return OASIS_EUNSUPPORTED;
+    for (int attempt = 0;; ++attempt) {
+        a.join = join_ticks();
+        a.lose = lose_wait(w.lose, attempt);
+        hipLaunchKernelGGL(k_words_clear<T>, dim3(grid_for(n, kBlock, 1024)), dim3(kBlock), 0, s, n, a);
+        OASIS_TRY_LAUNCH();
+        if (hipLaunchKernel(kern, dim3(grid), dim3(bs), args, 0, s) != hipSuccess) {
+            // refused (nothing has run): the caller takes the other kernels
+            (void)hipGetLastError();
+            return OASIS_EUNSUPPORTED;
+        }
+        OASIS_TRY(read_state(s, w.stage, w.st, h, sizeof(*h)));
+        if (h->flag < kCoopLate) return OASIS_OK;
+        *lost += 1;
+        // (a later wait is lost after blocks may have written x)
+        if (h->flag != kCoopLate || attempt + 1 == kCoopTries) return OASIS_OK;
     }
-    return OASIS_OK;
 }
 
-template bool cg_coop_fits<double>(int, const CGWork<double> &);
-template bool cg_coop_fits<float>(int, const CGWork<float> &);
+template bool cg_coop_fits<double>(hipStream_t, int, const CGWork<double> &);
+template bool cg_coop_fits<float>(hipStream_t, int, const CGWork<float> &);
 template int cg_coop_run<double>(hipStream_t, int, CGWork<double> &, double *, const double *, const double *, int,
-                                 int, bool);
+                                 int, bool, CGState *, int *);
 template int cg_coop_run<float>(hipStream_t, int, CGWork<float> &, float *, const float *, const float *, int, int,
-                                bool);
+                                bool, CGState *, int *);
 
 }  // namespace oasis

@@ -1,6 +1,22 @@
-// What the cooperative solver kernels (cg_coop.hip, bicg_coop.hip) share: the
-// words that cross blocks, and the columns of a block's rows.
+// What the cooperative solver kernels (cg_coop.hip, bicg_coop.hip) share: their
+// launch, the words that cross blocks, and the columns of a block's rows.
+//
+// The kernels are launched as any other.  A grid has at most a block per CU of
+// its stream, so its blocks come together as soon as what else runs on these
+// CUs has ended; the first exchange waits for that, a few ms at most, and a
+// launch that has waited in vain has changed nothing and is made again.  That
+// happens when two such grids, of two threads or processes, are dispatched
+// in the same few us and each holds CUs that the other needs: one in 1300
+// solves of two processes that did nothing else.  (hipLaunchCooperativeKernel
+// excludes it by a queue that the device gives to one process at a time, for
+// tens of ms: with two processes on one card a CG solve of 25,600 rows took one
+// of them 41 ms and the other 4.0, where alone it takes 1.0 and now takes both
+// 1.14; 199,680 rows 144 and 2.6 ms, now 4.6 and 4.6; BiCGStab with three
+// right-hand sides on 25,600 rows 54 and 6.0 ms, now 2.5 and 2.5.)
 #pragma once
+#include <algorithm>
+#include <chrono>
+
 #include "krylov.hpp"
 
 namespace oasis {
@@ -13,7 +29,11 @@ constexpr int kCoopThreads = 1024;             // most threads of a block
 constexpr int kCoopBlocks = 256;               // most blocks: four slots per lane of a reading wave
 constexpr int kCoopMaxRows = kCoopBlocks * kCoopThreads;
 constexpr int kBitWords = kCoopMaxRows / 32;
-constexpr long long kCoopTicks = 200000000ll;  // 2 s of the 100 MHz wall clock
+// The longest waits, in ticks of the 100 MHz wall clock: for the grid to come
+// together 5 to 10 ms (of two grids that hold each other up one should give in
+// well before the other), 2 s after that; and launches to come together in.
+constexpr unsigned kJoinTicks = 500000, kCoopTicks = 200000000;
+constexpr int kCoopTries = 6;
 
 // The exchanged words: a T's bits, or the empty mark, a NaN that no sent
 // value has (every NaN is sent as the quiet one).
@@ -100,6 +120,31 @@ template <int BS>
 constexpr int kCoopHaloPer = BS >= 1024 ? 4 : 8;
 // LDS of coop_columns.
 constexpr size_t kCoopSetup = kBitWords * (sizeof(unsigned) + sizeof(unsigned short));
+
+// Most blocks of a grid on this stream: one per CU that its kernels may use.
+inline int coop_blocks(hipStream_t s, int *blocks) {
+    int dev = 0, cu = 0;
+    OASIS_TRY_HIP(hipGetDevice(&dev));
+    OASIS_TRY_HIP(hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev));
+    uint32_t mask[kCoopBlocks / 32] = {};
+    int bits = 0;
+    if (hipExtStreamGetCUMask(s, kCoopBlocks / 32, mask) == hipSuccess)
+        for (uint32_t m : mask) bits += __builtin_popcount(m);
+    else
+        (void)hipGetLastError();
+    if (bits > 0) cu = std::min(cu, bits);
+    *blocks = std::min(cu, kCoopBlocks);
+    return OASIS_OK;
+}
+
+// A launch's kJoinTicks to twice that.
+inline unsigned join_ticks() {
+    return kJoinTicks + static_cast<unsigned>(std::chrono::steady_clock::now().time_since_epoch().count() % kJoinTicks);
+}
+
+// The wait (1, 2, ...) that launch number `attempt` is to lose; see
+// OASIS_KRYLOV_LOSE_WAIT.
+inline int lose_wait(int lose, int attempt) { return attempt == 0 || (lose & 0x4000) ? lose & 0x3fff : 0; }
 
 // This thread's row of the matrix (row `at` of [r0, r1)): its values, zero if
 // it has no row (own), and its columns as positions in a block's vector of BS

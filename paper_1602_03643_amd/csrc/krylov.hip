@@ -995,7 +995,7 @@ static int cg_run(hipStream_t s, int n, const int *rp, const int *ci, const T *v
     };
     OASIS_TRY(residual(0, 0));
     if (sr) OASIS_TRY(loop.start(0, false));
-    bool coop = sizeof(T) == 8 && cg_coop_fits(n, w);
+    bool coop = sizeof(T) == 8 && cg_coop_fits(s, n, w);
     CGState h;
     ChunkPlan plan(check_every);
     // a cooperative run tests the start residual itself
@@ -1018,7 +1018,7 @@ static int cg_run(hipStream_t s, int n, const int *rp, const int *ci, const T *v
     while (true) {
         const int m = std::min(coop ? (check_every > 0 ? check_every : kCoopRun) : plan.next, maxit - it);
         if (coop && m > 0) {
-            const int rcc = cg_coop_run<T>(s, n, w, x, wgt, nullptr, it, m, it == restart_at);
+            const int rcc = cg_coop_run<T>(s, n, w, x, wgt, nullptr, it, m, it == restart_at, &h, &out.lost);
             if (rcc == OASIS_EUNSUPPORTED) {
                 OASIS_TRY(leave_coop(it));
                 continue;
@@ -1050,9 +1050,9 @@ static int cg_run(hipStream_t s, int n, const int *rp, const int *ci, const T *v
             }
         }
         it += m;
-        OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
-        if (coop && m > 0) (h.flag >= kCoopLost ? out.lost : out.coop) += 1;
-        if (h.flag >= kCoopLost) {
+        if (!coop || m <= 0) OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
+        else if (h.flag < kCoopLate) out.coop += 1;
+        if (h.flag >= kCoopLate) {
             // no iteration counts
             it -= m;
             OASIS_TRY(leave_coop(it));
@@ -1154,7 +1154,7 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
     const CgGrids<BS> g = CgGrids<BS>::template make<C>(n, cap);
     const bool ell = w.cols.any() && w.eval && w.tun.ell();
     // cooperative runs keep the (r, p) pairs of the two-kernel form
-    bool coop = cg_coop_fits(n, w);
+    bool coop = cg_coop_fits(s, n, w);
     bool sr = ell && w.tun.single(4) && !coop;
     SrLoop<float> loop(s, n, w, wgt32, vnull, vscale);
     const int g1 = ell ? launch_p1_ell<float, BS>(s, cap, n, w.cols, w.eval, nullptr, nullptr, nullptr, nullptr, 0,
@@ -1219,7 +1219,8 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
     while (true) {
         const int m = std::min(coop ? (check_every > 0 ? check_every : kCoopRun) : plan.next, maxit - it);
         if (coop && m > 0) {
-            const int rcc = cg_coop_run<float>(s, n, w, xlo, wgt32, vnull, it, m, it == restart_at);
+            const int rcc = cg_coop_run<float>(s, n, w, xlo, wgt32, vnull, it, m, it == restart_at, &h,
+                                                    &out.lost);
             if (rcc == OASIS_EUNSUPPORTED) {
                 OASIS_TRY(leave_coop(it));
                 nin = gv;
@@ -1250,9 +1251,9 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
         }
         it += m;
         nin = g.p2;
-        OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
-        if (coop && m > 0) (h.flag >= kCoopLost ? out.lost : out.coop) += 1;
-        if (h.flag >= kCoopLost) {
+        if (!coop || m <= 0) OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
+        else if (h.flag < kCoopLate) out.coop += 1;
+        if (h.flag >= kCoopLate) {
             // no iteration counts
             it -= m;
             OASIS_TRY(leave_coop(it));

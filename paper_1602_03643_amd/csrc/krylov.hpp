@@ -16,7 +16,7 @@ struct CGState {
     double upd2;       // mixed precision: replace the residual once wrr <= upd2
     int flag;          // 0 running, 1 converged candidate, 2 breakdown, 3 non-finite,
                        // 4 residual replacement due (mixed precision),
-                       // kCoopLost or kCoopUnfit: a cooperative run that does not count
+                       // kCoopLate and above: a cooperative run that does not count
     int it_done;       // iteration index at which flag was raised
     double wrr_it;     // weighted r.r entering iteration it_last (the last one that ran)
     int it_last;
@@ -167,24 +167,27 @@ int cg_mixed_solve(hipStream_t s, int n, const int *rp, const int *ci, const dou
 // Cooperative CG runs (cg_coop.hip): up to m iterations in one launch on
 // the (r, p) pairs, from iteration it0, with k_cg_p1 / k_cg_p2's recurrences,
 // tests and state; beta_zero starts a fresh direction.  cg_coop_fits: whether
-// the system, the device and the tuning allow them.  cg_coop_run:
-// EUNSUPPORTED when the launch was refused.
+// the system, the device and the tuning allow them.  cg_coop_run reads the
+// state into *h (flag kCoopLate or above: the run does not count) and adds the
+// launches that do not count to *lost; EUNSUPPORTED when the launch was
+// refused.
 template <typename T>
-bool cg_coop_fits(int n, const CGWork<T> &w);
+bool cg_coop_fits(hipStream_t s, int n, const CGWork<T> &w);
 template <typename T>
-int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T *vnull, int it0, int m, bool beta_zero);
-// The flags of a run that does not count: a wait that ran out (something else
-// holds the CUs that the rest of the grid needs), or too wide a halo, which
-// outweighs the waits that it leaves unmet.  The solve goes on with the other
-// kernels.
-constexpr int kCoopLost = 5, kCoopUnfit = 6;
+int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T *vnull, int it0, int m, bool beta_zero,
+                CGState *h, int *lost);
+// The flags of a run that does not count: the grid did not come together
+// (something else holds the CUs that the rest of it needs; nothing has been
+// changed), a later wait ran out, or too wide a halo, which outweighs the waits
+// that it leaves unmet.
+constexpr int kCoopLate = 5, kCoopLost = 6, kCoopUnfit = 7;
 // Iterations of one cooperative run at most (it stops by itself).
 constexpr int kCoopRun = 4096;
 
 // A whole BiCGStab solve in one cooperative launch (bicg_coop.hip), for one to
 // three right-hand sides; arguments and results of bicgstab_solve.
-// EUNSUPPORTED: not for this system, device or tuning, or out of time; the
-// other kernels go on from x.  *lost: launches that do not count.
+// EUNSUPPORTED: not for this system, device or tuning, or out of time; x is as
+// it was.  *lost: launches that do not count.
 template <typename T>
 int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const *b, T *const *x, double rtol, int maxit,
                     BiWork<T> &w, SolveOut *out, bool inner, int *lost);

@@ -147,21 +147,28 @@ def _bicgstab(oa, A, b, x0, prec, flags=0, **kw):
 @pytest.mark.parametrize("mesh", [lambda: synth.channel(17, 17, 13), lambda: synth.channel(49, 45, 41),
                                   lambda: synth.channel(65, 64, 65)])
 def test_bicgstab_after_a_lost_wait(oa, mesh, precision):
-    """A wait lost in the first sum, in products, in sums and late in the solve:
-    the launched form must start from the caller's iterate, so the results are
-    its own, bit for bit, whatever the lost launch had done to x."""
+    """A wait lost in the first sum, in products, in sums and late in the solve.
+    The repeat, and after too many of them the launched form, must start from
+    the caller's iterate: results are those of an undisturbed solve, bit for
+    bit, whatever the lost launches had done to x."""
     mesh = mesh()
     say("bicgstab lost wait", mesh.name, precision)
     prec = oa.F64 if precision == "f64" else oa.F32
     A, H, rng = _system(oa, mesh, 6)
     b, x0 = T(rng.normal(size=(2, mesh.n_dof))), T(rng.normal(size=(2, mesh.n_dof)))
     torch.cuda.synchronize()
-    rc, ref, st = _bicgstab(oa, A, b, x0, prec, grid_cap=512)
-    assert rc == 0 and st[0].coop_runs == 0
+    refs = []
+    for always, cap in ((0, 0), (1, 512)):
+        rc, x, st = _bicgstab(oa, A, b, x0, prec, grid_cap=cap)
+        assert rc == 0 and (st[0].coop_runs == 0) == (always == 1) and st[0].coop_lost == 0
+        refs.append((x, [s.iters for s in st]))
     for k in (1, 2, 3, 4, 5, 6, 7, 16, 17, 18):
-        rc, x, got = _bicgstab(oa, A, b, x0, prec, flags=k << 16)
-        assert rc == 0 and [g.coop_lost for g in got] == [1, 1], k
-        assert torch.equal(x, ref) and [g.iters for g in got] == [s.iters for s in st], k
+        for always, (ref, iters) in enumerate(refs):
+            rc, x, st = _bicgstab(oa, A, b, x0, prec, flags=(k + (always << 14)) << 16)
+            # once for each solve (the refinement steps of FP32), or every time
+            lost = range(6, 7) if always else range(1, 1 + max(1, st[0].outer_iters))
+            assert rc == 0 and all(s.coop_lost in lost and (s.coop_runs > 0) == (not always) for s in st), (k, always)
+            assert torch.equal(x, ref) and [s.iters for s in st] == iters, (k, always)
 
 
 def _pcg(oa, A, b, prec, flags=0):
@@ -192,12 +199,16 @@ def test_cg_after_a_lost_wait(oa, mesh, precision):
     A, H, b = _spd(oa, mesh, 6)
     B = T(b)
     torch.cuda.synchronize()
-    rc, x, ref = _pcg(oa, A, B, prec)
+    rc, first, ref = _pcg(oa, A, B, prec)
     assert rc == 0 and ref.coop_runs > 0 and ref.coop_lost == 0
     # a mixed solve's first launch ends when the residual has fallen tenfold
     last = [2 * ref.iters + 1] * 4 if precision == "f64" else []
-    for k in [1, 2, 3, 4, 9, 10] + last:
+    for k in [2, 3, 4, 9, 10, (1 << 14) + 1] + last:
         rc, x, st = _pcg(oa, A, B, prec, flags=k << 16)
-        assert rc == 0 and st.coop_lost == 1 and st.coop_runs == 0, (k, st.coop_lost, st.coop_runs)
+        assert rc == 0 and st.coop_lost == (6 if k >> 14 else 1) and st.coop_runs == 0, (k, st.coop_lost, st.coop_runs)
         assert np.linalg.norm(b - H @ x.cpu().numpy()) <= 1.001 * RTOL * np.linalg.norm(b), k
-        assert abs(st.iters - ref.iters) <= max(3, ref.iters // 10) + k // 2
+        assert abs(st.iters - ref.iters) <= max(3, ref.iters // 10) + (k & 0x3fff) // 2
+    # a grid that does not come together has changed nothing and is launched again
+    rc, y, st = _pcg(oa, A, B, prec, flags=1 << 16)
+    assert rc == 0 and st.coop_runs == ref.coop_runs and st.coop_lost == (1 if precision == "f64" else ref.coop_runs)
+    assert torch.equal(y, first) and st.iters == ref.iters
