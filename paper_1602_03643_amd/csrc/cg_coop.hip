@@ -461,6 +461,48 @@ __global__ __launch_bounds__(kBlock) void k_words_clear(int n, CoopArgs a) {
 
 }  // namespace
 
+namespace {
+
+// *most = the widest halo of the blocks of `rows` rows, from the ELL offsets
+__global__ __launch_bounds__(kCoopThreads) void k_coop_halo(int n, int rows, const short *__restrict__ ecol, int *most) {
+    __shared__ unsigned bits[kBitWords];
+    __shared__ int count;
+    const int t = threadIdx.x, r0 = blockIdx.x * rows, r1 = min(n, r0 + rows), nw = (n + 31) / 32;
+    for (int w = t; w < nw; w += kCoopThreads) bits[w] = 0u;
+    if (t == 0) count = 0;
+    __syncthreads();
+    constexpr int Q = kEll / 4;               // four offsets at a time
+    for (int i = r0 * Q + t; i < r1 * Q; i += kCoopThreads) {
+        const short4 d = reinterpret_cast<const short4 *>(ecol)[i];
+        const int row = i / Q;
+        const int c[4] = {ell_col(row, d.x, n), ell_col(row, d.y, n), ell_col(row, d.z, n), ell_col(row, d.w, n)};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (c[k] < r0 || c[k] >= r1) atomicOr(&bits[c[k] >> 5], 1u << (c[k] & 31));
+    }
+    __syncthreads();
+    int mine = 0;
+    for (int w = t; w < nw; w += kCoopThreads) mine += __popc(bits[w]);
+    if (mine) atomicAdd(&count, mine);
+    __syncthreads();
+    if (t == 0 && count) atomicMax(most, count);
+}
+
+}  // namespace
+
+int coop_halo(hipStream_t s, int n, const short *ecol, int *most, int *room) {
+    int blocks = 0;
+    *room = 0;
+    OASIS_TRY(coop_blocks(s, &blocks));
+    if (n > blocks * kCoopThreads) return OASIS_OK;
+    const int grid = std::min(blocks, (n + kBlock - 1) / kBlock), rows = (n + grid - 1) / grid;
+    *room = rows <= 256 ? kCoopHaloPer<256> * 256 : rows <= 512 ? kCoopHaloPer<512> * 512 : kCoopHaloPer<1024> * 1024;
+    if (n - rows <= *room) return OASIS_OK;   // whatever the columns are
+    hipLaunchKernelGGL(k_coop_halo, dim3(grid), dim3(kCoopThreads), 0, s, n, rows, ecol, most);
+    OASIS_TRY_LAUNCH();
+    return OASIS_OK;
+}
+
 template <typename T>
 bool cg_coop_fits(hipStream_t s, int n, const CGWork<T> &w) {
     // one row per thread of one block per CU; the kernel and grid the caller

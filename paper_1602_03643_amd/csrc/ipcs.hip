@@ -1270,15 +1270,20 @@ struct oasis_ipcs {
 
 // ELL copy of a matrix on a CSR pattern and the pattern dictionary of its
 // offsets; *cols receives the columns the products use (none when the
-// offsets do not fit, and the products then run on CSR).  Synchronises.
+// offsets do not fit, and the products then run on CSR); *off: cooperative
+// runs have no room for the columns (asking here, beside the other questions,
+// takes 8 us; a solve that is refused by its first launch had lost 75 us, a
+// sixth of a loose solve of 3264 rows).  tmp: two ints.  Synchronises.
 static int ell_setup(hipStream_t s, int n, const int *rp, const int *ci, const double *val, short *ecol,
                      unsigned short *pid, short *ptab, double *eval, float *eval32, int *tmp, const Tuning &tun,
-                     EllCols *cols, int *storage = nullptr) {
-    bool fits = false;
+                     EllCols *cols, bool *off, int *storage = nullptr) {
+    bool fits = false, coop = false;
+    *off = true;
     *cols = EllCols{};
     if (storage) *storage = 0;
     if (!tun.ell()) return OASIS_OK;
-    OASIS_TRY(csr_to_ell(s, n, rp, ci, val, ecol, eval, eval32, tmp, &fits));
+    OASIS_TRY(csr_to_ell(s, n, rp, ci, val, ecol, eval, eval32, tmp, &fits, tun.grid_auto ? &coop : nullptr));
+    *off = !coop;
     if (!fits) return OASIS_OK;
     int npat = 0;
     OASIS_TRY(ell_dictionary(s, n, ecol, pid, ptab, tmp, &npat, tun.dict()));
@@ -1556,9 +1561,11 @@ extern "C" int oasis_ipcs_create(void *stream, const oasis_mesh *mesh, const int
     // ELL copy of the pressure matrix for the CG product when its rows and
     // column offsets allow it (else the CSR product runs)
     {
+        bool off = false;
         const int rc4 = ell_setup(s, n, row_ptr, col_idx, h->Ks, h->ecol, h->pid, h->ptab, h->eval, h->eval32,
-                                  h->flag + 24, h->tun, &h->cols);
+                                  h->flag + 24, h->tun, &h->cols, &off);
         if (rc4 != OASIS_OK) return fail(rc4);
+        h->cg.coop_off = h->cg32.coop_off = h->cgM.coop_off = h->bi.coop_off = h->bi32.coop_off = off;
         const bool fits = h->cols.any();
         h->ell = fits;
         if (fits && h->consistent) {
@@ -2286,8 +2293,10 @@ static int pcg_run(void *stream, const oasis_csr *A, const double *b, double *x,
     int ell_storage = 0;
     {
         EllCols cols;
+        bool off = false;
         OASIS_TRY(ell_setup(s, n, A->row_ptr, A->col_idx, k.val, k.ecol, k.pid, k.ptab, k.eval, k.eval32,
-                            k.flag + 8, tun, &cols, &ell_storage));
+                            k.flag + 8, tun, &cols, &off, &ell_storage));
+        k.cg.coop_off = k.cg32.coop_off = off;
         if (cols.any() && mixed) {
             k.cg32.cols = cols;
             k.cg32.eval = k.eval32;
@@ -2405,8 +2414,10 @@ extern "C" int oasis_bicgstab(void *stream, const oasis_csr *A, int32_t nrhs, co
     int ell_storage = 0;
     {
         EllCols cols;
+        bool off = false;
         OASIS_TRY(ell_setup(s, n, A->row_ptr, A->col_idx, k.val, k.ecol, k.pid, k.ptab, k.eval, k.eval32,
-                            k.flag + 8, tun, &cols, &ell_storage));
+                            k.flag + 8, tun, &cols, &off, &ell_storage));
+        k.bi.coop_off = k.bi32.coop_off = off;
         if (cols.any() && mixed) {
             k.bi32.cols = cols;
             k.bi32.eval = k.eval32;

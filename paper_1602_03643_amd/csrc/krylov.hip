@@ -686,16 +686,18 @@ int csr_max_row(hipStream_t s, int n, const int *rp, int *tmp, int *out) {
 }
 
 int csr_to_ell(hipStream_t s, int n, const int *rp, const int *ci, const double *val, short *ecol,
-               double *eval, float *eval32, int *tmp, bool *fits) {
+               double *eval, float *eval32, int *tmp, bool *fits, bool *coop) {
     if (!ecol || (!eval && !eval32) || !tmp || !fits) return OASIS_EINVAL;
-    hipLaunchKernelGGL(k_fill<int>, dim3(1), dim3(kBlock), 0, s, 1, tmp, 0);
+    hipLaunchKernelGGL(k_fill<int>, dim3(1), dim3(kBlock), 0, s, coop ? 2 : 1, tmp, 0);
     hipLaunchKernelGGL(k_csr_to_ell, dim3(grid_for(n, kBlock / kEll, 16384)), dim3(kBlock), 0, s, n, rp, ci, val, ecol,
                        eval, eval32, tmp);
     OASIS_TRY_LAUNCH();
-    int misfit = 1;
-    OASIS_TRY_HIP(hipMemcpyAsync(&misfit, tmp, sizeof(int), hipMemcpyDeviceToHost, s));
+    int room = 0, got[2] = {1, 0};            // a misfit, the widest halo
+    if (coop) OASIS_TRY(coop_halo(s, n, ecol, tmp + 1, &room));
+    OASIS_TRY_HIP(hipMemcpyAsync(got, tmp, (coop ? 2 : 1) * sizeof(int), hipMemcpyDeviceToHost, s));
     OASIS_TRY_HIP(hipStreamSynchronize(s));
-    *fits = misfit == 0;
+    *fits = got[0] == 0;
+    if (coop) *coop = *fits && room > 0 && got[1] <= room;
     return OASIS_OK;
 }
 

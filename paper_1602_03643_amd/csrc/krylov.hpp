@@ -199,9 +199,14 @@ int csr_max_row(hipStream_t s, int n, const int *rp, int *tmp, int *out);
 // spmv.hpp): ecol [n][kEll] 16-bit cyclic column offsets, and the values
 // as FP64 (eval) and/or their FP32 rounding (eval32); either value array
 // may be null, not both.  *fits (host) tells whether every offset fitted;
-// if not, the copy must not be used.  tmp: one device int.  Synchronises.
+// if not, the copy must not be used.  tmp: one device int, two with `coop`.
+// coop (host, nullable): whether the blocks of a cooperative run have room for
+// the columns that they reference in other blocks' rows.  Synchronises.
 int csr_to_ell(hipStream_t s, int n, const int *rp, const int *ci, const double *val, short *ecol,
-               double *eval, float *eval32, int *tmp, bool *fits);
+               double *eval, float *eval32, int *tmp, bool *fits, bool *coop = nullptr);
+// The widest such halo into the device int *most, which must be zero; *room:
+// what fits (0: no cooperative runs at this size).
+int coop_halo(hipStream_t s, int n, const short *ecol, int *most, int *room);
 
 // Most distinct offset lists an ELL pattern dictionary holds.
 constexpr int kMaxEllPatterns = 4096;
