@@ -599,12 +599,12 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
     // one row per thread of one block per CU; a kernel and grid that the
     // caller asked for are left as they are.  An iteration takes 10-20 us:
     // kCoopRun of them bound a launch that does not converge.
-    if (w.coop_off || !w.cols.any() || !w.eval || !w.tun.ell() || !w.tun.grid_auto || n > kCoopMaxRows ||
+    if (!w.cols.any() || !w.eval || !w.tun.ell() || !w.tun.grid_auto || n > kCoopMaxRows ||
         maxit > kCoopRun)
         return OASIS_EUNSUPPORTED;
     int most = 0;
     OASIS_TRY(coop_blocks(s, &most));
-    if (n > most * kCoopThreads) return OASIS_EUNSUPPORTED;
+    if (n > most * kCoopThreads || !w.coop.next()) return OASIS_EUNSUPPORTED;
     const int grid = std::min(most, (n + kBlock - 1) / kBlock);
     BiCoopArgs a{};
     a.n = n;
@@ -652,11 +652,16 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
             hipLaunchKernelGGL(k_bi_coop_back<T>, dim3(grid_for(n, kBlock, 1024)), dim3(kBlock), 0, s, nrhs, a);
             OASIS_TRY_LAUNCH();
         }
-        if (h.glob.pause == kCoopUnfit || attempt + 1 == kCoopTries) {
-            w.coop_off = true;
+        if (h.glob.pause == kCoopUnfit) {
+            w.coop.never = true;
+            return OASIS_EUNSUPPORTED;
+        }
+        if (attempt + 1 == kCoopTries) {
+            w.coop.gave_up();
             return OASIS_EUNSUPPORTED;
         }
     }
+    w.coop.worked();
     int worst = OASIS_OK;
     for (int k = 0; k < nrhs; ++k) {
         const BiState &o = h.st[k];

@@ -504,14 +504,14 @@ int coop_halo(hipStream_t s, int n, const short *ecol, int *most, int *room) {
 }
 
 template <typename T>
-bool cg_coop_fits(hipStream_t s, int n, const CGWork<T> &w) {
+bool cg_coop_fits(hipStream_t s, int n, CGWork<T> &w) {
     // one row per thread of one block per CU; the kernel and grid the caller
     // asked for by name are left as they are
-    if (w.coop_off || !w.cols.any() || !w.eval || !w.tun.ell() || w.tun.cg_form != OASIS_CG_FORM_AUTO ||
+    if (!w.cols.any() || !w.eval || !w.tun.ell() || w.tun.cg_form != OASIS_CG_FORM_AUTO ||
         !w.tun.grid_auto || n > kCoopMaxRows)
         return false;
     int most = 0;
-    return coop_blocks(s, &most) == OASIS_OK && n <= most * kCoopThreads;
+    return coop_blocks(s, &most) == OASIS_OK && n <= most * kCoopThreads && w.coop.next();
 }
 
 template <typename T>
@@ -584,8 +584,8 @@ int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T 
     }
 }
 
-template bool cg_coop_fits<double>(hipStream_t, int, const CGWork<double> &);
-template bool cg_coop_fits<float>(hipStream_t, int, const CGWork<float> &);
+template bool cg_coop_fits<double>(hipStream_t, int, CGWork<double> &);
+template bool cg_coop_fits<float>(hipStream_t, int, CGWork<float> &);
 template int cg_coop_run<double>(hipStream_t, int, CGWork<double> &, double *, const double *, const double *, int,
                                  int, bool, CGState *, int *);
 template int cg_coop_run<float>(hipStream_t, int, CGWork<float> &, float *, const float *, const float *, int, int,

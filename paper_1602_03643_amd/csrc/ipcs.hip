@@ -1565,7 +1565,8 @@ extern "C" int oasis_ipcs_create(void *stream, const oasis_mesh *mesh, const int
         const int rc4 = ell_setup(s, n, row_ptr, col_idx, h->Ks, h->ecol, h->pid, h->ptab, h->eval, h->eval32,
                                   h->flag + 24, h->tun, &h->cols, &off);
         if (rc4 != OASIS_OK) return fail(rc4);
-        h->cg.coop_off = h->cg32.coop_off = h->cgM.coop_off = h->bi.coop_off = h->bi32.coop_off = off;
+        h->cg.coop.never = h->cg32.coop.never = h->cgM.coop.never = off;
+        h->bi.coop.never = h->bi32.coop.never = off;
         const bool fits = h->cols.any();
         h->ell = fits;
         if (fits && h->consistent) {
@@ -2296,7 +2297,7 @@ static int pcg_run(void *stream, const oasis_csr *A, const double *b, double *x,
         bool off = false;
         OASIS_TRY(ell_setup(s, n, A->row_ptr, A->col_idx, k.val, k.ecol, k.pid, k.ptab, k.eval, k.eval32,
                             k.flag + 8, tun, &cols, &off, &ell_storage));
-        k.cg.coop_off = k.cg32.coop_off = off;
+        k.cg.coop.never = k.cg32.coop.never = off;
         if (cols.any() && mixed) {
             k.cg32.cols = cols;
             k.cg32.eval = k.eval32;
@@ -2417,7 +2418,7 @@ extern "C" int oasis_bicgstab(void *stream, const oasis_csr *A, int32_t nrhs, co
         bool off = false;
         OASIS_TRY(ell_setup(s, n, A->row_ptr, A->col_idx, k.val, k.ecol, k.pid, k.ptab, k.eval, k.eval32,
                             k.flag + 8, tun, &cols, &off, &ell_storage));
-        k.bi.coop_off = k.bi32.coop_off = off;
+        k.bi.coop.never = k.bi32.coop.never = off;
         if (cols.any() && mixed) {
             k.bi32.cols = cols;
             k.bi32.eval = k.eval32;

@@ -1011,9 +1011,12 @@ static int cg_run(hipStream_t s, int n, const int *rp, const int *ci, const T *v
         out.rel_res = wbb > 0.0 ? std::sqrt(wrr / wbb) : std::sqrt(wrr);
     };
     // the other kernels go on from the explicit residual
-    auto leave_coop = [&](int at) -> int {
+    auto leave_coop = [&](int at, bool unfit) -> int {
         coop = false;
-        w.coop_off = true;
+        if (unfit)
+            w.coop.never = true;
+        else
+            w.coop.gave_up();
         restart_at = at;
         return residual(1, at);
     };
@@ -1022,7 +1025,7 @@ static int cg_run(hipStream_t s, int n, const int *rp, const int *ci, const T *v
         if (coop && m > 0) {
             const int rcc = cg_coop_run<T>(s, n, w, x, wgt, nullptr, it, m, it == restart_at, &h, &out.lost);
             if (rcc == OASIS_EUNSUPPORTED) {
-                OASIS_TRY(leave_coop(it));
+                OASIS_TRY(leave_coop(it, false));
                 continue;
             }
             OASIS_TRY(rcc);
@@ -1052,12 +1055,16 @@ static int cg_run(hipStream_t s, int n, const int *rp, const int *ci, const T *v
             }
         }
         it += m;
-        if (!coop || m <= 0) OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
-        else if (h.flag < kCoopLate) out.coop += 1;
+        if (!coop || m <= 0) {
+            OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
+        } else if (h.flag < kCoopLate) {
+            out.coop += 1;
+            w.coop.worked();
+        }
         if (h.flag >= kCoopLate) {
             // no iteration counts
             it -= m;
-            OASIS_TRY(leave_coop(it));
+            OASIS_TRY(leave_coop(it, h.flag == kCoopUnfit));
             continue;
         }
         if (h.flag == 0) {
@@ -1209,9 +1216,12 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
     int rc = OASIS_OK;
     // the single-reduction (or two-kernel) iterations go on from the FP64
     // residual with a fresh direction
-    auto leave_coop = [&](int at) -> int {
+    auto leave_coop = [&](int at, bool unfit) -> int {
         coop = false;
-        w.coop_off = true;
+        if (unfit)
+            w.coop.never = true;
+        else
+            w.coop.gave_up();
         sr = ell && w.tun.single(4);
         restart_at = at;
         OASIS_TRY(fold());
@@ -1224,7 +1234,7 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
             const int rcc = cg_coop_run<float>(s, n, w, xlo, wgt32, vnull, it, m, it == restart_at, &h,
                                                     &out.lost);
             if (rcc == OASIS_EUNSUPPORTED) {
-                OASIS_TRY(leave_coop(it));
+                OASIS_TRY(leave_coop(it, false));
                 nin = gv;
                 continue;
             }
@@ -1253,12 +1263,16 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
         }
         it += m;
         nin = g.p2;
-        if (!coop || m <= 0) OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
-        else if (h.flag < kCoopLate) out.coop += 1;
+        if (!coop || m <= 0) {
+            OASIS_TRY(read_state(s, w.stage, w.st, &h, sizeof(h)));
+        } else if (h.flag < kCoopLate) {
+            out.coop += 1;
+            w.coop.worked();
+        }
         if (h.flag >= kCoopLate) {
             // no iteration counts
             it -= m;
-            OASIS_TRY(leave_coop(it));
+            OASIS_TRY(leave_coop(it, h.flag == kCoopUnfit));
             nin = gv;
             continue;
         }

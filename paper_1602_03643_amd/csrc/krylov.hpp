@@ -3,6 +3,7 @@
 // points and the IPCS step.
 #pragma once
 
+#include "coop_use.hpp"
 #include "internal.hpp"
 #include "spmv.hpp"
 
@@ -56,7 +57,7 @@ struct CGWork {
     const T *eval = nullptr;
     Tuning tun;
     HostStage stage;   // the owner's read-back block (may be null)
-    bool coop_off = false;   // the pattern's halo is too wide for cooperative runs
+    CoopUse coop;
     int lose = 0;            // the wait of a cooperative run that is taken as lost (tests)
 };
 
@@ -110,7 +111,7 @@ struct BiWork {
     const T *eval = nullptr;
     HostStage stage;   // the owner's read-back block (may be null)
     Tuning tun;
-    bool coop_off = false;   // the pattern's halo is too wide for a cooperative solve
+    CoopUse coop;
     int lose = 0;            // the wait of a cooperative solve that is taken as lost (tests)
 };
 
@@ -166,13 +167,13 @@ int cg_mixed_solve(hipStream_t s, int n, const int *rp, const int *ci, const dou
 
 // Cooperative CG runs (cg_coop.hip): up to m iterations in one launch on
 // the (r, p) pairs, from iteration it0, with k_cg_p1 / k_cg_p2's recurrences,
-// tests and state; beta_zero starts a fresh direction.  cg_coop_fits: whether
-// the system, the device and the tuning allow them.  cg_coop_run reads the
+// tests and state; beta_zero starts a fresh direction.  cg_coop_fits, asked once
+// a solve: whether the system, the device, the tuning and w.coop allow them.  cg_coop_run reads the
 // state into *h (flag kCoopLate or above: the run does not count) and adds the
 // launches that do not count to *lost; EUNSUPPORTED when the launch was
 // refused.
 template <typename T>
-bool cg_coop_fits(hipStream_t s, int n, const CGWork<T> &w);
+bool cg_coop_fits(hipStream_t s, int n, CGWork<T> &w);
 template <typename T>
 int cg_coop_run(hipStream_t s, int n, CGWork<T> &w, T *x, const T *wgt, const T *vnull, int it0, int m, bool beta_zero,
                 CGState *h, int *lost);
