@@ -997,7 +997,8 @@ static int cg_run(hipStream_t s, int n, const int *rp, const int *ci, const T *v
     };
     OASIS_TRY(residual(0, 0));
     if (sr) OASIS_TRY(loop.start(0, false));
-    bool coop = sizeof(T) == 8 && cg_coop_fits(s, n, w);
+    // (the launches to be timed are those of the iterations)
+    bool coop = sizeof(T) == 8 && !time_kernel && cg_coop_fits(s, n, w);
     CGState h;
     ChunkPlan plan(check_every);
     // a cooperative run tests the start residual itself
@@ -1163,7 +1164,7 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
     const CgGrids<BS> g = CgGrids<BS>::template make<C>(n, cap);
     const bool ell = w.cols.any() && w.eval && w.tun.ell();
     // cooperative runs keep the (r, p) pairs of the two-kernel form
-    bool coop = cg_coop_fits(s, n, w);
+    bool coop = !time_kernel && cg_coop_fits(s, n, w);
     bool sr = ell && w.tun.single(4) && !coop;
     SrLoop<float> loop(s, n, w, wgt32, vnull, vscale);
     const int g1 = ell ? launch_p1_ell<float, BS>(s, cap, n, w.cols, w.eval, nullptr, nullptr, nullptr, nullptr, 0,

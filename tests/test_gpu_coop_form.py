@@ -213,3 +213,19 @@ def test_cg_after_a_lost_wait(oa, mesh, precision):
     rc, y, st = _pcg(oa, A, B, prec, flags=1 << 16)
     assert rc == 0 and st.coop_runs == ref.coop_runs and st.coop_lost == (1 if precision == "f64" else ref.coop_runs)
     assert torch.equal(y, first) and st.iters == ref.iters
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_timed_launches_are_the_iterations(oa, precision):
+    """OASIS_KRYLOV_TIME repeats the launch that the iterations made: in FP32
+    the single-reduction pass, in FP64 the product of two kernels.  The
+    iterates are therefore that form's, bit for bit."""
+    mesh = synth.channel(17, 17, 13)
+    say("timed launches", mesh.name, precision)
+    A, H, b = _spd(oa, mesh, 8)
+    prec, form = (oa.F64, oa.CG_FORM_TWO) if precision == "f64" else (oa.F32, oa.CG_FORM_SINGLE)
+    x, y = (torch.zeros(mesh.n_dof, dtype=torch.float64, device="cuda") for _ in range(2))
+    st = oa.pcg(A, T(b), x, rtol=1e-30, maxit=9, precision=prec, time_kernel=True, raise_on=False)
+    oa.pcg(A, T(b), y, rtol=1e-30, maxit=9, precision=prec, cg_form=form, raise_on=False)
+    assert st["status"] == oa.ENOTCONV and st["kernel_count"] == 9 and st["kernel_ms"] > 0 and st["coop_runs"] == 0
+    assert torch.equal(x, y)
