@@ -113,12 +113,14 @@ int oasis_p1_pattern(void *stream, const oasis_mesh *mesh, int32_t *row_ptr,
                      int32_t *col_idx, int64_t col_capacity, int32_t *nnz_out,
                      void *ws, size_t ws_bytes);
 
-/* The column indices (device int32 [nnz]) after oasis_p1_pattern with
- * col_idx = NULL on the same mesh and workspace: it reads the lists that that
- * call left in ws, instead of building them again, and the row_ptr that it
- * wrote.  Synchronises `stream`. */
+/* The column indices (device int32 [col_capacity]) after oasis_p1_pattern
+ * with col_idx = NULL on the same mesh and workspace: it reads the lists that
+ * that call left in ws, instead of building them again, and the row_ptr that
+ * it wrote.  EINVAL, and nothing out of range touched, when ws does not hold
+ * the lists of a mesh of these sizes, when row_ptr is not that mesh's or when
+ * col_capacity is too small.  Synchronises `stream`. */
 int oasis_p1_pattern_columns(void *stream, const oasis_mesh *mesh, const int32_t *row_ptr,
-                             int32_t *col_idx, void *ws, size_t ws_bytes);
+                             int32_t *col_idx, int64_t col_capacity, void *ws, size_t ws_bytes);
 
 /* Greedy first-fit colouring of the cells, visiting cells in decreasing
  * `priority` (device int32 [n_cell], pairwise distinct): every cell takes

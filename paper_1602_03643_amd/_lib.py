@@ -100,7 +100,7 @@ class StepStats(C.Structure):
 _SIGS = {
     "oasis_graph_workspace_size": (i32, [P(Mesh), P(sz)]),
     "oasis_p1_pattern": (i32, [vp, P(Mesh), vp, vp, i64, P(i32), vp, sz]),
-    "oasis_p1_pattern_columns": (i32, [vp, P(Mesh), vp, vp, vp, sz]),
+    "oasis_p1_pattern_columns": (i32, [vp, P(Mesh), vp, vp, i64, vp, sz]),
     "oasis_color_cells": (i32, [vp, P(Mesh), vp, vp, P(i32), vp, sz]),
     "oasis_color_classes": (i32, [vp, i32, vp, i32, P(i32), vp, vp, sz]),
     "oasis_rcm_workspace_size": (i32, [i32, P(sz)]),

@@ -119,7 +119,7 @@ def p1_pattern(mesh: DeviceMesh, stream=None) -> DeviceCSR:
     L.check(lib.oasis_p1_pattern(_stream(stream), C.byref(cm), _p(row_ptr), None, 0, C.byref(nnz),
                                  _p(ws), ws.numel()), "oasis_p1_pattern")
     col_idx = torch.empty(max(nnz.value, 1), dtype=torch.int32, device=mesh.coords.device)[: nnz.value]
-    L.check(lib.oasis_p1_pattern_columns(_stream(stream), C.byref(cm), _p(row_ptr), _p(col_idx),
+    L.check(lib.oasis_p1_pattern_columns(_stream(stream), C.byref(cm), _p(row_ptr), _p(col_idx), nnz.value,
                                          _p(ws), ws.numel()), "oasis_p1_pattern_columns")
     return DeviceCSR(row_ptr, col_idx)
 

@@ -174,6 +174,14 @@ __global__ __launch_bounds__(kBlock) void k_inc_sort(int ndof, const int *__rest
     }
 }
 
+// What a workspace's incidence lists are of, and what the columns' pass wants
+// them to be, with the columns that there is room for.  First in the
+// workspace: whatever else is put there (colour classes) writes over it.
+struct ListsOf {
+    int magic, dim, n_cell, n_dof, room, bad;
+    static constexpr int kMagic = 0x6f617369;
+};
+
 // Distinct neighbour dofs of each dof, ascending; count only when col ==
 // nullptr.  One thread per dof reads its cells once and keeps the distinct
 // dofs in its column of LDS (they are few: 15 on Kuhn-split hexahedra, 7 on
@@ -182,15 +190,33 @@ __global__ __launch_bounds__(kBlock) void k_inc_sort(int ndof, const int *__rest
 // instead.  Bound by the gathers incidence -> vertices -> dofs: selecting
 // for every row read them once per entry, 1.60 ms per pass on 112,000 dofs
 // of a randomly numbered mesh; 0.11 ms this way.
+// The pass that counts (len) says in `lists` what the lists are of; the one
+// that writes the columns (col) does so only if that is what it wants, and
+// only the rows for which rp has the place; else lists->bad is raised.
 constexpr int kPatBlock = 128, kPatCap = 32;
 template <int NV>
 __global__ __launch_bounds__(kPatBlock) void k_row_pattern(int ndof, const int *__restrict__ cells,
                                                            const int *__restrict__ v2d,
                                                            const int *__restrict__ iptr,
                                                            const int *__restrict__ inc,
-                                                           const int *__restrict__ rp, int *len, int *col) {
+                                                           const int *__restrict__ rp, int *len, int *col,
+                                                           ListsOf want, ListsOf *lists) {
     __shared__ int seen[kPatCap][kPatBlock];
     const int t = threadIdx.x;
+    if (!col) {
+        if (blockIdx.x == 0 && t == 0) *lists = want;
+    } else if (lists->magic != want.magic || lists->dim != want.dim || lists->n_cell != want.n_cell ||
+               lists->n_dof != want.n_dof) {
+        if (blockIdx.x == 0 && t == 0) lists->bad = 1;
+        return;
+    }
+    // whether rp has `count` entries for row d, and the columns room for them
+    auto room = [&](long long d, int count) -> bool {
+        const int out = rp[d];
+        if (out >= 0 && count >= 0 && rp[d + 1] - out == count && count <= want.room - out) return true;
+        atomicOr(&lists->bad, 1);
+        return false;
+    };
     for (long long d = blockIdx.x * (long long)kPatBlock + t; d < ndof; d += (long long)gridDim.x * kPatBlock) {
         const int s = iptr[d], e = iptr[d + 1];
         int count = 0;
@@ -215,7 +241,7 @@ __global__ __launch_bounds__(kPatBlock) void k_row_pattern(int ndof, const int *
                 }
         }
         if (count <= kPatCap) {
-            if (col) {
+            if (col && room(d, count)) {
                 const int out = rp[d];
                 for (int k = 0; k < count; ++k) {
                     const int v = seen[k][t];
@@ -225,6 +251,8 @@ __global__ __launch_bounds__(kPatBlock) void k_row_pattern(int ndof, const int *
                 }
             }
         } else {
+            const int most = col ? rp[d + 1] - rp[d] : 0x7fffffff;
+            if (col && !room(d, most)) continue;
             int prev = -1, out = col ? rp[d] : 0;
             count = 0;
             while (true) {
@@ -236,7 +264,10 @@ __global__ __launch_bounds__(kPatBlock) void k_row_pattern(int ndof, const int *
                         if (q > prev && q < best) best = q;
                     }
                 }
-                if (best == 0x7fffffff) break;
+                if (best == 0x7fffffff || count == most) {
+                    if (col && (best != 0x7fffffff || count != most)) atomicOr(&lists->bad, 1);
+                    break;
+                }
                 if (col) col[out++] = best;
                 ++count;
                 prev = best;
@@ -247,6 +278,7 @@ __global__ __launch_bounds__(kPatBlock) void k_row_pattern(int ndof, const int *
 }
 
 struct GraphWs {
+    ListsOf *lists;
     int *iptr, *inc, *cnt, *tmp, *flag;
     int *round_of, *color_cnt, *pos, *more;
     unsigned long long *used;
@@ -255,11 +287,13 @@ struct GraphWs {
 static void carve_graph(Carver &c, const oasis_mesh *m, GraphWs &g) {
     const long long nv = m->dim + 1;
     const int nmax = std::max(m->n_dof, m->n_cell);
+    int *head = c.take<int>(32);
+    g.lists = reinterpret_cast<ListsOf *>(head);
+    g.flag = head ? head + 16 : nullptr;
     g.iptr = c.take<int>((size_t)m->n_dof + 1);
     g.inc = c.take<int>((size_t)m->n_cell * nv);
     g.cnt = c.take<int>((size_t)nmax + 1);
     g.tmp = c.take<int>(scan_ws_ints(nmax) + 16);
-    g.flag = c.take<int>(16);
     g.round_of = c.take<int>((size_t)m->n_cell);
     g.color_cnt = c.take<int>(256);
     g.pos = c.take<int>((size_t)nmax + 1);
@@ -280,14 +314,17 @@ static int build_incidence(hipStream_t s, const oasis_mesh *m, GraphWs &g, bool 
     const int nv = m->dim + 1;
     const int gc = grid_for(m->n_cell, kBlock, 8192);
     OASIS_TRY(fill_i(s, m->n_dof + 1, g.cnt, 0));
-    OASIS_TRY(fill_i(s, 16, g.flag, 0));
+    if (g.lists)   // (and the flags behind it)
+        OASIS_TRY(fill_i(s, 32, &g.lists->magic, 0));
+    else
+        OASIS_TRY(fill_i(s, 16, g.flag, 0));
     hipLaunchKernelGGL(k_inc_count, dim3(gc), dim3(kBlock), 0, s, m->n_cell, nv, m->n_vert, m->n_dof,
                        m->cells, m->vert2dof, g.cnt, g.flag);
     OASIS_TRY_LAUNCH();
     int err0 = 0;
     OASIS_TRY_HIP(hipMemcpyAsync(&err0, g.flag, sizeof(int), hipMemcpyDeviceToHost, s));
     OASIS_TRY_HIP(hipStreamSynchronize(s));
-    if (err0 & 2) return OASIS_EINVAL;
+    if (err0) return err0 & 2 ? OASIS_EINVAL : OASIS_EUNSUPPORTED;
     OASIS_TRY(exclusive_scan(s, m->n_dof, g.cnt, g.iptr, g.tmp));
     OASIS_TRY(fill_i(s, m->n_dof + 1, g.cnt, 0));
     hipLaunchKernelGGL(k_inc_fill, dim3(gc), dim3(kBlock), 0, s, m->n_cell, nv, m->cells,
@@ -298,10 +335,7 @@ static int build_incidence(hipStream_t s, const oasis_mesh *m, GraphWs &g, bool 
                            g.inc);
         OASIS_TRY_LAUNCH();
     }
-    int err = 0;
-    OASIS_TRY_HIP(hipMemcpyAsync(&err, g.flag, sizeof(int), hipMemcpyDeviceToHost, s));
-    OASIS_TRY_HIP(hipStreamSynchronize(s));
-    return err ? OASIS_EUNSUPPORTED : OASIS_OK;
+    return OASIS_OK;
 }
 
 // Incidence lists for an external user (the IPCS handle): iptr [n_dof+1],
@@ -782,18 +816,34 @@ extern "C" int oasis_graph_workspace_size(const oasis_mesh *mesh, size_t *bytes)
     return OASIS_OK;
 }
 
-// row lengths (len), or with the row offsets rp the columns, from the
-// incidence lists in g
-static int pattern_rows(hipStream_t s, const oasis_mesh *mesh, const GraphWs &g, const int *rp, int *len, int *col) {
+// row lengths (len), or with the row offsets rp the columns into room for
+// col_capacity of them, from the incidence lists in g
+static int pattern_rows(hipStream_t s, const oasis_mesh *mesh, const GraphWs &g, const int *rp, int *len, int *col,
+                        int64_t col_capacity) {
     const int gd = grid_for(mesh->n_dof, kPatBlock, 1 << 20);
+    const ListsOf want{ListsOf::kMagic, mesh->dim, mesh->n_cell, mesh->n_dof,
+                       static_cast<int>(std::min<int64_t>(col_capacity, 0x7fffffff)), 0};
     if (mesh->dim == 3)
         hipLaunchKernelGGL(k_row_pattern<4>, dim3(gd), dim3(kPatBlock), 0, s, mesh->n_dof, mesh->cells,
-                           mesh->vert2dof, g.iptr, g.inc, rp, len, col);
+                           mesh->vert2dof, g.iptr, g.inc, rp, len, col, want, g.lists);
     else
         hipLaunchKernelGGL(k_row_pattern<3>, dim3(gd), dim3(kPatBlock), 0, s, mesh->n_dof, mesh->cells,
-                           mesh->vert2dof, g.iptr, g.inc, rp, len, col);
+                           mesh->vert2dof, g.iptr, g.inc, rp, len, col, want, g.lists);
     OASIS_TRY_LAUNCH();
     return OASIS_OK;
+}
+
+// the columns; EINVAL when the lists, row_ptr or the room do not allow them
+static int pattern_columns(hipStream_t s, const oasis_mesh *mesh, const GraphWs &g, const int *row_ptr, int *col_idx,
+                           int64_t col_capacity) {
+    OASIS_TRY(pattern_rows(s, mesh, g, row_ptr, nullptr, col_idx, col_capacity));
+    int bad = 0;
+    OASIS_TRY_HIP(hipMemcpyAsync(&bad, &g.lists->bad, sizeof(int), hipMemcpyDeviceToHost, s));
+    OASIS_TRY_HIP(hipStreamSynchronize(s));
+    if (!bad) return OASIS_OK;
+    OASIS_TRY(fill_i(s, 1, &g.lists->bad, 0));   // the lists are as they were
+    OASIS_TRY_HIP(hipStreamSynchronize(s));
+    return OASIS_EINVAL;
 }
 
 extern "C" int oasis_p1_pattern(void *stream, const oasis_mesh *mesh, int32_t *row_ptr,
@@ -807,7 +857,7 @@ extern "C" int oasis_p1_pattern(void *stream, const oasis_mesh *mesh, int32_t *r
     carve_graph(c, mesh, g);
     if (!c.ok) return OASIS_EWORKSPACE;
     OASIS_TRY(build_incidence(s, mesh, g, false));
-    OASIS_TRY(pattern_rows(s, mesh, g, nullptr, g.cnt, nullptr));
+    OASIS_TRY(pattern_rows(s, mesh, g, nullptr, g.cnt, nullptr, 0));
     OASIS_TRY(exclusive_scan(s, mesh->n_dof, g.cnt, row_ptr, g.tmp));
     int nnz = 0;
     OASIS_TRY_HIP(hipMemcpyAsync(&nnz, row_ptr + mesh->n_dof, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -815,23 +865,19 @@ extern "C" int oasis_p1_pattern(void *stream, const oasis_mesh *mesh, int32_t *r
     *nnz_out = nnz;
     if (!col_idx) return OASIS_OK;
     if (col_capacity < nnz) return OASIS_EINVAL;
-    OASIS_TRY(pattern_rows(s, mesh, g, row_ptr, nullptr, col_idx));
-    OASIS_TRY_HIP(hipStreamSynchronize(s));
-    return OASIS_OK;
+    return pattern_columns(s, mesh, g, row_ptr, col_idx, col_capacity);
 }
 
 extern "C" int oasis_p1_pattern_columns(void *stream, const oasis_mesh *mesh, const int32_t *row_ptr,
-                                        int32_t *col_idx, void *ws, size_t ws_bytes) {
+                                        int32_t *col_idx, int64_t col_capacity, void *ws, size_t ws_bytes) {
     OASIS_TRY(check_mesh(mesh));
-    if (!row_ptr || !col_idx || !ws) return OASIS_EINVAL;
+    if (!row_ptr || !col_idx || col_capacity < 0 || !ws) return OASIS_EINVAL;
     hipStream_t s = as_stream(stream);
     Carver c(ws, ws_bytes);
     GraphWs g;
     carve_graph(c, mesh, g);
     if (!c.ok) return OASIS_EWORKSPACE;
-    OASIS_TRY(pattern_rows(s, mesh, g, row_ptr, nullptr, col_idx));
-    OASIS_TRY_HIP(hipStreamSynchronize(s));
-    return OASIS_OK;
+    return pattern_columns(s, mesh, g, row_ptr, col_idx, col_capacity);
 }
 
 extern "C" int oasis_color_cells(void *stream, const oasis_mesh *mesh, const int32_t *priority,
