@@ -223,8 +223,9 @@ typedef struct {
     oasis_tuning tuning;
 } oasis_krylov_opts;
 
-/* Kernel timing.  oasis_pcg: when the solve stops at maxit, its last
- * product launch is repeated maxit times back to back between two HIP
+/* Kernel timing.  oasis_pcg: when the solve stops at maxit, the product
+ * launch of its next iteration (as launched iterations make it, also after
+ * cooperative runs) is repeated maxit times back to back between two HIP
  * events: in F32 mode the whole single-reduction iteration (its iterate
  * update goes to scratch memory), in F64 mode the direction+product kernel.
  * kernel_ms is their total and kernel_count = maxit (0 when the solve

@@ -997,8 +997,7 @@ static int cg_run(hipStream_t s, int n, const int *rp, const int *ci, const T *v
     };
     OASIS_TRY(residual(0, 0));
     if (sr) OASIS_TRY(loop.start(0, false));
-    // (the launches to be timed are those of the iterations)
-    bool coop = sizeof(T) == 8 && !time_kernel && cg_coop_fits(s, n, w);
+    bool coop = sizeof(T) == 8 && cg_coop_fits(s, n, w);
     CGState h;
     ChunkPlan plan(check_every);
     // a cooperative run tests the start residual itself
@@ -1164,7 +1163,7 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
     const CgGrids<BS> g = CgGrids<BS>::template make<C>(n, cap);
     const bool ell = w.cols.any() && w.eval && w.tun.ell();
     // cooperative runs keep the (r, p) pairs of the two-kernel form
-    bool coop = !time_kernel && cg_coop_fits(s, n, w);
+    bool coop = cg_coop_fits(s, n, w);
     bool sr = ell && w.tun.single(4) && !coop;
     SrLoop<float> loop(s, n, w, wgt32, vnull, vscale);
     const int g1 = ell ? launch_p1_ell<float, BS>(s, cap, n, w.cols, w.eval, nullptr, nullptr, nullptr, nullptr, 0,
@@ -1308,11 +1307,15 @@ static int cg_mixed_run(hipStream_t s, int n, const int *rp, const int *ci, cons
         if (at >= maxit) {
             out.iters = at;
             out.status = rc = OASIS_ENOTCONV;
-            if (time_kernel && sr) {
+            if (time_kernel && (sr || coop)) {
                 // repeat iteration `at` from the replaced residual; x_lo is
-                // left alone (the repeats advance a scratch copy)
-                OASIS_TRY(cast(at, true));
-                OASIS_TRY(time_product(s, maxit, [&] { loop.iterate(at, 0, w.q); }, out));
+                // left alone (the repeats advance a scratch copy).  After
+                // cooperative runs the record holds (r, p) pairs, and the
+                // iteration starts a direction.
+                const bool keep = sr;
+                sr = true;
+                OASIS_TRY(cast(at, keep));
+                OASIS_TRY(time_product(s, maxit, [&] { loop.iterate(at, keep ? 0 : 1, w.q); }, out));
             } else if (time_kernel) {
                 // repeat iteration `at` (FP32 pair in place, k_cg_init's partials)
                 OASIS_TRY(time_product(

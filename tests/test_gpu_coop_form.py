@@ -216,16 +216,31 @@ def test_cg_after_a_lost_wait(oa, mesh, precision):
 
 
 @pytest.mark.parametrize("precision", ["f64", "f32"])
-def test_timed_launches_are_the_iterations(oa, precision):
-    """OASIS_KRYLOV_TIME repeats the launch that the iterations made: in FP32
-    the single-reduction pass, in FP64 the product of two kernels.  The
-    iterates are therefore that form's, bit for bit."""
-    mesh = synth.channel(17, 17, 13)
+def test_timed_launches_are_those_of_the_header(oa, precision):
+    """OASIS_KRYLOV_TIME repeats the single-reduction pass in FP32 and the
+    product of the two-kernel form in FP64, also after cooperative runs (of
+    which it leaves the iterates alone): the times are those of the calls that
+    ask for that form, within a fifth.  The other form's launch takes under
+    three quarters or over five quarters of it."""
+    mesh = synth.channel(65, 64, 65)
     say("timed launches", mesh.name, precision)
     A, H, b = _spd(oa, mesh, 8)
-    prec, form = (oa.F64, oa.CG_FORM_TWO) if precision == "f64" else (oa.F32, oa.CG_FORM_SINGLE)
-    x, y = (torch.zeros(mesh.n_dof, dtype=torch.float64, device="cuda") for _ in range(2))
-    st = oa.pcg(A, T(b), x, rtol=1e-30, maxit=9, precision=prec, time_kernel=True, raise_on=False)
-    oa.pcg(A, T(b), y, rtol=1e-30, maxit=9, precision=prec, cg_form=form, raise_on=False)
-    assert st["status"] == oa.ENOTCONV and st["kernel_count"] == 9 and st["kernel_ms"] > 0 and st["coop_runs"] == 0
-    assert torch.equal(x, y)
+    b = T(b)
+    prec = oa.F64 if precision == "f64" else oa.F32
+
+    def timed(**kw):
+        x, best = torch.zeros_like(b), []
+        for _ in range(5):
+            x.zero_()
+            st = oa.pcg(A, b, x, rtol=1e-30, maxit=200, precision=prec, time_kernel=True, raise_on=False, **kw)
+            assert st["status"] == oa.ENOTCONV and st["kernel_count"] == 200
+            best.append(st["kernel_ms"] / 200)
+        return sorted(best)[2], st["coop_runs"], x
+
+    us, runs, x = timed()
+    two, single = timed(cg_form=oa.CG_FORM_TWO), timed(cg_form=oa.CG_FORM_SINGLE)
+    say("us: here %.2f, two %.2f, single %.2f" % (1e3 * us, 1e3 * two[0], 1e3 * single[0]))
+    want, other = (two[0], single[0]) if precision == "f64" else (single[0], two[0])
+    assert runs > 0 and two[1] == single[1] == 0
+    assert not 0.75 <= other / want <= 1.25
+    assert abs(us / want - 1) <= 0.2
