@@ -73,24 +73,28 @@ __global__ __launch_bounds__(1024) void k_scan_sums(int ntiles, int *sums) {
     if (threadIdx.x == 0) sums[ntiles] = carry;
 }
 
-__global__ __launch_bounds__(kBlock) void k_scan_add(int n, int *out, const int *sums) {
+__global__ __launch_bounds__(kBlock) void k_scan_add(int n, int *out, const int *sums, int *total) {
     const int i = blockIdx.x * kScanTile;
     const int off = sums[blockIdx.x];
     for (int k = threadIdx.x; k < kScanTile; k += blockDim.x)
         if (i + k < n) out[i + k] += off;
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = sums[gridDim.x];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        out[n] = sums[gridDim.x];
+        if (total) *total = sums[gridDim.x];
+    }
 }
 
 static size_t scan_ws_ints(int n) { return (size_t)(n + kScanTile - 1) / kScanTile + 1; }
 
-// out has n+1 entries; in may equal out only if n == 0
-static int exclusive_scan(hipStream_t s, int n, const int *in, int *out, int *tmp) {
+// out has n+1 entries; in may equal out only if n == 0; total (nullable)
+// receives out[n] too
+static int exclusive_scan(hipStream_t s, int n, const int *in, int *out, int *tmp, int *total = nullptr) {
     const int tiles = std::max(1, (n + kScanTile - 1) / kScanTile);
     hipLaunchKernelGGL(k_scan_tiles, dim3(tiles), dim3(kBlock), 0, s, n, in, out, tmp);
     OASIS_TRY_LAUNCH();
     hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, tiles, tmp);
     OASIS_TRY_LAUNCH();
-    hipLaunchKernelGGL(k_scan_add, dim3(tiles), dim3(kBlock), 0, s, n, out, tmp);
+    hipLaunchKernelGGL(k_scan_add, dim3(tiles), dim3(kBlock), 0, s, n, out, tmp, total);
     OASIS_TRY_LAUNCH();
     return OASIS_OK;
 }
@@ -146,7 +150,8 @@ __global__ __launch_bounds__(kBlock) void k_inc_count(int ncell, int nv, int nve
 __global__ __launch_bounds__(kBlock) void k_inc_fill(int ncell, int nv, const int *__restrict__ cells,
                                                      const int *__restrict__ v2d,
                                                      const int *__restrict__ ptr, int *fillc,
-                                                     int *inc) {
+                                                     int *inc, const int *err) {
+    if (*err) return;   // no index of a rejected mesh is followed
     for (long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x; c < ncell;
          c += (long long)gridDim.x * blockDim.x) {
         for (int a = 0; a < nv; ++a) {
@@ -200,10 +205,11 @@ __global__ __launch_bounds__(kPatBlock) void k_row_pattern(int ndof, const int *
                                                            const int *__restrict__ iptr,
                                                            const int *__restrict__ inc,
                                                            const int *__restrict__ rp, int *len, int *col,
-                                                           ListsOf want, ListsOf *lists) {
+                                                           ListsOf want, ListsOf *lists, const int *err) {
     __shared__ int seen[kPatCap][kPatBlock];
     const int t = threadIdx.x;
     if (!col) {
+        if (*err) return;
         if (blockIdx.x == 0 && t == 0) *lists = want;
     } else if (lists->magic != want.magic || lists->dim != want.dim || lists->n_cell != want.n_cell ||
                lists->n_dof != want.n_dof) {
@@ -308,9 +314,15 @@ static int check_mesh(const oasis_mesh *m) {
     return OASIS_OK;
 }
 
+// what g.flag[0] says of a mesh (k_inc_count)
+static int mesh_status(int err) {
+    return err == 0 ? OASIS_OK : err & 2 ? OASIS_EINVAL : OASIS_EUNSUPPORTED;
+}
+
 // sorted: every list ascending (the pattern and the colouring do not depend
-// on the order within a list)
-static int build_incidence(hipStream_t s, const oasis_mesh *m, GraphWs &g, bool sorted) {
+// on the order within a list).  Not `look`: the caller reads g.flag itself,
+// and until then no kernel may follow the lists where it is not zero.
+static int build_incidence(hipStream_t s, const oasis_mesh *m, GraphWs &g, bool sorted, bool look = true) {
     const int nv = m->dim + 1;
     const int gc = grid_for(m->n_cell, kBlock, 8192);
     OASIS_TRY(fill_i(s, m->n_dof + 1, g.cnt, 0));
@@ -321,14 +333,16 @@ static int build_incidence(hipStream_t s, const oasis_mesh *m, GraphWs &g, bool 
     hipLaunchKernelGGL(k_inc_count, dim3(gc), dim3(kBlock), 0, s, m->n_cell, nv, m->n_vert, m->n_dof,
                        m->cells, m->vert2dof, g.cnt, g.flag);
     OASIS_TRY_LAUNCH();
-    int err0 = 0;
-    OASIS_TRY_HIP(hipMemcpyAsync(&err0, g.flag, sizeof(int), hipMemcpyDeviceToHost, s));
-    OASIS_TRY_HIP(hipStreamSynchronize(s));
-    if (err0) return err0 & 2 ? OASIS_EINVAL : OASIS_EUNSUPPORTED;
+    if (look) {
+        int err = 0;
+        OASIS_TRY_HIP(hipMemcpyAsync(&err, g.flag, sizeof(int), hipMemcpyDeviceToHost, s));
+        OASIS_TRY_HIP(hipStreamSynchronize(s));
+        OASIS_TRY(mesh_status(err));
+    }
     OASIS_TRY(exclusive_scan(s, m->n_dof, g.cnt, g.iptr, g.tmp));
     OASIS_TRY(fill_i(s, m->n_dof + 1, g.cnt, 0));
     hipLaunchKernelGGL(k_inc_fill, dim3(gc), dim3(kBlock), 0, s, m->n_cell, nv, m->cells,
-                       m->vert2dof, g.iptr, g.cnt, g.inc);
+                       m->vert2dof, g.iptr, g.cnt, g.inc, g.flag);
     OASIS_TRY_LAUNCH();
     if (sorted) {
         hipLaunchKernelGGL(k_inc_sort, dim3(grid_for(m->n_dof, kBlock, 8192)), dim3(kBlock), 0, s, m->n_dof, g.iptr,
@@ -825,10 +839,10 @@ static int pattern_rows(hipStream_t s, const oasis_mesh *mesh, const GraphWs &g,
                        static_cast<int>(std::min<int64_t>(col_capacity, 0x7fffffff)), 0};
     if (mesh->dim == 3)
         hipLaunchKernelGGL(k_row_pattern<4>, dim3(gd), dim3(kPatBlock), 0, s, mesh->n_dof, mesh->cells,
-                           mesh->vert2dof, g.iptr, g.inc, rp, len, col, want, g.lists);
+                           mesh->vert2dof, g.iptr, g.inc, rp, len, col, want, g.lists, g.flag);
     else
         hipLaunchKernelGGL(k_row_pattern<3>, dim3(gd), dim3(kPatBlock), 0, s, mesh->n_dof, mesh->cells,
-                           mesh->vert2dof, g.iptr, g.inc, rp, len, col, want, g.lists);
+                           mesh->vert2dof, g.iptr, g.inc, rp, len, col, want, g.lists, g.flag);
     OASIS_TRY_LAUNCH();
     return OASIS_OK;
 }
@@ -856,13 +870,14 @@ extern "C" int oasis_p1_pattern(void *stream, const oasis_mesh *mesh, int32_t *r
     GraphWs g;
     carve_graph(c, mesh, g);
     if (!c.ok) return OASIS_EWORKSPACE;
-    OASIS_TRY(build_incidence(s, mesh, g, false));
+    OASIS_TRY(build_incidence(s, mesh, g, false, false));
     OASIS_TRY(pattern_rows(s, mesh, g, nullptr, g.cnt, nullptr, 0));
-    OASIS_TRY(exclusive_scan(s, mesh->n_dof, g.cnt, row_ptr, g.tmp));
-    int nnz = 0;
-    OASIS_TRY_HIP(hipMemcpyAsync(&nnz, row_ptr + mesh->n_dof, sizeof(int), hipMemcpyDeviceToHost, s));
+    OASIS_TRY(exclusive_scan(s, mesh->n_dof, g.cnt, row_ptr, g.tmp, g.flag + 1));
+    int got[2];                               // what was wrong, the entries
+    OASIS_TRY_HIP(hipMemcpyAsync(got, g.flag, sizeof(got), hipMemcpyDeviceToHost, s));
     OASIS_TRY_HIP(hipStreamSynchronize(s));
-    *nnz_out = nnz;
+    OASIS_TRY(mesh_status(got[0]));
+    const int nnz = *nnz_out = got[1];
     if (!col_idx) return OASIS_OK;
     if (col_capacity < nnz) return OASIS_EINVAL;
     return pattern_columns(s, mesh, g, row_ptr, col_idx, col_capacity);
