@@ -129,6 +129,8 @@ HostCsr matmul(const HostCsr &A, const HostCsr &B) {
     C.m = B.m;
     C.rp.reserve(A.n + 1);
     C.rp.push_back(0);
+    C.ci.reserve(A.ci.size());
+    C.v.reserve(A.ci.size());
     Spa spa(B.m);
     for (int i = 0; i < A.n; ++i) {
         for (int k = A.rp[i]; k < A.rp[i + 1]; ++k) {
@@ -209,7 +211,10 @@ HostCsr filtered(const HostCsr &A, const std::vector<char> &S, const std::vector
     HostCsr F;
     F.n = A.n;
     F.m = A.m;
+    F.rp.reserve(A.n + 1);
     F.rp.push_back(0);
+    F.ci.reserve(A.ci.size());
+    F.v.reserve(A.ci.size());
     for (int i = 0; i < A.n; ++i) {
         double lump = 0.0;
         for (int k = A.rp[i]; k < A.rp[i + 1]; ++k) {
@@ -241,40 +246,53 @@ HostCsr filtered(const HostCsr &A, const std::vector<char> &S, const std::vector
 //   b_c = R (b - A W b),
 // the prolongation and the post-smoothing
 //   t = W b + P x_c,  x = t + W (b - A t) = (2 W - W A W) b + (P - W A P) x_c.
+// A is symmetric, so R - R A W is the transpose of P - W A P, and both come
+// from A P, which the coarse matrix has needed already, by merging sorted rows
+// (with accumulated rows, and `down` as a product of its own, the set-up on
+// 200,000 rows took 227 ms; 194 this way, the halves included).
 void cycle_halves(HostLevel &lv, const std::vector<double> &d, const HostCsr &AP) {
-    const HostCsr &A = lv.A;
+    const HostCsr &A = lv.A, &P = lv.P;
     std::vector<double> w(A.n);
     for (int i = 0; i < A.n; ++i) w[i] = lv.omega / d[i];
-    {
-        HostCsr &D = lv.down;
-        D.n = lv.R.n;
-        D.m = A.n;
-        D.rp.push_back(0);
-        Spa spa(A.n);
-        for (int c = 0; c < lv.R.n; ++c) {
-            for (int k = lv.R.rp[c]; k < lv.R.rp[c + 1]; ++k) {
-                const int i = lv.R.ci[k];
-                const double r = lv.R.v[k];
-                spa.add(c, i, r);
-                for (int q = A.rp[i]; q < A.rp[i + 1]; ++q) spa.add(c, A.ci[q], -r * A.v[q] * w[A.ci[q]]);
-            }
-            spa.flush(D);
-        }
-    }
+    HostCsr D;                           // P - W A P
+    D.n = A.n;
+    D.m = P.m;
+    D.rp.reserve(A.n + 1);
+    D.rp.push_back(0);
+    D.ci.reserve(AP.ci.size());
+    D.v.reserve(AP.ci.size());
     HostCsr &U = lv.up;
     U.n = A.n;
-    U.m = A.n + lv.P.m;
+    U.m = A.n + P.m;
+    U.rp.reserve(A.n + 1);
     U.rp.push_back(0);
     U.ci.reserve(A.ci.size() + AP.ci.size());
     U.v.reserve(A.ci.size() + AP.ci.size());
-    Spa spa(U.m);
+    auto put = [](HostCsr &M, int c, double v) {
+        if (v == 0.0) return;
+        M.ci.push_back(c);
+        M.v.push_back(v);
+    };
     for (int i = 0; i < A.n; ++i) {
-        spa.add(i, i, 2.0 * w[i]);
-        for (int q = A.rp[i]; q < A.rp[i + 1]; ++q) spa.add(i, A.ci[q], -w[i] * A.v[q] * w[A.ci[q]]);
-        for (int k = lv.P.rp[i]; k < lv.P.rp[i + 1]; ++k) spa.add(i, A.n + lv.P.ci[k], lv.P.v[k]);
-        for (int k = AP.rp[i]; k < AP.rp[i + 1]; ++k) spa.add(i, A.n + AP.ci[k], -w[i] * AP.v[k]);
-        spa.flush(U);
+        for (int q = A.rp[i]; q < A.rp[i + 1]; ++q) {
+            const int j = A.ci[q];
+            const double v = -w[i] * A.v[q] * w[j];
+            put(U, j, j == i ? 2.0 * w[i] + v : v);
+        }
+        int k = P.rp[i], q = AP.rp[i];
+        const int ke = P.rp[i + 1], qe = AP.rp[i + 1];
+        while (k < ke || q < qe) {
+            const int cp = k < ke ? P.ci[k] : P.m, ca = q < qe ? AP.ci[q] : P.m, c = std::min(cp, ca);
+            double v = 0.0;
+            if (cp == c) v = P.v[k++];
+            if (ca == c) v += -w[i] * AP.v[q++];
+            put(D, c, v);
+            put(U, A.n + c, v);
+        }
+        D.rp.push_back(static_cast<int>(D.ci.size()));
+        U.rp.push_back(static_cast<int>(U.ci.size()));
     }
+    lv.down = transpose(D);
 }
 
 // Whether cycle_halves is faster than smoothing, restricting, prolonging and
@@ -368,7 +386,10 @@ int amg_build(const HostCsr &A0, const std::vector<double> &B0, const AmgHostPar
         HostCsr P;
         P.n = lv.A.n;
         P.m = na;
+        P.rp.reserve(lv.A.n + 1);
         P.rp.push_back(0);
+        P.ci.reserve(FP.ci.size());
+        P.v.reserve(FP.ci.size());
         for (int i = 0; i < lv.A.n; ++i) {
             const double dinv = 1.0 / dF[i];
             bool has_own = false;
@@ -394,14 +415,14 @@ int amg_build(const HostCsr &A0, const std::vector<double> &B0, const AmgHostPar
         }
         // Galerkin coarse matrix
         const HostCsr AP = matmul(lv.A, P);
-        const HostCsr R = transpose(P);
+        HostCsr R = transpose(P);
         HostLevel next;
         next.A = matmul(R, AP);
         next.B = nrm;
         lv.agg = std::move(agg);
         lv.n_agg = na;
         lv.P = std::move(P);
-        lv.R = R;
+        lv.R = std::move(R);
         if (l > 0 && (levels[l - 1].up.n || multiply_out(lv, AP))) cycle_halves(lv, d, AP);
         levels.push_back(std::move(next));
     }
