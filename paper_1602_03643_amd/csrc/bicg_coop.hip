@@ -287,7 +287,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
     auto get = [&](int i) { return scal[wv][i]; };
     auto put = [&](int i, double value) {         // value of lane k in entry i + k
         if (wl < NR) scal[wv][i + wl] = value;
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
     };
     // the right-hand sides for which a condition holds in their lane
     auto those = [&](bool c) { return static_cast<int>(__ballot(wl < NR && c)); };
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
         restarted |= 1 << k;
         again[k] += 1;
         if (wl == 0) scal[wv][kRho + k] = scal[wv][kAlpha + k] = scal[wv][kOmega + k] = 1.0;
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         u[k] = T(0);
         set_h(k, r[k]);
         return true;

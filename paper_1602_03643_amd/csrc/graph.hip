@@ -438,7 +438,7 @@ __global__ __launch_bounds__(kBlock) void k_color_sort(int ndof, const int *__re
             cell[wv][i] = c;
             key[wv][i] = pri[c];
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         for (int i = lane; i < n; i += kWave) {
             const int c = cell[wv][i], p = key[wv][i];
             int r = 0, same = 0;
@@ -453,7 +453,7 @@ __global__ __launch_bounds__(kBlock) void k_color_sort(int ndof, const int *__re
             if (tie) atomicOr(bad, 2);
             if (r == 0 && atomicAdd(&turns[c], same) + same == NV) ready.push(c);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
     }
     ready.flush();
 }

@@ -102,6 +102,16 @@ inline int grid_for(long long work, int per_block, int cap = kMaxPartials) {
     return static_cast<int>(g);
 }
 
+// Between LDS writes of a wave's lanes and reads of them by its other lanes.
+// The wave's LDS accesses are made in order, so this costs nothing; it keeps
+// the compiler from moving a read of another type, which it may take for one of
+// other memory, above the writes.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // ---------------------------------------------------------------------------
 // device reductions (fixed order => bitwise deterministic)
 

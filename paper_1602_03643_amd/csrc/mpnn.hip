@@ -467,7 +467,7 @@ __global__ __launch_bounds__(kBlock) void k_mp_layer(int n, int l, const int *__
             }
         }
         if (STORE || !LAST) {
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();
             const int ln = threadIdx.x >> 2, f0 = (threadIdx.x & 3) * 8;   // a row of this wave
             const long long i = base + ln;
             if (i < n) {
@@ -704,7 +704,7 @@ __global__ __launch_bounds__(kGzBlock) void k_mp_bwd_gz(int n, int l, const doub
             gc = mfma16(af, one, gc);
         }
         // a wave's own 16 rows of Ty, in 16-byte pieces (thread t's row is its wave's)
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         if (base + ln < n)
             *reinterpret_cast<uint4 *>(Y + (base + ln) * kHid + f0) = *reinterpret_cast<const uint4 *>(&Ty[ln][f0]);
     }
@@ -788,7 +788,7 @@ __global__ __launch_bounds__(kBlock) void k_mp_bwd_h(int n, int l, const int *__
                 sum = acc[q] + sum;
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         if (i < n) {   // a row of this wave
             const float4 s0 = *reinterpret_cast<const float4 *>(&Tagg[ln][f0]);
             const float4 s1 = *reinterpret_cast<const float4 *>(&Tagg[ln][f0 + 4]);
