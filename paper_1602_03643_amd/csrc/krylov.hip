@@ -764,7 +764,11 @@ __global__ __launch_bounds__(kDictBlock) void k_dict_insert(int n, int max_pat, 
         }
         int slot = static_cast<int>(h & (M - 1));
         bool open = i < n;
-        while (__syncthreads_or(open ? 1 : 0)) {
+        for (int tried = 0; __syncthreads_or(open ? 1 : 0); ++tried) {
+            if (tried == M) {   // a row met every slot: more lists than slots
+                if (threadIdx.x == 0) atomicOr(&t->over, 1);
+                return;
+            }
             if (open && rep[slot] == -1) atomicCAS(&rep[slot], -1, mine);
             __syncthreads();
             if (open && rep[slot] == mine) {

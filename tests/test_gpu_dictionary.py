@@ -44,3 +44,17 @@ def test_dictionary_size(oa, mesh):
     want = _lists(pat)
     assert out["rc"] == 0
     assert out["ell_patterns"] == (want if want <= min(4096, mesh.n_dof // 8) else -1)
+
+
+def test_far_more_lists_than_slots(oa):
+    """Nearly every one of 49,920 rows has a list of its own, and the table has
+    8192 slots: the search gives up, and the per-entry offsets stay."""
+    mesh = synth.permute_mesh(synth.channel(41, 39, 33), 3)[0]
+    say("dictionary", mesh.name)
+    dm, pat, _ = device_mesh(mesh)
+    assert _lists(pat) > 40000
+    A = pat.with_values(oa.assemble_p1(dm, pat, oa.FORM_STIFF, base=oa.assemble_p1(dm, pat, oa.FORM_MASS, alpha=10.0)))
+    b = T(np.random.default_rng(1).normal(size=mesh.n_dof))
+    for _ in range(3):
+        out = oa.pcg(A, b, torch.zeros_like(b), rtol=1e-3)
+        assert out["rc"] == 0 and out["ell_patterns"] == -1
