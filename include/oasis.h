@@ -167,9 +167,10 @@ int oasis_assemble_p1(void *stream, const oasis_mesh *mesh, int32_t form,
                       oasis_csr *out);
 
 /* The same assembly for callers with scratch memory (at least
- * oasis_assemble_p1_workspace_size bytes): the colours place every dof's
- * cells in a table, and each row adds its own entries.  At most 128 colours
- * (EUNSUPPORTED). */
+ * oasis_assemble_p1_workspace_size bytes: about 4 bytes a colour and dof, 16
+ * a vertex and dimension, one a cell): the colours place every dof's cells in
+ * a table, and each row adds its own entries, of a cell that color_cells names
+ * twice once.  At most 128 colours (EUNSUPPORTED). */
 int oasis_assemble_p1_workspace_size(const oasis_mesh *mesh, size_t *bytes);
 int oasis_assemble_p1_ws(void *stream, const oasis_mesh *mesh, int32_t form,
                          const double *const *uab, double alpha, const oasis_csr *base,

@@ -117,7 +117,8 @@ int assemble_colored(hipStream_t s, const oasis_mesh *m, const int *rp, const in
 // 97x97x73 channel 40 launches of 83 us (3.4 ms) moved some 8 GB; the table
 // takes 0.32 ms here and the rows 0.43.
 
-// colour of every cell; classes: the host's class starts, by value
+// colour of every cell that a class lists; classes: the host's class starts,
+// by value
 struct ClassPtr {
     int n, start[129];
 };
@@ -135,9 +136,13 @@ __global__ __launch_bounds__(kBlock) void k_cell_colors(int ncell, ClassPtr cp, 
             else
                 hi = mid - 1;
         }
-        color[clist[q]] = static_cast<unsigned char>(lo);
+        const int c = clist[q];
+        if (c >= 0 && c < ncell) color[c] = static_cast<unsigned char>(lo);
     }
 }
+
+// a cell that no class lists: it has no slots, and nothing is added for it
+constexpr int kNoColor = 255;
 
 template <int NV>
 __global__ __launch_bounds__(kBlock) void k_slot_fill(int ncell, int w, const int *__restrict__ cells,
@@ -146,6 +151,7 @@ __global__ __launch_bounds__(kBlock) void k_slot_fill(int ncell, int w, const in
                                                       int *__restrict__ slots) {
     for (int c = blockIdx.x * kBlock + threadIdx.x; c < ncell; c += gridDim.x * kBlock) {
         const int k = color[c];
+        if (k == kNoColor) continue;
 #pragma unroll
         for (int a = 0; a < NV; ++a) {
             const int d = v2d[cells[(long long)c * NV + a]];
@@ -182,9 +188,13 @@ __global__ __launch_bounds__(kBlock) void k_slot_pack(int n, int w, int *slots, 
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_slot_clear(long long m, int4 *slots) {
-    for (long long i = blockIdx.x * (long long)kBlock + threadIdx.x; i < m; i += (long long)gridDim.x * kBlock)
-        slots[i] = int4{-1, -1, -1, -1};
+// empty slots, and no cell with a colour (words of four: the array's end is
+// padded)
+__global__ __launch_bounds__(kBlock) void k_slot_clear(long long m, int4 *slots, int words, unsigned *color) {
+    static_assert(kNoColor == 0xff, "all ones");
+    const long long i0 = blockIdx.x * (long long)kBlock + threadIdx.x, step = (long long)gridDim.x * kBlock;
+    for (long long i = i0; i < m; i += step) slots[i] = int4{-1, -1, -1, -1};
+    for (long long i = i0; i < words; i += step) color[i] = ~0u;
 }
 
 // What the convection form needs of a vertex besides its dof, coordinates and
@@ -511,10 +521,10 @@ int assemble_rows(hipStream_t s, const oasis_mesh *m, int form, P3 U, double alp
     cp.n = m->n_colors;
     for (int k = 0; k <= m->n_colors; ++k) cp.start[k] = m->color_ptr[k];
     const int gc = grid_for(nc, kBlock, 8192);
-    hipLaunchKernelGGL(k_cell_colors, dim3(gc), dim3(kBlock), 0, s, nc, cp, m->color_cells, a.color);
     const long long quads = (long long)n * a.w / 4;
     hipLaunchKernelGGL(k_slot_clear, dim3(grid_for(quads, kBlock, 8192)), dim3(kBlock), 0, s, quads,
-                       reinterpret_cast<int4 *>(a.slots));
+                       reinterpret_cast<int4 *>(a.slots), (nc + 3) / 4, reinterpret_cast<unsigned *>(a.color));
+    hipLaunchKernelGGL(k_cell_colors, dim3(gc), dim3(kBlock), 0, s, nc, cp, m->color_cells, a.color);
     hipLaunchKernelGGL(k_slot_fill<NV>, dim3(gc), dim3(kBlock), 0, s, nc, a.w, m->cells, m->vert2dof, a.color,
                        a.slots);
     hipLaunchKernelGGL(k_slot_pack, dim3(grid_for((long long)n * kWave, kBlock, 16384)), dim3(kBlock), 0, s, n, a.w,

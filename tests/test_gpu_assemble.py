@@ -87,3 +87,24 @@ def test_rows_out_of_column_order(oa):
     for form in (oa.FORM_MASS, oa.FORM_CONV):
         want = oa.assemble_p1(dm, pat, form, uab=u)[torch.as_tensor(back, device=pat.col_idx.device)]
         assert torch.equal(oa.assemble_p1(dm, rev, form, uab=u), want)
+
+
+def test_cells_that_no_class_lists_are_left_out(oa):
+    """A list that names one cell twice and another not at all: the first is
+    added once, the second not, and no slot beside the table is written."""
+    mesh = synth.channel(9, 9, 7)
+    say("assembly with a cell missing", mesh.name)
+    dm, pat, _ = device_mesh(mesh)
+    ref_mesh, _, _ = device_mesh(mesh)
+    two = dm.color_cells[:2].cpu().numpy()
+    dm.color_cells = dm.color_cells.clone()
+    dm.color_cells[0] = dm.color_cells[1]
+    one = oa.DeviceMesh(dm.dim, dm.coords, dm.cells[int(two[0])][None].contiguous(), dm.vert2dof, dm.n_dof,
+                        np.array([0, 1], np.int32), T([0], torch.int32))
+    uab = [T(v) for v in np.random.default_rng(7).normal(size=(3, mesh.n_dof))]
+    for form in (oa.FORM_MASS, oa.FORM_STIFF, oa.FORM_CONV):
+        whole = oa.assemble_p1(ref_mesh, pat, form, uab=uab).cpu().numpy()
+        lost = _colour_wise(oa, one, pat, form, uab, 1.0, None).cpu().numpy()
+        for _ in range(3):
+            got = oa.assemble_p1(dm, pat, form, uab=uab).cpu().numpy()
+            assert np.abs(got - (whole - lost)).max() <= 1e-14 * max(1.0, np.abs(whole).max())
