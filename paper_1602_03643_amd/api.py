@@ -190,10 +190,16 @@ def assemble_p1(mesh: DeviceMesh, pattern: DeviceCSR, form: int, uab=None, alpha
     lib, cm = _lib(), mesh.c()
     nb = C.c_size_t()
     Bp = None if B is None else C.byref(B)
+    ws = None
     if mesh.n_colors and lib.oasis_assemble_p1_workspace_size(C.byref(cm), C.byref(nb)) == L.OK:
-        # the workspace belongs to the stream that uses it
-        with torch.cuda.stream(stream):
-            ws = _workspace(nb.value, val.device)
+        # the workspace belongs to the stream that uses it; without room for
+        # it the colours are assembled one by one, which needs none
+        try:
+            with torch.cuda.stream(stream):
+                ws = _workspace(nb.value, val.device)
+        except torch.cuda.OutOfMemoryError:
+            pass
+    if ws is not None:
         rc = lib.oasis_assemble_p1_ws(_stream(stream), C.byref(cm), form, arr, float(alpha), Bp, C.byref(A), _p(ws),
                                       ws.numel())
     else:

@@ -108,3 +108,20 @@ def test_cells_that_no_class_lists_are_left_out(oa):
         for _ in range(3):
             got = oa.assemble_p1(dm, pat, form, uab=uab).cpu().numpy()
             assert np.abs(got - (whole - lost)).max() <= 1e-14 * max(1.0, np.abs(whole).max())
+
+
+def test_without_room_for_the_workspace(oa, monkeypatch):
+    """The call that had needed no memory still succeeds when there is none for
+    the rows' workspace: the colours one by one, bit for bit."""
+    from paper_1602_03643_amd import api
+    mesh = synth.channel(9, 9, 7)
+    say("assembly without memory", mesh.name)
+    dm, pat, _ = device_mesh(mesh)
+    uab = [T(v) for v in np.random.default_rng(7).normal(size=(3, mesh.n_dof))]
+    ref = _colour_wise(oa, dm, pat, oa.FORM_CONV, uab, 0.5, None)
+
+    def none(nbytes, device=None):
+        raise torch.cuda.OutOfMemoryError("none left")
+
+    monkeypatch.setattr(api, "_workspace", none)
+    assert torch.equal(oa.assemble_p1(dm, pat, oa.FORM_CONV, uab=uab, alpha=0.5), ref)
