@@ -194,6 +194,9 @@ def assemble_p1(mesh: DeviceMesh, pattern: DeviceCSR, form: int, uab=None, alpha
     if mesh.n_colors and lib.oasis_assemble_p1_workspace_size(C.byref(cm), C.byref(nb)) == L.OK:
         # the workspace belongs to the stream that uses it; without room for
         # it the colours are assembled one by one, which needs none
+        if stream is not None and not isinstance(stream, torch.cuda.Stream):
+            p = stream.cuda_stream
+            stream = torch.cuda.ExternalStream(p, device=val.device) if p else torch.cuda.default_stream(val.device)
         try:
             with torch.cuda.stream(stream):
                 ws = _workspace(nb.value, val.device)

@@ -125,3 +125,51 @@ def test_without_room_for_the_workspace(oa, monkeypatch):
 
     monkeypatch.setattr(api, "_workspace", none)
     assert torch.equal(oa.assemble_p1(dm, pat, oa.FORM_CONV, uab=uab, alpha=0.5), ref)
+
+
+def test_streams_of_other_kinds(oa):
+    """Any object with a cuda_stream is a stream, as in the other calls."""
+    mesh = synth.channel(9, 9, 7)
+    say("assembly on streams", mesh.name)
+    dm, pat, _ = device_mesh(mesh)
+    ref = oa.assemble_p1(dm, pat, oa.FORM_STIFF)
+    s = torch.cuda.Stream()
+
+    class Other:
+        def __init__(self, p):
+            self.cuda_stream = p
+
+    torch.cuda.synchronize()
+    for stream in (s, Other(s.cuda_stream), Other(0), torch.cuda.ExternalStream(s.cuda_stream), torch.cuda.default_stream()):
+        out = torch.zeros(pat.nnz, dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        oa.assemble_p1(dm, pat, oa.FORM_STIFF, out=out, stream=stream)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+
+
+def test_captured(oa):
+    """Under capture the workspace is the graph's; every replay gives the eager
+    bits on the velocity of its time, with eager work and synchronisations
+    between the replays."""
+    mesh = synth.channel(9, 9, 7)
+    say("assembly captured", mesh.name)
+    dm, pat, _ = device_mesh(mesh)
+    rng = np.random.default_rng(8)
+    uab = [T(v) for v in rng.normal(size=(3, mesh.n_dof))]
+    out = torch.zeros(pat.nnz, dtype=torch.float64, device="cuda")
+    oa.assemble_p1(dm, pat, oa.FORM_CONV, uab=uab, out=out)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        oa.assemble_p1(dm, pat, oa.FORM_CONV, uab=uab, out=out)
+    for _ in range(4):
+        for u in uab:
+            u.copy_(T(rng.normal(size=mesh.n_dof)))
+        ref = oa.assemble_p1(dm, pat, oa.FORM_CONV, uab=uab)
+        junk = [torch.full((50000,), 7, dtype=torch.int32, device="cuda") for _ in range(8)]
+        out.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref) and all(bool((j == 7).all()) for j in junk)
