@@ -410,7 +410,7 @@ struct BlockQueue {
 // round is a chain of seven dependent accesses.  (Blocks that colour what they
 // made ready themselves, without a launch in between, run out of cells while
 // a few have all of them: 35 us a step.)
-constexpr int kColorList = 512;   // 128 colours, and a cell may have all its vertices on one dof
+constexpr int kColorList = 128;   // the cells of a dof have colours of their own, at most 128
 
 // The cells of every dof in decreasing priority, in place of their codes; the
 // first one's turn.  A wave a dof.  Bits of *bad: 1 too many cells for 128
@@ -441,17 +441,16 @@ __global__ __launch_bounds__(kBlock) void k_color_sort(int ndof, const int *__re
         wave_lds_sync();
         for (int i = lane; i < n; i += kWave) {
             const int c = cell[wv][i], p = key[wv][i];
-            int r = 0, same = 0;
+            int r = 0;
             bool tie = false;
             for (int q = 0; q < n; ++q) {
-                const int cq = cell[wv][q], pq = key[wv][q];
-                r += pq > p || (pq == p && (cq < c || (cq == c && q < i))) ? 1 : 0;
-                tie |= pq == p && cq != c;
-                same += cq == c ? 1 : 0;
+                const int pq = key[wv][q];
+                r += pq > p || (pq == p && q < i) ? 1 : 0;
+                tie |= pq == p && q != i;
             }
             inc[b + r] = c;
             if (tie) atomicOr(bad, 2);
-            if (r == 0 && atomicAdd(&turns[c], same) + same == NV) ready.push(c);
+            if (r == 0 && atomicAdd(&turns[c], 1) + 1 == NV) ready.push(c);
         }
         wave_lds_sync();
     }
@@ -475,19 +474,13 @@ __global__ __launch_bounds__(kBlock) void k_color_round(const int *__restrict__ 
     BlockQueue ready(lds, next, size + 1);
     for (long long q = q0 + threadIdx.x / 4; q < m; q += static_cast<long long>(gridDim.x) * QUADS) {
         const int c = queue[q];
-        const int d = a < NV ? v2d[cells[static_cast<long long>(c) * NV + a]] : -1;
-        // vertices on one dof: the first of them acts
-        bool mine = a < NV;
-        for (int k = 0; k < NV - 1; ++k) {
-            const int other = __shfl(d, k, 4);
-            mine = mine && !(k < a && other == d);
-        }
         unsigned long long u0 = 0ull, u1 = 0ull;
-        int at = 0, e = 0;
-        if (mine) {
+        int d = 0, at = 0, e = 0;
+        if (a < NV) {
+            d = v2d[cells[static_cast<long long>(c) * NV + a]];
             u0 = used[2 * static_cast<long long>(d)];
             u1 = used[2 * static_cast<long long>(d) + 1];
-            at = head[d];
+            at = head[d] + 1;
             e = iptr[d + 1];
         }
         unsigned long long s0 = u0, s1 = u1;
@@ -503,22 +496,16 @@ __global__ __launch_bounds__(kBlock) void k_color_round(const int *__restrict__ 
         else if (a == 0)
             atomicOr(bad, 1);
         if (a == 0) color[c] = k;
-        if (!mine) continue;
+        if (a >= NV) continue;
         // no other cell of this round is on this dof
         if (k < 64)
             used[2 * static_cast<long long>(d)] = u0 | 1ull << k;
         else
             used[2 * static_cast<long long>(d) + 1] = u1 | 1ull << (k - 64);
-        int nx = -1, same = 0;
-        for (++at; at < e; ++at) {
-            nx = list[at];
-            if (nx != c) break;
-            nx = -1;
-        }
         head[d] = at;
-        if (nx < 0) continue;
-        for (int i = at; i < e && list[i] == nx; ++i) ++same;
-        if (atomicAdd(&turns[nx], same) + same == NV) ready.push(nx);
+        if (at == e) continue;
+        const int nx = list[at];
+        if (atomicAdd(&turns[nx], 1) + 1 == NV) ready.push(nx);
     }
     ready.flush();
 }

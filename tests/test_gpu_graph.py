@@ -92,3 +92,21 @@ def test_pattern_in_one_call_and_in_two(oa):
     assert L.load().oasis_p1_pattern(None, C.byref(cm), ptr(rp), ptr(ci), ci.numel(), C.byref(nnz), ptr(ws),
                                      ws.numel()) == 0
     assert torch.equal(rp, pat.row_ptr) and torch.equal(ci, pat.col_idx) and nnz.value == ci.numel()
+
+
+def test_cells_with_a_dof_twice_are_refused(oa):
+    """The kernels count on distinct dofs within a cell: pattern and colouring
+    refuse a mesh where two vertices of one share theirs, or an index is out of
+    range."""
+    import torch
+    mesh = synth.unit_square(3)
+    for v2d, code in ((np.minimum(mesh.vert2dof, mesh.n_dof - 5), oa.EUNSUPPORTED),
+                      (mesh.vert2dof + 1, oa.EINVAL), (mesh.vert2dof - 1, oa.EINVAL)):
+        dm = oa.DeviceMesh.from_arrays(2, mesh.coords, mesh.cells, v2d.astype(np.int32), mesh.n_dof, dev())
+        for call in (lambda: oa.p1_pattern(dm),
+                     lambda: oa.color_cells(dm, T(np.arange(mesh.n_cell), torch.int32))):
+            with pytest.raises(oa.OasisError) as e:
+                call()
+            assert e.value.code == code
+    dm = oa.DeviceMesh.from_arrays(2, mesh.coords, mesh.cells, mesh.vert2dof, mesh.n_dof, dev())
+    assert oa.p1_pattern(dm).n == mesh.n_dof
