@@ -255,8 +255,8 @@ typedef struct {
                              per-row offset lists of the ELL dictionary, -1 per-entry
                              16-bit ELL offsets, 0 CSR */
     int32_t coop_runs;    /* launches that did many iterations each (CG) or a whole solve
-                             (BiCGStab) on systems of up to 1024 rows per CU; 0: every
-                             iteration was launched */
+                             (BiCGStab, for maxit of 1 to 4096) on systems of up to 1024
+                             rows per CU; 0: every iteration was launched */
     int32_t coop_lost;    /* such launches that do not count: what they need was held by other
                              work for too long, or the matrix does not suit them; they were
                              repeated, or the solve went on with launched iterations (its

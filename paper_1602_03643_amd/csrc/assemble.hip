@@ -111,11 +111,11 @@ int assemble_colored(hipStream_t s, const oasis_mesh *m, const int *rp, const in
 //
 // The colours give every cell of a dof a slot of its own, so the dof -> cells
 // table is one scatter without atomics: slot k of dof d holds its cell of
-// colour k.  Each row then adds its cells' contributions in registers, in
-// ascending order of the cells, and writes each entry once.  The
-// colour launches instead touch every row's lines once per colour: on the
-// 97x97x73 channel 40 launches of 83 us (3.4 ms) moved some 8 GB; the table
-// takes 0.32 ms here and the rows 0.43.
+// colour k.  Each row then adds its cells' contributions in LDS, in ascending
+// order of the cells (in that of the colours where they are more than 64), and
+// writes each entry once.  The colour launches instead touch every row's lines
+// once per colour: on the 97x97x73 channel 40 launches of 83 us (3.4 ms) moved
+// some 8 GB; the table takes 0.32 ms here and the rows 0.30.
 
 // colour of every cell that a class lists; classes: the host's class starts,
 // by value

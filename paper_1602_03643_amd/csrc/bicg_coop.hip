@@ -33,12 +33,15 @@
 // sends nothing more, and the host puts the start iterate back before the solve
 // is begun again: blocks that got further may have moved their part of x.
 //
-// Per iteration with three right-hand sides in FP64: 199,680 rows 37 us
-// (product 9, halo 9, sums 14, scalars and updates 4, barriers; three kernels
-// of 42 and the read-backs before it: 75), 3264 rows 15 us.  The velocity
-// solve of a time step went from 1570 to 890 us on 199,680 rows, from 1040 to
-// 545 on 105,000, from 620 to 310 on 3264 and from 437 to 158 on the
-// 1089-row square.
+// The kernel's duration by its iterations, with three right-hand sides in FP64
+// (kernel trace; the set-up of its columns and the confirmations are in it):
+// 199,680 rows 39 us of 64 iterations (product 9, halo 9, sums 14, scalars and
+// updates 4, barriers; three kernels of 42 and the read-backs before it: 75),
+// 3264 rows 17 us of 25; with one right-hand side 17 and 11.5.  The velocity
+// phase of a time step whose iteration cap lets it come here (kCoopRun) went
+// from 1650 to 900 us on 199,680 rows, from 1110 to 540 on 105,000, from 670 to 300
+// on 3264 (the first of two solves), and from 460 to 146 on the 1089-row
+// square.
 // Nine sums by one exchange of lanes (coop.hpp's wave_sums) took 3.5 us of an
 // iteration where nine wave sums took 7; vector words by right-hand side, not
 // by row, 8 us where rows of three took 17; the scalars in lane k, not in all,
@@ -597,8 +600,10 @@ template <typename T>
 int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const *b, T *const *x, double rtol, int maxit,
                     BiWork<T> &w, SolveOut *out, bool inner, int *lost) {
     // one row per thread of one block per CU; a kernel and grid that the
-    // caller asked for are left as they are.  An iteration takes 10-20 us:
-    // kCoopRun of them bound a launch that does not converge.
+    // caller asked for are left as they are.  An iteration takes 11 to 40 us:
+    // kCoopRun of them bound a launch that does not converge to 0.16 s.  A
+    // higher cap, the entry points' default of 10000 among them, takes the
+    // launched form from the start: a solve is not handed over in the middle.
     if (!w.cols.any() || !w.eval || !w.tun.ell() || !w.tun.grid_auto || n > kCoopMaxRows ||
         maxit > kCoopRun)
         return OASIS_EUNSUPPORTED;

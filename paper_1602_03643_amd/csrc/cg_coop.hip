@@ -6,7 +6,7 @@
 // took 20 us in k_cg_p1_ell (12 us) and k_cg_p2 (6.4 us) and the gaps
 // between them, against about 4 us that its 33 MB need at the cache rates; on the
 // 1089-row Taylor-Green square each launch took 3.9 us for no work at all.
-// Here a cooperative grid of 1024-thread blocks, one per CU, keeps the
+// Here a grid of blocks of up to 1024 threads, at most one per CU, keeps the
 // matrix (values and local column indices) and the CG vectors in registers
 // and each block's part of the direction, with the neighbours' entries it
 // gathers, in LDS.  The recurrences are those of k_cg_p1 / k_cg_p2.
@@ -34,11 +34,12 @@
 //
 // Every wait is bounded by the clock (coop.hpp).
 //
-// Per iteration, before and now: 65x65x49 FP64 20.0 -> 5.7 us (256 blocks,
-// 780 rows each: about 1.7 us for each exchange, 0.4 us for the product, the
-// rest block reductions, barriers and two divisions), FP32 with the null
-// vector 12 -> 6.2 us, 33x33x25 FP32 9.5 -> 4.7 us, 17x17x13 FP64 12 -> 3.8
-// us, the 1089-row square 8 -> 3.3 us, and by one block (k_cg_one) 2.7 us.
+// Per iteration, the kernel's duration by the iterations it ran (kernel trace),
+// before and now: 65x65x49 FP64 20.0 -> 5.8 us (256 blocks, 780 rows each:
+// about 1.7 us for each exchange, 0.4 us for the product, the rest block
+// reductions, barriers and two divisions), FP32 with the null vector 12 -> 6.1
+// us, 33x33x25 FP32 9.5 -> 5.0 us, 17x17x13 FP64 12 -> 4.0 us, a square of 2116
+// rows 3.6 us, and by one block (k_cg_one) the one of 1089 rows 8 -> 2.5 us.
 #include <algorithm>
 
 #include "coop.hpp"
@@ -311,9 +312,9 @@ __global__ __launch_bounds__(BS) void k_cg_coop(CoopArgs a) {
 
 // The same run by one block, R rows a thread, for systems that fit it: what
 // the blocks exchange lies in LDS, and an iteration is two block sums and
-// three barriers.  1089 rows of 7 entries, FP64: 3.7 us an iteration by five
-// blocks, 2.7 by one (3.5 with the padding's gathers); the limit is the
-// registers of two rows.
+// three barriers.  1089 rows of 7 entries, FP64: an iteration took 3.7 us of a
+// solve by five blocks, 2.7 by one (3.5 with the padding's gathers); the limit
+// is the registers of two rows.
 constexpr int kOneThreads = 1024, kOneRows = 2;
 template <typename T, int R>
 __global__ __launch_bounds__(kOneThreads) void k_cg_one(CoopArgs a) {

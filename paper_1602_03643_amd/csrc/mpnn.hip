@@ -509,7 +509,7 @@ __global__ __launch_bounds__(kBlock) void k_mp_layer(int n, int l, const int *__
 // g_delta wd; partials of the loss (mean squared error only), g_wd, g_cd
 // Half a wave works on a node, lane o on feature o, so that G and H3 move in
 // 128- and 64-byte rows; kRowsAhead nodes' loads are issued together (one
-// node per thread, feature by feature, took 33 us on 200,000 nodes; 14 us).
+// node per thread, feature by feature, took 33 us on 200,000 nodes; 15 us).
 // The scalar sums are taken by kDecBlocks blocks of kBlock threads in one
 // order that does not depend on the launch: with the K-norm loss g_cd is the
 // sum of K e, zero but for its rounding, and a first Adam step takes that
@@ -809,7 +809,7 @@ __global__ __launch_bounds__(kWideBlock) void k_mp_bwd_enc(int n, const float *_
     const int o = threadIdx.x & (kHid - 1);
     float gw[kIn], gc = 0.f;
     for (int k = 0; k < kIn; ++k) gw[k] = 0.f;
-    // kEncAhead nodes' loads issued together (one at a time: 59 us on 200,000 nodes; 17 us)
+    // kEncAhead nodes' loads issued together (one at a time: 59 us on 200,000 nodes; 16 us)
     constexpr int kEncAhead = 4;
     const long long step = (long long)gridDim.x * (kWideBlock / kHid);
     for (long long i0 = blockIdx.x * (long long)(kWideBlock / kHid) + threadIdx.x / kHid; i0 < n; i0 += kEncAhead * step) {
@@ -853,7 +853,7 @@ __global__ __launch_bounds__(kWideBlock) void k_mp_bwd_enc(int n, const float *_
 
 // grad[p] = sum over blocks of gpart[b][p] (fixed order); loss.  A block sums
 // kHid parameters, kRedRows rows of threads each a part of the partials,
-// whose loads are in flight together (one thread per parameter: 62 us; 9 us).
+// whose loads are in flight together (one thread per parameter: 62 us; 6 us).
 // The last block has the decoder's bias alone, summed in block order.
 constexpr int kRedRows = kWideBlock / kHid;
 __global__ __launch_bounds__(kWideBlock) void k_mp_grad_reduce(const float *__restrict__ gpart, int nb, float *grad,
