@@ -219,7 +219,9 @@ typedef struct {
                              0.1).  BiCGStab: inner tolerance of each refinement step
                              (0 = 1e-4; tightened automatically for the last step) */
     int32_t max_outer;    /* F32 mode BiCGStab: cap on refinement steps (0 = 50) */
-    int32_t check_every;  /* iterations launched between host convergence polls (0 = auto) */
+    int32_t check_every;  /* iterations launched between host convergence polls (0 = auto;
+                             cooperative runs, which test every residual themselves: at
+                             least 16) */
     int32_t flags;        /* OASIS_KRYLOV_TIME, OASIS_KRYLOV_NULLSPACE_CONST */
     oasis_tuning tuning;
 } oasis_krylov_opts;

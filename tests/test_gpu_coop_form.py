@@ -244,3 +244,20 @@ def test_timed_launches_are_those_of_the_header(oa, precision):
     assert runs > 0 and two[1] == single[1] == 0
     assert not 0.75 <= other / want <= 1.25
     assert abs(us / want - 1) <= 0.2
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("check", [1, 4, 16, 40])
+def test_polls_of_cooperative_runs(oa, check, precision):
+    """However often the caller asks for polls, a run is not cut into pieces of
+    fewer than 16 iterations, and the result is that without polls, bit for
+    bit."""
+    mesh = synth.channel(17, 17, 13)
+    say("polls", mesh.name, check, precision)
+    A, H, b = _spd(oa, mesh, 9)
+    prec = oa.F64 if precision == "f64" else oa.F32
+    x, y = (torch.zeros(mesh.n_dof, dtype=torch.float64, device="cuda") for _ in range(2))
+    one = oa.pcg(A, T(b), x, rtol=RTOL, precision=prec)
+    st = oa.pcg(A, T(b), y, rtol=RTOL, precision=prec, check_every=check)
+    assert torch.equal(x, y) and st["iters"] == one["iters"] and st["coop_lost"] == 0
+    assert one["coop_runs"] <= st["coop_runs"] <= one["coop_runs"] + st["iters"] // max(check, 16)
