@@ -105,6 +105,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
     // a wait of a sum, of a product, was lost: two, so that a wave still at the
     // test of one cannot see what a wave ahead of it sets in the next
     __shared__ int quit[2];
+    constexpr int kTold = 1, kRanOut = 2;         // by the flag; by the clock
     const int t = threadIdx.x, wv = t / kWave, wl = t & (kWave - 1);
     const int nb = gridDim.x, bid = blockIdx.x;
     const int r0 = bid * a.rows, r1 = min(a.n, r0 + a.rows);
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
     // of them ran out
     int waits = 0;
     auto ended = [&](int kind) -> bool {
-        if (++waits == a.lose && bid == nb - 1 && t == 0) quit[kind] = 1;
+        if (++waits == a.lose && bid == nb - 1 && t == 0) quit[kind] = kRanOut;
         __syncthreads();
         return __builtin_amdgcn_readfirstlane(quit[kind]) == 0;
     };
@@ -142,9 +143,10 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
         const unsigned began = static_cast<unsigned>(wall_clock64()), most = waits == 0 ? a.join : kCoopTicks;
         int k = 0;
         while (again()) {
-            if ((++k & 63) == 0 && (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopLate ||
-                                    static_cast<unsigned>(wall_clock64()) - began > most)) {
-                quit[kind] = 1;
+            if ((++k & 63) != 0) continue;
+            const bool told = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kCoopLate;
+            if (told || static_cast<unsigned>(wall_clock64()) - began > most) {
+                quit[kind] = told ? kTold : kRanOut;
                 return;
             }
         }
@@ -541,7 +543,8 @@ __global__ __launch_bounds__(BS) void k_bi_coop(BiCoopArgs a) {
         step = kP;
     }
     if (quit[0] | quit[1]) {
-        if (t == 0) atomicMax(flag, kCoopLost);
+        // (a block that was told leaves the flag as it is)
+        if (t == 0 && ((quit[0] | quit[1]) & kRanOut)) atomicMax(flag, waits == 1 ? kCoopLate : kCoopLost);
         return;
     }
     if (bid == 0 && t == 0) {
@@ -661,7 +664,8 @@ int bicg_coop_solve(hipStream_t s, int n, int nrhs, const T *wgt, const T *const
             w.coop.never = true;
             return OASIS_EUNSUPPORTED;
         }
-        if (attempt + 1 == kCoopTries) {
+        // (a wait of 2 s is not taken twice over)
+        if (attempt + 1 >= (h.glob.pause == kCoopLate ? kCoopTries : 2)) {
             w.coop.gave_up();
             return OASIS_EUNSUPPORTED;
         }
